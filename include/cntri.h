@@ -227,7 +227,13 @@ cn_status cn_step(cn_handle_t handle, const cn_layout* layout, const cn_operator
  * K tile joints fill more than half of a whole-system tile of 2 rows per lane of the pass's
  * workgroup (64 W < K <= 128 W), the pass's last workgroup also solves that reduced system, so
  * a step is one launch (CN_INLINE=0 turns this off).  The result equals the chain of cn_step
- * calls up to rounding (not bit for bit); CN_FUSE=0 in the environment turns the fusion off. */
+ * calls up to rounding (not bit for bit); CN_FUSE=0 in the environment turns the fusion off.
+ * Real potentials on uniform batches of unit element stride with one dx and the automatic
+ * partition run on independent windows instead where that is faster (off-diagonals kappa up to
+ * about 4): a window of up to 4096 rows, cut off from its line, takes up to 128 steps in one
+ * launch with its rows in registers, and only its rows beyond the reach of the cut (below 2^-70
+ * of the state for any real potential) are stored.  A non-finite value makes its whole line
+ * non-finite, as in single steps.  CN_WINDOWS=0 in the environment turns the windows off. */
 cn_status cn_propagate(cn_handle_t handle, const cn_layout* layout, const cn_operator* op,
                        int64_t nsteps, const double* E, void* psi, void* ckpt, int64_t K,
                        cn_stream_t stream);
@@ -256,7 +262,10 @@ cn_status cn_propagate(cn_handle_t handle, const cn_layout* layout, const cn_ope
  * is set; then cn_propagate is the call.  The workgroups wait on each other: a launch that runs
  * beside other work on the same GPU (another stream, another resident propagation) may find
  * some of its workgroups unable to start; then the waits give up after a bound, the state is
- * left unspecified and cn_get_status returns CN_ERR_WAIT_TIMEOUT.  Enqueued on stream. */
+ * left unspecified and cn_get_status returns CN_ERR_WAIT_TIMEOUT.  Systems that cn_propagate
+ * runs on windows take those launches here as well where their steps are the faster ones (a real
+ * potential, partition 0, no poll bound in CN_RESIDENT_SPIN): their workgroups wait for nobody.
+ * Enqueued on stream. */
 cn_status cn_propagate_resident(cn_handle_t handle, const cn_layout* layout,
                                 const cn_operator* op, int64_t nsteps, const double* E,
                                 void* psi, void* ckpt, int64_t K, cn_stream_t stream);
@@ -307,7 +316,10 @@ cn_status cn_radial_step(cn_handle_t handle, const cn_radial* op, double E, cons
  * second workspace (allocated on first use).  The results are the same in either form; the
  * call is ordered on the caller's stream as usual.  Under graph capture the segments run one
  * after the other on the caller's stream, as the same fused chain when the second workspace
- * exists (cn_reserve, or an earlier call), else one step at a time (equal up to rounding). */
+ * exists (cn_reserve, or an earlier call), else one step at a time (equal up to rounding).
+ * Where cn_propagate runs on windows, so does the reverse mode: the states of a segment are
+ * rebuilt backwards from the next checkpoint beside the recursion (the last segment's end is
+ * stepped forward from its own checkpoint), both in the same launches. */
 cn_status cn_propagate_adjoint(cn_handle_t handle, const cn_layout* layout,
                                const cn_operator* op, int64_t nsteps, const double* E,
                                const void* ckpt, int64_t K, void* seg, void* g,

@@ -4,6 +4,7 @@
 
 #include <algorithm>
 #include <climits>
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -17,6 +18,7 @@
 #include "../../include/cntri.h"
 #include "kern_table.hpp"
 #include "nshaped_kernels.hpp"
+#include "nshaped_windows.hpp"
 
 using nsd::cd;
 using nsd::KArgs;
@@ -36,6 +38,8 @@ nsk::Tables& nsk::tables() {
     reg_mrhs(x);
     reg_aux(x);
     reg_resident(x);
+    reg_windows(x);
+    reg_windows_grad(x);
     return x;
   }();
   return t;
@@ -200,6 +204,8 @@ struct Plan {
   int64_t o_part = -1;  // workspace for per-block partial sums
   int64_t nparts = 0;
   int64_t ntiles1 = 0;  // level-1 tiles of a uniform CN plan (partial sums of the adjoint)
+  int64_t t_bad = -1;   // tables: marks of the window launches, one int per system, zero between
+                        // calls (uniform CN plans of unit stride)
   std::vector<char> host_tab;  // no-allocation plans: the tables, copied into scratch per call
   ~Plan() {
     if (tables) (void)hipFree(tables);
@@ -701,6 +707,134 @@ void plan_level(Builder& B, std::vector<Launch>& L, const BatchDesc& bd, int src
 
 }  // namespace
 
+// ------------------------------------------------------------------------------ windows
+namespace {
+
+// sequences of steps on independent windows (k_window; CN_WINDOWS=0 turns them off)
+bool windows_enabled() {
+  static const bool on = [] {
+    const char* e = getenv("CN_WINDOWS");
+    return !(e && e[0] == '0');
+  }();
+  return on;
+}
+
+// Minimum of f over eta in (0, hi) by golden-section search (f has one minimum there).
+template <typename F>
+double min_over(double hi, const F& f) {
+  const double g = 0.6180339887498949;
+  double a = 0.0, b = hi, x1 = b - g * (b - a), x2 = a + g * (b - a), f1 = f(x1), f2 = f(x2);
+  for (int i = 0; i < 48; ++i) {
+    if (f1 < f2) {
+      b = x2;
+      x2 = x1;
+      f2 = f1;
+      x1 = b - g * (b - a);
+      f1 = f(x1);
+    } else {
+      a = x1;
+      x1 = x2;
+      f1 = f2;
+      x2 = a + g * (b - a);
+      f2 = f(x2);
+    }
+  }
+  return std::min(f1, f2);
+}
+double eta_max(double kap) { return kap > 0.0 ? std::min(8.0, std::asinh(0.5 / kap)) : 8.0; }
+
+// Rows that a cut of the line has to stay away after s steps (nshaped_windows.hpp): the smallest
+// D with r^s exp(-eta D) / (2 sinh eta) <= 2^-70 for some eta.
+double window_halo(double kap, int64_t s) {
+  return std::ceil(min_over(eta_max(kap), [&](double e) {
+    const double th = std::min(2.0 * kap * std::sinh(e), 1.0 - 1e-12);
+    return (70.0 * M_LN2 + (double)s * std::log((1.0 + th) / (1.0 - th)) -
+            std::log(2.0 * std::sinh(e))) / e;
+  })) + 1.0;
+}
+// Levels of lane blocks of M rows whose reduced systems are diagonal to 2^-66: the coupling
+// kappa^2 (T^-1)_{1,m} of two joint lines B = M * 2^levels rows apart against a diagonal of real
+// part at least 1.  More than 6 levels would leave the wavefront: -1.
+int window_levels(double kap, int M) {
+  for (int lv = nsk::kWinLevelMin; lv < nsk::kWinLevelMin + nsk::kNumWinLevel; ++lv) {
+    const double B = (double)(M << lv);
+    const double c = min_over(eta_max(kap), [&](double e) {
+      const double th = std::min(2.0 * kap * std::sinh(e), 1.0 - 1e-12);
+      return 2.0 * std::log(std::max(kap, 1e-30)) - e * (B - 2.0) - std::log(1.0 - th);
+    });
+    if (c <= -66.0 * M_LN2) return lv;
+  }
+  return -1;
+}
+
+// A piece of a sequence in launches of at most s steps each.
+struct WinPlan {
+  int cfg = -1, lv = 0;
+  int64_t s = 0, nwin = 0, vr = 0, halo = 0;
+  double us = 0.0;  // estimated time per step
+};
+
+// The windows for pieces of m steps of `batch` systems of n rows: the window size and the steps
+// per launch of the smallest estimated time.  More steps in a launch share its read and write of
+// the state, but need wider halos, whose rows are computed twice.  nr = 2: state and gradient.
+// The estimate, in microseconds: a launch 5 plus its bytes at 4.5 TB/s, and a step of q wavefronts
+// on a SIMD  t0 + q t1, fitted to launches of 8 to 64 steps over 2^16, 2^20, 2^22 and 2^24 rows
+// (with 8 rows per lane and no field, 1.4 us at q = 1, 22 at q = 34).
+WinPlan window_plan(int64_t n, int64_t batch, double kap, int64_t m, int nr, bool field) {
+  WinPlan best;
+  if (!(kap >= 1e-60) || !std::isfinite(kap)) return best;  // the rows are divided by kappa
+  for (int ci = 0; ci < nsk::kNumWinCfg; ++ci) {
+    const Cfg cfg = nsk::kWinCfgs[nr - 1][ci];
+    const int64_t W = cfg.W, T = cfg.T();
+    int lv = window_levels(kap, cfg.M);
+    // one wavefront that holds the whole system runs all its levels: any off-diagonal
+    if (lv < 0 && W == 1 && n <= T) lv = nsk::kWinLevelMin + nsk::kNumWinLevel - 1;
+    if (lv < 0) continue;
+    double t0, t1;
+    if (nr == 1) {
+      t0 = cfg.M == 8 ? (field ? 0.85 : 0.70) : (field ? 1.15 : 0.90);
+      t1 = cfg.M == 8 ? (field ? 1.40 : 0.66) : (field ? 1.00 : 0.54);
+    } else {
+      t0 = cfg.M == 6 ? (field ? 1.70 : 1.20) : (field ? 1.50 : 1.20);
+      t1 = cfg.M == 6 ? (field ? 2.15 : 1.40) : (field ? 1.95 : 1.28);
+    }
+    int64_t last = 0;
+    for (int64_t c = 1; c <= nsd::kWinSteps; c *= 2) {
+      int64_t s = std::min(c, m);
+      const int64_t nl = (m + s - 1) / s;  // launches; equal shares
+      s = (m + nl - 1) / nl;
+      if (s == last) continue;
+      last = s;
+      int64_t nwin = 1, vr = T, halo = 0;
+      if (n > T) {
+        const double hd = window_halo(kap, s);
+        if (hd > (double)(3 * T / 8)) continue;
+        halo = (int64_t)hd;
+        vr = T - 2 * halo;
+        nwin = (n - 2 * halo + vr - 1) / vr;
+      }
+      const double nwg = (double)batch * (double)nwin;
+      if (nwg > 2147483647.0) continue;
+      const double rows = (double)n * (double)batch;
+      const double mem = (nwg * (double)T * (16.0 * nr + 8.0) + rows * 16.0 * nr) / 4.5e6;
+      const double q = std::ceil(nwg / (W < 4 ? 1024.0 / (double)W : 256.0)) * (W < 4 ? 1 : W / 4);
+      const double us = (5.0 + mem) / (double)s + t0 + q * t1;
+      if (best.cfg < 0 || us < best.us) {
+        best.cfg = ci;
+        best.lv = lv;
+        best.s = s;
+        best.nwin = nwin;
+        best.vr = vr;
+        best.halo = halo;
+        best.us = us;
+      }
+    }
+  }
+  return best;
+}
+
+}  // namespace
+
 // ------------------------------------------------------------------------------- handle
 struct cn_handle_s {
   int device = 0;
@@ -743,6 +877,8 @@ struct cn_handle_s {
   // resident propagation: slots, edge rows and joint values of its tiles, then the field
   void* res = nullptr;
   size_t res_size = 0;
+  // window launches chosen for (rows, batch, off-diagonal, steps, right-hand sides)
+  std::map<std::string, WinPlan> windows;
   // plan log (cn_profile): HIP events around every launch of run_plan, with a label each
   bool profiling = false;
   struct Rec {
@@ -910,6 +1046,10 @@ cn_status build_plan(const cn_layout* L, int src, bool adjoint_ws, Plan& P,
     for (const Launch& l : P.L)
       if (l.level == 1 && (l.ph == nsd::PH_SINGLE || l.ph == nsd::PH_SUBST))
         P.ntiles1 = l.a.nitems > 0 ? (int64_t)l.a.nitems : (int64_t)l.grid.x * l.grid.y;
+    if (src == nsd::SRC_CN && !L->offsets && L->elem_stride == 1) {
+      const std::vector<int> zero(L->batch, 0);
+      P.t_bad = B.add_tab(zero.data(), zero.size() * sizeof(int));
+    }
   }
   P.ws_bytes = B.ws;
   P.desc = B.desc;
@@ -1481,6 +1621,254 @@ UserArgs cn_args(const cn_operator* op, double E, const cd* in, cd* out) {
   return u;
 }
 
+// ------------------------------------------------------------------ sequences on windows
+// The window plan for pieces of m steps, or cfg < 0 when the sequence is not taken on windows:
+// a real potential, one dx, uniform batches of unit element stride, the automatic partition, and
+// an off-diagonal for which the estimate beats the chained passes.  Those take per step about
+// 16 us of launches, or 6 us where one tile holds the system, plus the state and potential once
+// at 4 TB/s (48 and 40 bytes per row).
+WinPlan sequence_windows(cn_handle_t h, const cn_layout* L, const cn_operator* op, const Plan* P,
+                         int64_t m, int nr, bool field) {
+  WinPlan none;
+  if (!windows_enabled() || !fuse_enabled() || P->t_bad < 0 || L->offsets || L->elem_stride != 1 ||
+      L->partition || L->rows_per_thread || L->levels || op->absorb || op->dx_per_system || m < 1)
+    return none;
+  const double kap = std::fabs(0.5 * op->dt * 0.5 * (1.0 / (op->dx * op->dx)));
+  char key[128];
+  snprintf(key, sizeof(key), "%lld|%lld|%a|%lld|%d|%d", (long long)L->n, (long long)L->batch, kap,
+           (long long)m, nr, field ? 1 : 0);
+  auto it = h->windows.find(key);
+  if (it == h->windows.end()) {
+    if (h->windows.size() >= 256) h->windows.clear();
+    WinPlan w = window_plan(L->n, L->batch, kap, m, nr, field);
+    const double rows = (double)L->n * (double)L->batch;
+    const double chain = nr * (L->n > kSingleMax ? 16.0 + rows * 48.0 / 4.0e6
+                                                 : 6.0 + rows * 40.0 / 4.0e6);
+    if (w.cfg >= 0 && w.us > chain) w = none;
+    if (log_enabled())
+      fprintf(stderr, "cntri: windows of n=%lld batch=%lld kappa=%g steps=%lld: T=%lld levels=%d "
+              "s=%lld windows=%lld halo=%lld, %.2f us per step\n", (long long)L->n,
+              (long long)L->batch, kap, (long long)m,
+              w.cfg < 0 ? 0LL : (long long)nsk::kWinCfgs[nr - 1][w.cfg].T(), w.lv, (long long)w.s,
+              (long long)w.nwin, (long long)w.halo, w.us);
+    it = h->windows.emplace(key, w).first;
+  }
+  return it->second;
+}
+
+// One launch of nst steps on the windows of w.  in, out: state (and gradient, with nr = 2) and
+// the elements between their systems; E: the fields of the steps, or null.
+struct WinIo {
+  const cd* in = nullptr;
+  cd* out = nullptr;
+  int64_t ibs = 0, obs = 0;
+};
+nsd::WinArgs window_args(cn_handle_t h, const Plan* P, const cn_layout* L, const cn_operator* op,
+                         const WinPlan& w, double dt) {
+  nsd::WinArgs a{};
+  a.V = op->V;
+  a.xg = op->xgrid;
+  a.vbs = L->shared_coefficients ? 0 : L->batch_stride;
+  a.n = L->n;
+  a.nwin = w.nwin;
+  a.vr = w.vr;
+  a.halo = w.halo;
+  a.vscale = op->v_scale;
+  a.tau = 0.5 * dt;
+  a.idx2 = 1.0 / (op->dx * op->dx);
+  a.kap = (0.5 * dt) * 0.5 * a.idx2;
+  a.status = h->status;
+  a.bad = (int*)((char*)P->tables + P->t_bad);
+  return a;
+}
+cn_status launch_window(nsd::WinArgs& a, const WinPlan& w, int64_t batch, int nr,
+                        const WinIo* io, int64_t nst, bool xg, hipStream_t s) {
+  for (int r = 0; r < nr; ++r) {
+    a.in[r] = io[r].in;
+    a.out[r] = io[r].out;
+    a.ibs[r] = io[r].ibs;
+    a.obs[r] = io[r].obs;
+  }
+  a.nst = (int)nst;
+  const void* fn = nsk::tables().win[nr - 1][w.cfg][w.lv - nsk::kWinLevelMin][xg ? 1 : 0];
+  void* params[] = {&a};
+  if (hipLaunchKernel(fn, dim3((unsigned)(w.nwin * batch)), dim3(64 * nsk::kWinCfgs[nr - 1][w.cfg].W),
+                      params, 0, s) != hipSuccess)
+    return CN_ERR_HIP;
+  return CN_OK;
+}
+// The end of a sequence on windows: the lines of systems with a mark become NaN, the marks zero.
+cn_status launch_window_end(const nsd::WinArgs& a, int64_t batch, const WinIo* out, double* dV,
+                            hipStream_t s) {
+  nsd::WinEnd e{};
+  e.bad = a.bad;
+  e.n = a.n;
+  for (int r = 0; r < 2; ++r) {
+    e.x[r] = out[r].out;
+    e.bs[r] = out[r].obs;
+  }
+  e.dV = dV;
+  e.vbs = a.vbs;
+  void* params[] = {&e};
+  if (hipLaunchKernel(aux_fn(nsk::AUX_WINDOW_END), dim3((unsigned)batch), dim3(256), params, 0,
+                      s) != hipSuccess)
+    return CN_ERR_HIP;
+  return CN_OK;
+}
+
+// m steps (fields E[0 .. m-1], or null) from `in` to `dst` as nl launches of equal shares, through
+// `other` in between: counted back from the end, dst, other, dst, ...; no launch reads the buffer
+// that it writes, so `in` is neither dst nor (of an even count) other, or the systems have one
+// window each.  pitch(p): the elements between the systems of a buffer.
+template <typename Pitch>
+cn_status window_piece(nsd::WinArgs& a, const WinPlan& w, int64_t batch, const cd* in, cd* dst,
+                       cd* other, int64_t m, int64_t nl, const double* E, const Pitch& pitch,
+                       hipStream_t s) {
+  int64_t k = 0;
+  for (int64_t i = 0; i < nl; ++i) {
+    const int64_t k1 = m * (i + 1) / nl;
+    WinIo io[1];
+    io[0].in = in;
+    io[0].out = ((nl - 1 - i) % 2 == 1 && w.nwin > 1) ? other : dst;
+    io[0].ibs = pitch(in);
+    io[0].obs = pitch(io[0].out);
+    for (int64_t j = k; j < k1; ++j) a.E[j - k] = E ? E[j] : 0.0;
+    const cn_status st = launch_window(a, w, batch, 1, io, k1 - k, E != nullptr, s);
+    if (st != CN_OK) return st;
+    a.later = 1;
+    in = io[0].out;
+    k = k1;
+  }
+  return CN_OK;
+}
+
+// The systems of p (batch stride bs) back to back in tmp.
+cn_status gather_systems(cd* tmp, const cd* p, const cn_layout* L, hipStream_t s) {
+  const size_t w = (size_t)L->n * sizeof(cd);
+  if (L->batch == 1 || L->batch_stride == L->n)
+    HIP_TRY(hipMemcpyAsync(tmp, p, w * L->batch, hipMemcpyDeviceToDevice, s));
+  else
+    HIP_TRY(hipMemcpy2DAsync(tmp, w, p, (size_t)L->batch_stride * sizeof(cd), w, L->batch,
+                             hipMemcpyDeviceToDevice, s));
+  return CN_OK;
+}
+
+// nsteps steps in place on psi (and checkpoints, as cn_propagate) as launches on windows.  The
+// state alternates between psi and the plan's spare state vector, and passes through the
+// checkpoints themselves where a launch ends on one.
+cn_status run_windows(cn_handle_t h, const Plan* P, const cn_layout* L, const cn_operator* op,
+                      const WinPlan& w, int64_t nsteps, const double* E, cd* psi, cd* ckpt,
+                      int64_t K, hipStream_t s) {
+  cd* tmp = (cd*)((char*)h->ws + P->o_aux);
+  auto pitch = [&](const cd* p) { return p == tmp ? L->n : L->batch_stride; };
+  if (!op->xgrid) E = nullptr;
+  nsd::WinArgs a = window_args(h, P, L, op, w, op->dt);
+  cn_status st;
+  const cd* cur = psi;
+  if (ckpt) {
+    HIP_TRY(hipMemcpyAsync(ckpt, psi, P->span * sizeof(cd), hipMemcpyDeviceToDevice, s));
+    cur = ckpt;
+  }
+  for (int64_t k = 0; k < nsteps;) {
+    // the piece up to the next checkpoint or the end
+    const int64_t kend = ckpt ? std::min(nsteps, (k / K + 1) * K) : nsteps, m = kend - k;
+    int64_t nl = (m + w.s - 1) / w.s;
+    cd* dst = kend == nsteps ? psi : ckpt + (kend / K) * P->span;
+    if (w.nwin > 1 && cur == dst && nl % 2 == 1) {
+      // the state starts in the buffer that it has to end in: one more launch, or a copy
+      if (m > nl) {
+        ++nl;
+      } else {
+        if ((st = gather_systems(tmp, cur, L, s)) != CN_OK) return st;
+        cur = tmp;
+      }
+    }
+    if ((st = window_piece(a, w, L->batch, cur, dst, tmp, m, nl, E ? E + k : nullptr, pitch,
+                           s)) != CN_OK)
+      return st;
+    cur = dst;
+    k = kend;
+  }
+  WinIo e[2];
+  e[0].out = psi;
+  e[0].obs = L->batch_stride;
+  return launch_window_end(a, L->batch, e, nullptr, s);
+}
+
+// The reverse mode (propagate_adjoint_impl) on windows: state and gradient go backwards together,
+// since a backward step of either is a Crank-Nicolson step with dt -> -dt, the same matrix for
+// both, and y = T^-H g is lambda itself.  The states are rebuilt from the segments' ends: the next
+// checkpoint (the last segment's is stepped forward from its own), or psi_T alone.  S[0], S[1]:
+// two states of scratch.  part: rows of w.nwin * batch * wavefronts values, one per step of a
+// segment.
+cn_status run_windows_adjoint(cn_handle_t h, const Plan* P, const cn_layout* L,
+                              const cn_operator* op, const WinPlan& w, const WinPlan& w1,
+                              int64_t nsteps, const double* E, const cd* ckpt, const cd* psi_T,
+                              int64_t K, cd* const (&S)[2], cd* g, double* dV, double* dE,
+                              double* part, hipStream_t s) {
+  cd* tmp = (cd*)((char*)h->ws + P->o_aux);
+  auto pitch = [&](const cd* p) { return p == tmp ? L->n : L->batch_stride; };
+  if (!op->xgrid) E = nullptr;
+  const int64_t nseg = (nsteps + K - 1) / K, span = P->span;
+  const int64_t nparts = w.nwin * L->batch * nsk::kWinCfgs[1][w.cfg].W;
+  cn_status st;
+  const cd* psi = psi_T;
+  nsd::WinArgs a = window_args(h, P, L, op, w, -op->dt);
+  if (ckpt) {
+    const int64_t k0 = (nseg - 1) * K, m = nsteps - k0;
+    nsd::WinArgs f = window_args(h, P, L, op, w1, op->dt);
+    if ((st = window_piece(f, w1, L->batch, ckpt + (nseg - 1) * span, S[0], S[1], m,
+                           (m + w1.s - 1) / w1.s, E ? E + k0 : nullptr, pitch, s)) != CN_OK)
+      return st;
+    psi = S[0];
+    a.later = 1;
+  }
+  a.dV = dV;
+  a.acc_dV = op->v_scale * op->dt;
+  // the kernel's terms carry -(tau / kappa) x = -2 dx^2 x
+  a.acc_dE = -0.5 * op->dt * a.idx2;
+  a.nparts = -nparts;  // steps go backwards through a segment's rows
+  const bool xg = E || dE;
+  auto launches = [&](int64_t sg) {
+    const int64_t m = std::min(nsteps, (sg + 1) * K) - sg * K;
+    return (m + w.s - 1) / w.s;
+  };
+  cd* cur = g;
+  if (w.nwin > 1 && (launches(nseg - 1) + (nseg - 1) * launches(0)) % 2 == 1) {
+    if ((st = gather_systems(tmp, g, L, s)) != CN_OK) return st;
+    cur = tmp;
+  }
+  for (int64_t sg = nseg - 1; sg >= 0; --sg) {
+    const int64_t k0 = sg * K, m = std::min(nsteps, k0 + K) - k0, nl = launches(sg);
+    if (ckpt && sg < nseg - 1) psi = ckpt + (sg + 1) * span;
+    int64_t k = m;  // steps of the segment still to go
+    for (int64_t i = 0; i < nl; ++i) {
+      const int64_t ns = k - m * (nl - 1 - i) / nl;
+      WinIo io[2];
+      io[0].in = psi;
+      // the state goes on to the next launch of the segment, or (no checkpoints) to the next one
+      io[0].out = (i + 1 < nl || (!ckpt && sg > 0)) ? (psi == S[0] ? S[1] : S[0]) : nullptr;
+      io[0].ibs = io[0].obs = L->batch_stride;
+      io[1].in = cur;
+      io[1].out = w.nwin == 1 ? g : (cur == g ? tmp : g);
+      io[1].ibs = pitch(cur);
+      io[1].obs = pitch(io[1].out);
+      for (int64_t j = 0; j < ns; ++j) a.E[j] = E ? E[k0 + k - 1 - j] : 0.0;
+      a.part = dE ? part + (k - 1) * nparts : nullptr;
+      if ((st = launch_window(a, w, L->batch, 2, io, ns, xg, s)) != CN_OK) return st;
+      a.later = 1;
+      psi = io[0].out;
+      cur = io[1].out;
+      k -= ns;
+    }
+    if (dE && (st = launch_sum_partials(part, nparts, dE + k0, m, s)) != CN_OK) return st;
+  }
+  WinIo e[2];
+  e[1].out = g;
+  e[1].obs = L->batch_stride;
+  return launch_window_end(a, L->batch, e, dV, s);
+}
+
 }  // namespace
 
 // =============================================================================== C ABI
@@ -1755,6 +2143,12 @@ cn_status cn_propagate(cn_handle_t h, const cn_layout* L, const cn_operator* op,
     }
     return CN_OK;
   }
+  if (nsteps >= 1) {
+    const WinPlan w = sequence_windows(h, L, op, P, ckpt ? std::min(K, nsteps) : nsteps, 1,
+                                      E && op->xgrid);
+    if (w.cfg >= 0)
+      return run_windows(h, P, L, op, w, nsteps, E, (cd*)psi, (cd*)ckpt, K, s);
+  }
   UserArgs u = cn_args(op, 0.0, (const cd*)psi, (cd*)psi);
   if (nsteps >= 2 && fuse_enabled()) {
     const FusePlan f = fuse_plan(P);
@@ -1893,6 +2287,18 @@ cn_status cn_propagate_resident(cn_handle_t h, const cn_layout* L, const cn_oper
   const bool cap = capturing(s);
   if (E && cap) return CN_ERR_UNSUPPORTED;  // the field is uploaded by a host copy
   if (nsteps == 0) return CN_OK;
+  // on windows, whose workgroups need not wait for each other, where the estimate is below the
+  // resident kernel's step (9.6 us at 2^16 rows, 24 at 2^20; with windows 1.4 and 3.6); a poll
+  // bound or a tile size set by the caller asks for the resident kernel
+  if (!wa && L->partition == 0 && !getenv("CN_RESIDENT_SPIN")) {
+    Plan* P = nullptr;
+    if (get_plan(h, L, nsd::SRC_CN, s, &P) == CN_OK) {
+      const WinPlan w = sequence_windows(h, L, op, P, ckpt ? std::min(K_ckpt, nsteps) : nsteps, 1,
+                                         E && op->xgrid);
+      if (w.cfg >= 0 && w.us < 9.0)
+        return run_windows(h, P, L, op, w, nsteps, E, (cd*)psi, (cd*)ckpt, K_ckpt, s);
+    }
+  }
   const int64_t T = nsk::kResCfgs[ci].T(), K = (L->n + T - 1) / T;
   const ResLayout RL(K);
   const size_t o_oU = RL.o_oU, o_oD = RL.o_oD, o_h = RL.o_h, o_E = RL.o_E;
@@ -2158,11 +2564,18 @@ cn_status propagate_adjoint_impl(cn_handle_t h, const cn_layout* L, const cn_ope
   if (!fused) return CN_ERR_UNSUPPORTED;
   cd* segs = (cd*)seg;
   const int64_t span = P->span;
+  const bool field = op->xgrid && (E || dE);
+  WinPlan w = sequence_windows(h, L, op, P, std::min(K, nsteps), 2, field), w1;
+  if (w.cfg >= 0 && ckpt) {
+    w1 = sequence_windows(h, L, op, P, nsteps - (nsteps - 1) / K * K, 1, E && op->xgrid);
+    if (w1.cfg < 0) w.cfg = -1;
+  }
   // dE: every step of a segment writes its row of per-tile partials; one launch per segment
   // sums the rows (the same fixed order as one sum per step)
   double* part = nullptr;
   if (dE) {
-    const size_t need = (size_t)std::min<int64_t>(K, nsteps) * (size_t)P->ntiles1;
+    const int64_t cols = w.cfg >= 0 ? w.nwin * L->batch * nsk::kWinCfgs[1][w.cfg].W : P->ntiles1;
+    const size_t need = (size_t)std::min<int64_t>(K, nsteps) * (size_t)cols;
     if (h->rows_cap < need) {
       if (capturing(s)) return CN_ERR_NOT_RESERVED;
       size_t bytes = h->rows_cap * sizeof(double);
@@ -2173,6 +2586,11 @@ cn_status propagate_adjoint_impl(cn_handle_t h, const cn_layout* L, const cn_ope
       if (st != CN_OK) return st;
     }
     part = h->rows_buf;
+  }
+  if (w.cfg >= 0) {
+    cd* const S[2] = {segs, segs + span};
+    return run_windows_adjoint(h, P, L, op, w, w1, nsteps, E, (const cd*)ckpt, (const cd*)psi_T, K,
+                               S, (cd*)g, dV_accum, dE, part, s);
   }
   auto Ek = [&](int64_t k) { return E ? E[k] : 0.0; };
   const int64_t nseg = (nsteps + K - 1) / K;

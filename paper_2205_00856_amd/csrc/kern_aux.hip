@@ -2,6 +2,7 @@
 // of a solve, the adjoint accumulation of a Crank-Nicolson step and fixed-order partial sums.
 #include "kern_table.hpp"
 #include "nshaped_kernels.hpp"
+#include "nshaped_windows.hpp"
 
 namespace nsd {
 
@@ -200,6 +201,23 @@ __global__ void k_radial_coupling(AuxArgs A) {
   A.d[t] = mk(p.x + cb * lo.y + cc * hi.y, p.y - cb * lo.x - cc * hi.x);
 }
 
+// The end of a sequence on windows: one non-finite value makes its whole line non-finite in exact
+// steps, which the windows that it did not reach do not see.  Workgroup s fills the arrays of a
+// marked system s with NaN (dV if either mark is set) and clears the mark.
+__global__ __launch_bounds__(256) void k_window_end(WinEnd A) {
+  const int64_t s = blockIdx.x;
+  const int m = A.bad[s];
+  if (m == 0) return;
+  const double nan = __builtin_nan("");
+  for (int r = 0; r < 2; ++r)
+    if (((m >> r) & 1) && A.x[r])
+      for (int64_t i = threadIdx.x; i < A.n; i += 256) A.x[r][s * A.bs[r] + i] = mk(nan, nan);
+  if (A.dV)
+    for (int64_t i = threadIdx.x; i < A.n; i += 256) A.dV[s * A.vbs + i] = nan;
+  __syncthreads();
+  if (threadIdx.x == 0) A.bad[s] = 0;
+}
+
 }  // namespace nsd
 
 namespace nsk {
@@ -212,5 +230,6 @@ void reg_aux(Tables& t) {
   t.aux[AUX_RS_SERIAL] = (const void*)&nsd::k_rs_serial;
   t.aux[AUX_RADIAL_VEFF] = (const void*)&nsd::k_radial_veff;
   t.aux[AUX_RADIAL_COUPLING] = (const void*)&nsd::k_radial_coupling;
+  t.aux[AUX_WINDOW_END] = (const void*)&nsd::k_window_end;
 }
 }  // namespace nsk

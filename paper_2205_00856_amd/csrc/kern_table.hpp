@@ -27,6 +27,17 @@ constexpr int kNumColCfg = sizeof(kColCfgs) / sizeof(kColCfgs[0]);
 constexpr Cfg kResCfgs[] = {{8, 1}, {8, 2}, {8, 4}};
 constexpr int kNumResCfg = sizeof(kResCfgs) / sizeof(kResCfgs[0]);
 
+// Windows of a sequence of steps (k_window), of the state alone and of state and gradient, and
+// 3 .. 6 levels joining the lane blocks.  8 rows per lane keep a state's rows and factors in 200
+// registers, 2 wavefronts per SIMD; with the gradient they spill (2^20 rows and a field: 15.1 us
+// a step against 11.5 with 6 rows).  4 rows shorten the chain of a step that one wavefront per
+// SIMD runs alone (65536 rows and a field: 2.19 against 2.33 us, with the gradient 3.46 against
+// 3.84).
+constexpr Cfg kWinCfgs[2][5] = {{{8, 1}, {8, 2}, {8, 4}, {8, 8}, {4, 4}},
+                                {{6, 1}, {6, 2}, {6, 4}, {6, 8}, {4, 4}}};
+constexpr int kNumWinCfg = 5;
+constexpr int kWinLevelMin = 3, kNumWinLevel = 4;
+
 constexpr int kNumSrc = 6;  // nsd::Src
 constexpr int kNumPh = 4;   // nsd::Phase
 
@@ -39,6 +50,7 @@ enum AuxKernel : int {
   AUX_RS_SERIAL,
   AUX_RADIAL_VEFF,
   AUX_RADIAL_COUPLING,
+  AUX_WINDOW_END,
   kNumAux
 };
 
@@ -48,6 +60,7 @@ struct Tables {
   const void* cols[kNumColCfg][kNumSrc][3];
   const void* mrhs[kNumCfg][3];  // one matrix, several right-hand sides (explicit source)
   const void* aux[kNumAux];
+  const void* win[2][kNumWinCfg][kNumWinLevel][2];  // [with gradient][.][.][with a field]
   const void* res[kNumResCfg][2];  // resident propagation of one system: [SRC_CN, SRC_CNW]
   // explicit solve with first-level partitions of C = 2 or 4 chunks of 4096 rows (8192 and
   // 16384 rows, k_tile_chunk): [C == 4][0: PH_REDUCE, 1: PH_SUBST]
@@ -67,6 +80,8 @@ void reg_cols(Tables& t);
 void reg_pers(Tables& t);
 void reg_mrhs(Tables& t);
 void reg_aux(Tables& t);
+void reg_windows(Tables& t);
+void reg_windows_grad(Tables& t);
 void reg_resident(Tables& t);
 
 template <int M, int W>
