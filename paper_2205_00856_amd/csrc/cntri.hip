@@ -36,6 +36,7 @@ nsk::Tables& nsk::tables() {
     reg_cols(x);
     reg_pers(x);
     reg_mrhs(x);
+    reg_link(x);
     reg_aux(x);
     reg_resident(x);
     reg_windows(x);
@@ -206,9 +207,19 @@ struct Plan {
   int64_t ntiles1 = 0;  // level-1 tiles of a uniform CN plan (partial sums of the adjoint)
   int64_t t_bad = -1;   // tables: marks of the window launches, one int per system, zero between
                         // calls (uniform CN plans of unit stride)
+  // one pass instead of two for the level-1 tiles (k_tile<PH_LINK>): the launches it stands for,
+  // the tiles, and the device memory of lines, marks and words; -1 / null without
+  int link_red = -1, link_sub = -1;
+  int64_t link_n = 0;
+  char* link = nullptr;
+  size_t link_bytes = 0;
+  int* link_hint = nullptr;  // host memory: whether the last pass left a tile
+  int link_skip = 0;         // calls to take in two passes before one pass is tried again
   std::vector<char> host_tab;  // no-allocation plans: the tables, copied into scratch per call
   ~Plan() {
     if (tables) (void)hipFree(tables);
+    if (link) (void)hipFree(link);
+    if (link_hint) (void)hipHostFree(link_hint);
   }
 };
 
@@ -1167,6 +1178,59 @@ cn_status cache_store(cn_handle_t h, const std::map<std::string, float>& ms) {
   return ok ? CN_OK : CN_ERR_INVALID_ARG;
 }
 
+// multi-tile systems in one pass (CN_LINK=0 turns it off)
+bool link_enabled() {
+  static const bool on = [] {
+    const char* e = getenv("CN_LINK");
+    return !(e && e[0] == '0');
+  }();
+  return on;
+}
+
+// Whether the level-1 tiles of an automatic plan are taken in one pass, and its device memory.
+// Tiles of at least 1024 rows: their joints decouple when the inverse falls faster than 0.956 a
+// row (a Crank-Nicolson matrix with kappa = 50 in a potential near zero: 0.904), and the launches
+// of plans with smaller tiles (below 2^20 rows) are bound by latency, not by their passes.
+cn_status plan_link(const cn_layout* L, Plan& P) {
+  if (!link_enabled() || L->partition || L->rows_per_thread || L->levels) return CN_OK;
+  int red = -1, sub = -1;
+  for (int i = 0; i < (int)P.L.size(); ++i) {
+    const Launch& l = P.L[i];
+    if (l.level != 1) continue;
+    if (l.cfg < 0 || l.ph < 0) return CN_OK;
+    if (l.ph == nsd::PH_REDUCE && l.fn == g_kern[l.cfg][l.src][nsd::PH_REDUCE]) red = i;
+    if (l.ph == nsd::PH_SUBST && l.fn == g_kern[l.cfg][l.src][nsd::PH_SUBST]) sub = i;
+  }
+  if (red < 0 || sub < 0 || P.L[red].cfg != P.L[sub].cfg) return CN_OK;
+  const Launch& R = P.L[red];
+  if (kCfgs[R.cfg].T() < 1024 || !nsk::tables().link[R.cfg][R.src][0]) return CN_OK;
+  const int64_t n = (int64_t)R.grid.x * R.grid.y;
+  const size_t bytes = (size_t)n * (2 * 16 * sizeof(double) + sizeof(int)) + 4 * sizeof(int);
+  if (hipMalloc((void**)&P.link, bytes) != hipSuccess) {
+    (void)hipGetLastError();  // two passes then
+    P.link = nullptr;
+    return CN_OK;
+  }
+  const size_t lines = (size_t)n * 2 * 16 * sizeof(double);
+  if (hipMemset(P.link, 0xFF, lines) != hipSuccess ||
+      hipMemset(P.link + lines, 0, bytes - lines) != hipSuccess)
+    return CN_ERR_HIP;
+  if (hipHostMalloc((void**)&P.link_hint, 64, hipHostMallocMapped) != hipSuccess) {
+    (void)hipGetLastError();
+    (void)hipFree(P.link);
+    P.link = nullptr;
+    P.link_hint = nullptr;
+    return CN_OK;
+  }
+  *P.link_hint = 0;
+  P.link_bytes = bytes;
+  P.link_n = n;
+  P.link_red = red;
+  P.link_sub = sub;
+  P.desc += "one pass over the tiles where their joints decouple; ";
+  return CN_OK;
+}
+
 cn_status get_plan(cn_handle_t h, const cn_layout* L, int src, hipStream_t s, Plan** out) {
   int64_t rows = 0, span = 0;
   cn_status st = validate(L, rows, span);
@@ -1210,6 +1274,8 @@ cn_status get_plan(cn_handle_t h, const cn_layout* L, int src, hipStream_t s, Pl
       P->tables_bytes = tab.size();
     }
     bind_tables(*P, (char*)P->tables);
+    st = plan_link(L, *P);
+    if (st != CN_OK) return st;
     if (log_enabled())
       fprintf(stderr, "cntri: plan for source %d, layout n=%lld batch=%lld%s: %s\n", src,
               (long long)L->n, (long long)L->batch, L->offsets ? " (uneven)" : "",
@@ -1298,6 +1364,7 @@ const char* phase_name(int ph) {
     case nsd::PH_REDUCE: return "reduce";
     case nsd::PH_SUBST: return "subst";
     case nsd::PH_FUSE: return "fuse";
+    case nsd::PH_LINK: return "link";
   }
   return "persistent";
 }
@@ -1306,8 +1373,46 @@ cn_status run_plan(cn_handle_t h, Plan* P, const UserArgs& u, hipStream_t s,
                    void* ws_base = nullptr) {
   char* ws = (char*)(ws_base ? ws_base : h->ws);
   const bool log = h->profiling && !capturing(s);
-  for (const Launch& l : P->L) {
+  // One pass over the level-1 tiles.  A matrix whose joints couple makes it a first pass with
+  // waits (2^24 rows 532 us against 448 in two passes; 253 where they decouple), so a plan whose
+  // last pass left a tile takes 63 calls in two passes before it tries again; the results are the
+  // same bits.  (The lines belong to the plan: a run on another workspace may overlap one on
+  // this.)
+  bool link = P->link && !ws_base;
+  if (link) {
+    if (*(volatile int*)P->link_hint) {
+      *(volatile int*)P->link_hint = 0;
+      P->link_skip = 63;
+    }
+    if (P->link_skip > 0) {
+      --P->link_skip;
+      link = false;
+    }
+  }
+  for (const Launch& lp : P->L) {
+    Launch l = lp;
     KArgs a = plan_args(h, l, u, ws);
+    const int i = (int)(&lp - P->L.data());
+    if (P->link && i == P->link_sub) {
+      const Launch& R = P->L[P->link_red];
+      a.lk_n = P->link_n;
+      a.oU = (cd*)(ws + R.o_oU);
+      a.oD = (cd*)(ws + R.o_oD);
+    }
+    if (link && (i == P->link_red || i == P->link_sub || l.level > 1)) {
+      a.lk = (double*)P->link;
+      a.lk_done = (int*)(a.lk + 2 * 16 * P->link_n);
+      a.lk_st = a.lk_done + P->link_n;
+      a.lk_n = P->link_n;
+      a.lk_hint = P->link_hint;
+      if (i == P->link_red) {
+        l.fn = nsk::tables().link[l.cfg][l.src][0];
+        l.ph = nsd::PH_LINK;
+      } else if (i == P->link_sub) {
+        l.fn = nsk::tables().link[l.cfg][l.src][1];
+        l.grid = dim3((unsigned)((P->link_n + 3) / 4));
+      }
+    }
     cn_handle_s::Rec r;
     if (log) {
       char lab[160];
@@ -2760,7 +2865,7 @@ cn_status cn_handle_info(cn_handle_t h, int64_t* device_bytes, int64_t* retired_
   if (device_bytes) {
     size_t b = h->ws_size + h->ws2_size + h->seg2_bytes + h->mat_size + h->rad_size +
                h->rows_cap * sizeof(double);
-    for (const auto& kv : h->plans) b += kv.second->tables_bytes;
+    for (const auto& kv : h->plans) b += kv.second->tables_bytes + kv.second->link_bytes;
     *device_bytes = (int64_t)b;
   }
   if (retired_buffers) *retired_buffers = (int64_t)h->retired.size();

@@ -57,6 +57,9 @@ enum AuxKernel : int {
 struct Tables {
   const void* tile[kNumCfg][kNumSrc][kNumPh];
   const void* pers[kNumCfg][kNumSrc];
+  // a multi-tile system in one pass, and the launch for the tiles it leaves: [0: k_tile<PH_LINK>,
+  // 1: k_tile_fix]
+  const void* link[kNumCfg][kNumSrc][2];
   const void* cols[kNumColCfg][kNumSrc][3];
   const void* mrhs[kNumCfg][3];  // one matrix, several right-hand sides (explicit source)
   const void* aux[kNumAux];
@@ -79,6 +82,7 @@ void reg_tile_slots(Tables& t);
 void reg_cols(Tables& t);
 void reg_pers(Tables& t);
 void reg_mrhs(Tables& t);
+void reg_link(Tables& t);
 void reg_aux(Tables& t);
 void reg_windows(Tables& t);
 void reg_windows_grad(Tables& t);

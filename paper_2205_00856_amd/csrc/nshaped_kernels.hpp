@@ -31,9 +31,12 @@ enum Phase : int {
   PH_SUBST = 2,   // second pass: re-reduce, take the tile's joint lines from above, SS
   PH_FUSE = 3,    // Crank-Nicolson sequences: PH_SUBST of step n, then PH_REDUCE of step n+1 on
                   // the new state (the tile's joint row defers its left neighbour, see ud_halo)
-  PH_RES = 4      // a step of the resident propagation (k_resident): PH_REDUCE's hand-over,
+  PH_RES = 4,     // a step of the resident propagation (k_resident): PH_REDUCE's hand-over,
                   // then, once the reduced system is solved in the same launch, PH_SUBST's
                   // substitution (not a phase of the kernel tables)
+  PH_LINK = 5     // a multi-tile system in one pass: PH_REDUCE's hand-over, then the tile's joint
+                  // lines from its neighbours' slots where those decouple (link_exchange), then
+                  // PH_SUBST's substitution
 };
 
 struct KArgs {
@@ -95,6 +98,14 @@ struct KArgs {
   const double* Wabs;
   double wscale;
   int64_t l0;  // SRC_LCOUP: partial wave of row 0
+  // PH_LINK and the launches after it: a line of 16 values per tile in each of two buffers of
+  // lk_n lines, words [buffer of the next pass, buffer of this one, whether the pass
+  // of buffer 0, 1 left a tile], and per tile whether the pass has finished it
+  double* lk;
+  int* lk_st;
+  int* lk_done;
+  int64_t lk_n;  // second passes: nonzero where a joint that decouples is taken as PH_LINK takes it
+  int* lk_hint;  // host memory: whether the last pass left a tile
   // PH_FUSE of one system: the reduced system of the tile joints is solved by the pass's last
   // workgroup (count of workgroups done, zero between launches), or null (a launch of its own)
   int* inl_sync;
@@ -115,12 +126,10 @@ __device__ __forceinline__ unsigned rev_linear(unsigned L, unsigned G) {
 }
 
 template <int PH>
-__device__ __forceinline__ Geo geometry(const KArgs& A) {
+__device__ __forceinline__ Geo geometry(const KArgs& A, unsigned bx, unsigned by) {
   Geo g;
-  unsigned bx = blockIdx.x;
-  const unsigned by = blockIdx.y;
   // second passes only (PH_SUBST, PH_FUSE); the host sets rev for one-dimensional grids
-  if constexpr (PH >= 2) {
+  if constexpr (PH == PH_SUBST || PH == PH_FUSE) {
     if (A.rev) bx = rev_linear(bx, gridDim.x);
   }
   if (A.wg_sys) {
@@ -129,7 +138,7 @@ __device__ __forceinline__ Geo geometry(const KArgs& A) {
   } else if (A.xcd_remap && gridDim.x == 1) {
     // Workgroups are handed to the 8 XCDs round-robin by linear id; give each XCD a contiguous
     // range of systems so that neighbouring (interleaved) systems share its L2.
-    const int64_t B = gridDim.y, id = blockIdx.y, x = id & 7, q = B >> 3, r = B & 7;
+    const int64_t B = gridDim.y, id = by, x = id & 7, q = B >> 3, r = B & 7;
     g.sys = x * q + (x < r ? x : r) + (id >> 3);
     g.tile = 0;
   } else {
@@ -156,6 +165,10 @@ __device__ __forceinline__ Geo geometry(const KArgs& A) {
   }
   g.cbase = A.cshared ? 0 : g.base;
   return g;
+}
+template <int PH>
+__device__ __forceinline__ Geo geometry(const KArgs& A) {
+  return geometry<PH>(A, blockIdx.x, blockIdx.y);
 }
 
 __device__ __forceinline__ double sel(bool p, double a, double b) { return p ? a : b; }
@@ -492,6 +505,8 @@ struct TileSmem {
   Node xnode[64];
   double wsum[W];
   cd wedge[W];  // PH_FUSE: last new-state row of every wavefront
+  double lkv[16];  // PH_LINK: the tile's line, then its neighbours' values
+  int lkf;         // PH_LINK: the tile is done in this pass
   __device__ __forceinline__ Blk* part(int w, int k) {
     if constexpr (kInStage)
       return reinterpret_cast<Blk*>(reinterpret_cast<char*>(lds[w]) + kOff) + k;
@@ -614,7 +629,8 @@ __device__ __forceinline__ void tile_run(const KArgs& A, const Geo& G, TileSmem<
   cd* buf = sm.lds[wave];
 
   cd Ar[M], Br[M], Cr[M], Dr[M], bK, fst, lst;
-  constexpr int PL = (PH == PH_FUSE) ? PH_SUBST : PH;  // the rows are those of a PH_SUBST pass
+  // the rows are those of a PH_SUBST pass, or (PH_LINK) of a first pass
+  constexpr int PL = (PH == PH_FUSE) ? PH_SUBST : (PH == PH_LINK) ? PH_REDUCE : PH;
   // PH_FUSE: diagonal of the next step, from this pass's loads of V and xgrid (imaginary parts)
   double ayn[M];
   double* ayp = (PH == PH_FUSE) ? ayn : nullptr;
@@ -651,8 +667,110 @@ __device__ __forceinline__ void st_coh(cd* p, cd v) {
 }
 
 struct NoMid {
-  __device__ void operator()(cd&, cd&) const {}
+  __device__ void operator()(const Blk&, cd&, cd&) const {}
 };
+
+// ------------------------------------------------------- one pass over a multi-tile system
+// The reduced system of a level couples tile joint J to its neighbours by DB of the tile before
+// and UC of the tile after it.  Both fall with the distance of the joints like the inverse of the
+// matrix (Crank-Nicolson matrices and diagonally dominant ones: exponentially), and for tiles of
+// some thousand rows they are usually nothing in FP64.  Then the joint's own row is the whole
+// system, psi_J = (DD of the tile before + UD) / (DA + UA), a tile needs its two neighbours only,
+// and the reduction and the substitution are one pass over memory: k_tile<PH_LINK> publishes the
+// tile's line (DA, DD, |DB| for the next tile, UA, UD, |UC| for the one before), polls for its
+// neighbours' values, which are those of workgroups started beside it, and substitutes from the
+// rows that it still holds.  A joint whose couplings exceed kLinkEps of its diagonal, a value
+// that is not finite or a wait that reaches its bound leaves the tile to the launches that follow
+// (the reduced system and k_tile_fix, the two-pass form): they return at once when no tile asks
+// for them.  The decision is the same in either launch (link_joints), so a result does not depend
+// on the waits, nor on the host's choice of one pass or two.
+//   A line's values are their own flags: it holds all-ones words (a NaN that no operation of the
+// kernel produces from other values; if an input carries it, the waits reach their bound) until
+// the tile's doubles arrive, one 8-byte store each.  Lines alternate between two buffers: a pass
+// clears the lines that the next one polls.  In place: a tile stores only when both neighbours
+// have published, so after they have loaded their rows and edges.
+//   Progress: a tile publishes before it waits, so only a neighbour that has not started keeps it
+// waiting; workgroups start in order, and the bound ends a wait that other work on the GPU draws
+// out.
+//   Bound by memory: the solve of 2^28 rows 6.80 -> 3.60 ms (80 bytes a row at 6.0 TB/s; the two
+// passes read the matrix twice), 2^24 rows 446 -> 253 us, an uneven step of 10^4 systems 1.59 ->
+// 1.08 ms.  Larger tiles are slower (2^28: 2048 rows of 4 per lane 4.05 ms, of 8 per lane 3.81).
+constexpr double kLinkEps = 0x1p-66;
+constexpr int kLinkSpin = 256;
+
+__device__ __forceinline__ double cmag(cd v) { return fmax(fabs(v.x), fabs(v.y)); }
+
+// psi at the tile's joint lines from its own slots b and its neighbours' (zero past the system's
+// ends); false when a joint is coupled beyond kLinkEps or not finite.
+__device__ __forceinline__ bool link_joints(const Blk& b, cd lDA, cd lDD, double lDB, cd rUA,
+                                            cd rUD, double rUC, bool right, cd& pJ, cd& pM) {
+  const cd a1 = cadd(lDA, b.UA), a2 = cadd(b.DA, rUA);
+  const double m1 = kLinkEps * cmag(a1), m2 = kLinkEps * cmag(a2);
+  bool ok = lDB <= m1 && cmag(b.UC) <= m1;
+  if (right) ok = ok && cmag(b.DB) <= m2 && rUC <= m2;
+  pJ = cmul(cadd(lDD, b.UD), crecip(a1));
+  pM = right ? cmul(cadd(b.DD, rUD), crecip(a2)) : czero();
+  return ok && cfinite(pJ) && cfinite(pM);
+}
+
+// Wavefront 0 of a PH_LINK tile; b, pJ and pM count in lane 0.  Returns whether the tile is done.
+template <typename SM>
+__device__ __forceinline__ bool link_exchange(const KArgs& A, const Geo& G, SM& sm, const Blk& b,
+                                              int lane, cd& pJ, cd& pM) {
+  const int e = A.lk_st[0] & 1;
+  double* mine = A.lk + ((int64_t)e * A.lk_n + G.gt) * 16;
+  if (lane == 0) {
+    sm.lkv[0] = b.DA.x;
+    sm.lkv[1] = b.DA.y;
+    sm.lkv[2] = b.DD.x;
+    sm.lkv[3] = b.DD.y;
+    sm.lkv[4] = cmag(b.DB);
+    sm.lkv[8] = b.UA.x;
+    sm.lkv[9] = b.UA.y;
+    sm.lkv[10] = b.UD.x;
+    sm.lkv[11] = b.UD.y;
+    sm.lkv[12] = cmag(b.UC);
+  }
+  wave_sync();
+  const bool slot = lane < 5 || (lane >= 8 && lane < 13);
+  if (slot) {
+    __hip_atomic_store(mine + lane, sm.lkv[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    A.lk[((int64_t)(1 - e) * A.lk_n + G.gt) * 16 + lane] = __longlong_as_double(-1ll);
+  }
+  wave_sync();
+  const bool left = G.tile > 0, right = G.tile + 1 < G.ntile;
+  const bool act = slot && (lane < 8 ? left : right);
+  const long long* src =
+      reinterpret_cast<const long long*>(mine + (act ? (lane < 8 ? -16 : 16) : 0) + (slot ? lane : 0));
+  long long v = act ? -1ll : 0ll;
+  for (int it = 0;; ++it) {
+    if (v == -1ll) v = __hip_atomic_load(src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (__all(v != -1ll) || it >= kLinkSpin) break;
+    __builtin_amdgcn_s_sleep(1);
+  }
+  bool ok = __all(v != -1ll);
+  if (lane < 16) sm.lkv[lane] = __longlong_as_double(v);
+  wave_sync();
+  const double* q = sm.lkv;
+  const bool dec = link_joints(b, mk(q[0], q[1]), mk(q[2], q[3]), q[4], mk(q[8], q[9]),
+                               mk(q[10], q[11]), q[12], right, pJ, pM);
+  ok = ok && __builtin_amdgcn_readfirstlane(dec);
+  if (lane == 0) {
+    A.lk_done[G.gt] = ok;
+    if (!ok) A.lk_st[2 + e] = 1;  // (a plain store: every tile that stores it stores the same)
+    if (G.gt == 0) {
+      A.lk_st[1] = e;
+      A.lk_st[2 + (1 - e)] = 0;
+    }
+    sm.lkf = ok;
+  }
+  return ok;
+}
+
+// The launches after a PH_LINK pass that finished every tile have nothing to do.
+__device__ __forceinline__ bool link_idle(const KArgs& A) {
+  return A.lk_st && A.lk_st[2 + A.lk_st[1]] == 0;
+}
 
 template <int M, int W, int SRC, int PH>
 struct RdSubst {
@@ -661,7 +779,7 @@ struct RdSubst {
 
 // COH: the slots and edge rows of a PH_REDUCE part are stored device-coherent (st_coh), for a
 // fused pass whose last workgroup solves the reduced system (fuse_reduced_last).
-// PH_RES: the hand-over of PH_REDUCE, then mid(pJ, pM) (run by the whole workgroup: it waits
+// PH_RES: the hand-over of PH_REDUCE, then mid(block, pJ, pM) (run by the whole workgroup: it waits
 // until every tile's slots are in, solves the reduced system and returns psi at the tile's two
 // joint lines), then the substitution of PH_SUBST.
 template <int M, int W, int SRC, int PH, bool IN, bool RDR = false, bool COH = false, typename SM,
@@ -747,9 +865,22 @@ __device__ __forceinline__ void tile_core(const KArgs& A, const Geo& G, SM& sm, 
       pJ = A.psi_if[G.gt];
       const cd nxt = A.psi_if[(G.tile + 1 < G.ntile) ? G.gt + 1 : G.gt];
       pM = csel(G.tile + 1 < G.ntile, nxt, czero());
+      if (SRC != SRC_SLOTS && A.lk_n) {
+        // the joints that a PH_LINK pass takes, where they decouple
+        const bool lf = G.tile > 0, rt = G.tile + 1 < G.ntile;
+        const cd* l = A.oD + 3 * (lf ? G.gt - 1 : G.gt);
+        const cd* r = A.oU + 3 * (rt ? G.gt + 1 : G.gt);
+        cd jJ, jM;
+        if (link_joints(blk, csel(lf, l[1], czero()), csel(lf, l[2], czero()),
+                        lf ? cmag(l[0]) : 0.0, csel(rt, r[0], czero()), csel(rt, r[2], czero()),
+                        rt ? cmag(r[1]) : 0.0, rt, jJ, jM)) {
+          pJ = jJ;
+          pM = jM;
+        }
+      }
     }
   }
-  if constexpr (PH == PH_RES) mid(pJ, pM);
+  if constexpr (PH == PH_RES) mid(blk, pJ, pM);
   if constexpr (PH != PH_REDUCE) {
     if constexpr (W == 1) {
       tree_down<6>(pJ, pM, wnode, lane);
@@ -880,7 +1011,8 @@ __device__ __forceinline__ void tile_finish(const KArgs& A, const Geo& G, TileSm
                                             cd bK, cd fst, cd lst, const double* ayn) {
   // the staging buffer is idle between the loads and the stores: it holds the nodes and, for
   // substitution along the RD rows, the diagonals after them
-  constexpr int PS = (PH == PH_FUSE) ? PH_SUBST : PH;  // the solve that ends in this pass
+  // the solve that ends in this pass
+  constexpr int PS = (PH == PH_FUSE) ? PH_SUBST : (PH == PH_LINK) ? PH_RES : PH;
   Node* wnode = reinterpret_cast<Node*>(buf);
   double* keep = reinterpret_cast<double*>(wnode + 64);
   static_assert(!RdSubst<M, W, SRC, PS>::on ||
@@ -900,8 +1032,17 @@ __device__ __forceinline__ void tile_finish(const KArgs& A, const Geo& G, TileSm
 #pragma unroll
     for (int j = 0; j < M; ++j) arn[j] = Ar[j].x;
   }
-  tile_core<M, W, SRC, PS, IN>(A, G, sm, wnode, keep, kap, J, lane, wave, Ar, Br, Cr, Dr, bK, fst,
-                               lst, xo, PH == PH_FUSE ? &pM : nullptr);
+  if constexpr (PH == PH_LINK) {
+    auto mid = [&](const Blk& b, cd& pj, cd& pm) {
+      if (wave == 0) link_exchange(A, G, sm, b, lane, pj, pm);
+    };
+    tile_core<M, W, SRC, PS, IN>(A, G, sm, wnode, keep, kap, J, lane, wave, Ar, Br, Cr, Dr, bK,
+                                 fst, lst, xo, nullptr, mid);
+    if (!sm.lkf) return;  // (the same in every wavefront: written before tile_core's barriers)
+  } else {
+    tile_core<M, W, SRC, PS, IN>(A, G, sm, wnode, keep, kap, J, lane, wave, Ar, Br, Cr, Dr, bK,
+                                 fst, lst, xo, PH == PH_FUSE ? &pM : nullptr);
+  }
   if constexpr (PS != PH_REDUCE) {
     check_rows<M, IN>(A, G, J, lane, xo);
     if constexpr (SRC == SRC_SLOTS) {
@@ -921,7 +1062,7 @@ __device__ __forceinline__ void tile_finish(const KArgs& A, const Geo& G, TileSm
 // register above the budget of 3 wavefronts; the others keep the compiler's choice.
 template <int M, int PH, int SRC = SRC_CN>
 constexpr int tile_min_waves() {
-  return (PH == PH_FUSE && M == 8 && cn_src(SRC)) ? 3 : 1;
+  return (PH == PH_FUSE && M == 8 && cn_src(SRC)) ? 3 : (PH == PH_LINK && M == 8 && SRC == SRC_CN) ? 4 : 1;
 }
 
 // The reduced system of a PH_FUSE pass over one system, solved in the same launch: every
@@ -969,11 +1110,46 @@ __device__ __forceinline__ void fuse_reduced_last(const KArgs& A, TileSmem<M, W>
 template <int M, int W, int SRC, int PH>
 __global__ __launch_bounds__(64 * W, (tile_min_waves<M, PH, SRC>())) void k_tile(KArgs A) {
   __shared__ TileSmem<M, W> sm;
+  if constexpr (SRC == SRC_SLOTS) {
+    if (link_idle(A)) return;
+  }
   const Geo G = geometry<PH>(A);
   tile_run<M, W, SRC, PH>(A, G, sm);
   if constexpr (PH == PH_FUSE && cn_src(SRC)) {
     __shared__ int last;
     if (A.inl_sync) fuse_reduced_last<M, W>(A, sm, last);
+  }
+}
+
+// The tiles that a PH_LINK pass has not finished, in second-pass form (psi_if: the reduced
+// system's solution), four tiles per workgroup: few enough workgroups that a launch with nothing to
+// do costs little (2^28 rows: 65536 workgroups), enough to keep the GPU full when every tile is
+// left.  A non-finite joint makes its system
+// non-finite in exact arithmetic: the tiles that the pass had finished become NaN with it.
+template <int M, int W, int SRC>
+__global__ __launch_bounds__(64 * W, M == 4 ? 4 : 1) void k_tile_fix(KArgs A) {
+  __shared__ TileSmem<M, W> sm;
+  constexpr int64_t T = 64 * W * M;
+  const int cur = A.lk_st[1];
+  if (!link_idle(A)) {
+    for (int64_t i = blockIdx.x; i < A.lk_n; i += gridDim.x) {
+      const Geo G = A.wg_sys ? geometry<PH_REDUCE>(A, (unsigned)i, 0)
+                             : geometry<PH_REDUCE>(A, (unsigned)(i % A.ntiles),
+                                                   (unsigned)(i / A.ntiles));
+      if (!A.lk_done[G.gt]) {
+        tile_run<M, W, SRC, PH_SUBST>(A, G, sm);
+      } else if (!cfinite(A.psi_if[G.gt]) ||
+                 (G.tile + 1 < G.ntile && !cfinite(A.psi_if[G.gt + 1]))) {
+        const double nan = __builtin_nan("");
+        for (int64_t r = G.tile * T + threadIdx.x; r < (G.tile + 1) * T && r < G.n; r += 64 * W)
+          A.x[G.base + r * G.es] = mk(nan, nan);
+      }
+      __syncthreads();
+    }
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    A.lk_st[0] = cur ^ 1;
+    __hip_atomic_store(A.lk_hint, A.lk_st[2 + cur], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 
@@ -1207,7 +1383,7 @@ __device__ __forceinline__ void resident_run(const KArgs& A, const ResArgs& R, c
     double* keep = reinterpret_cast<double*>(wnode + 64);
     cd xo[M];
     cd pM = czero();
-    auto mid = [&](cd& pj, cd& pm) { ok = res_exchange<M, W>(Ak, R, sm, k, pj, pm); };
+    auto mid = [&](const Blk&, cd& pj, cd& pm) { ok = res_exchange<M, W>(Ak, R, sm, k, pj, pm); };
     tile_core<M, W, SRC, PH_RES, IN, true, true>(Ak, G, sm.t, wnode, keep, kap, J, lane, wave, Ar,
                                                  Br, Cr, Dr, bK, fst, lst, xo, &pM, mid);
     if (!ok) return;

@@ -1,0 +1,191 @@
+"""GPU parity of multi-tile systems solved in one pass (k_tile<PH_LINK>) and of the tiles that such
+a pass leaves to the launches after it, against the CPU oracle.
+
+Tolerance: relative L2 <= 1e-11, as everywhere (the couplings that a tile drops are below 2^-66 of
+its diagonal); for steps with a large kappa 16 * 4 kappa * 2^-53, the rounding of a matrix of norm
+1 + 4 kappa whose inverse has norm 1.  Ill-conditioned matrices (slow, mixed: condition 2e7) are
+compared with the two-pass form on the same tiles (an explicit partition): bit for bit where every
+joint couples, else to 1e-11.  The plans take one pass from 2^20 rows on.  Cases: matrices whose joints decouple,
+matrices whose do not (the whole system in two passes), both kinds in one system, ragged ends, in
+place and out of place, the conjugate transpose, batches, uneven batches with a spacing per
+system, absorbing potentials, several calls in a row, graph replays, and non-finite values.
+"""
+import numpy as np
+import pytest
+
+import workloads
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-11
+N = (1 << 20) + 777
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2205_00856_amd as cn
+
+    cn.handle(0)
+    return torch, cn
+
+
+def rel(x, y):
+    return float(np.linalg.norm(x - y) / max(np.linalg.norm(y), 1e-300))
+
+
+def dev(torch, *arrs):
+    return [torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in arrs]
+
+
+def system(n, kind, seed=1):
+    """a, b, c, d: fast (diagonally dominant, couplings 1/4), slow (the joints of neighbouring
+    tiles couple: off-diagonals 1 - 1e-7 of half the diagonal) or half slow rows, half fast."""
+    g = np.random.default_rng(seed)
+    slow = {"fast": np.zeros(n, bool), "slow": np.ones(n, bool),
+            "mixed": (np.arange(n) // 100_000) % 2 == 0}[kind]
+    a = 2.0 + 0.1j * g.standard_normal(n) * ~slow
+    off = np.where(slow, -(1.0 - 1e-7), 0.25)
+    b, c = off * np.exp(0.3j * ~slow), off * np.exp(-0.2j * ~slow)
+    return a, b + 0j, c + 0j, workloads.complex_normal(g, n)
+
+
+def check(torch, cn, oracle_mod, kind, mats, got):
+    a, b, c, d = mats
+    if kind == "fast":
+        assert rel(got.cpu().numpy(), oracle_mod.thomas(a, b, c, d)) <= TOL
+        return
+    two = cn.solve(*dev(torch, a, b, c, d),
+                   layout=cn.Layout.contiguous(len(d), 1, partition=1024, rows_per_thread=4))
+    if kind == "slow":
+        assert torch.equal(got, two)
+    assert rel(got.cpu().numpy(), two.cpu().numpy()) <= TOL
+
+
+@pytest.mark.parametrize("n", [N, 1 << 21])
+@pytest.mark.parametrize("kind", ["fast", "slow", "mixed"])
+def test_solve(gpu, oracle_mod, kind, n):
+    torch, cn = gpu
+    a, b, c, d = system(n, kind)
+    ta, tb, tc, td = dev(torch, a, b, c, d)
+    assert "one pass" in cn.describe_plan(cn.Layout.contiguous(n, 1))
+    x = cn.solve(ta, tb, tc, td)
+    check(torch, cn, oracle_mod, kind, (a, b, c, d), x)
+    for _ in range(3):  # in place, the two line buffers in turn, the same bits
+        y = td.clone()
+        cn.solve(ta, tb, tc, y, out=y)
+        assert torch.equal(x, y)
+    assert cn.get_status() == 0
+
+
+def test_alternating_kinds(gpu, oracle_mod):
+    """Calls that finish in one pass and calls that do not, on one plan."""
+    torch, cn = gpu
+    for s, kind in enumerate(["fast", "slow", "slow", "fast", "mixed", "fast"]):
+        mats = system(N, kind, s)
+        check(torch, cn, oracle_mod, kind, mats, cn.solve(*dev(torch, *mats)))
+
+
+@pytest.mark.parametrize("kind", ["fast", "mixed"])
+def test_transposed(gpu, oracle_mod, kind):
+    torch, cn = gpu
+    a, b, c, d = system(N, kind)
+    if kind == "fast":
+        x = oracle_mod.thomas(a, b, c, d)
+        want = oracle_mod.thomas_adjoint(a, b, c, x, d)
+    else:
+        x = d
+        L = cn.Layout.contiguous(N, 1, partition=1024, rows_per_thread=4)
+        want = [t.cpu().numpy() for t in cn.solve_adjoint(*dev(torch, a, b, c, x, d), layout=L)]
+    got = cn.solve_adjoint(*dev(torch, a, b, c, x, d))
+    for t, ref in zip(got, want):
+        assert rel(t.cpu().numpy(), ref) <= TOL
+
+
+@pytest.mark.parametrize("absorb", [False, True])
+@pytest.mark.parametrize("kap", [0.5, 50.0, 5e5])
+def test_step(gpu, oracle_mod, kap, absorb):
+    """Steps in place (edge rows next to stored ones), joints that decouple and (5e5) not."""
+    torch, cn = gpu
+    dt = 0.02
+    dx = 0.5 * np.sqrt(dt / kap)
+    g = np.random.default_rng(7)
+    V, psi = g.uniform(-1.0, 0.0, N), workloads.complex_normal(g, N)
+    W = workloads.absorber(N) if absorb else None
+    ref = psi
+    tV, p = dev(torch, V, psi)
+    tW = dev(torch, W)[0] if absorb else None
+    for _ in range(3):
+        ref = oracle_mod.cn_step(ref, V, dx, dt, W=W)
+        cn.step(p, tV, dx, dt, out=p, W=tW)
+    tol = max(TOL, 64 * kap * 2.0 ** -53)
+    assert rel(p.cpu().numpy(), ref) <= 3 * tol
+    out = cn.step(dev(torch, psi)[0], tV, dx, dt, W=tW)
+    assert rel(out.cpu().numpy(), oracle_mod.cn_step(psi, V, dx, dt, W=W)) <= tol
+
+
+def test_batches(gpu, oracle_mod):
+    """A uniform batch of several tiles each, and an uneven one with a spacing per system (some
+    systems coupled, some not)."""
+    torch, cn = gpu
+    n, batch, dt = 9001, 150, 0.02
+    g = np.random.default_rng(5)
+    V, psi = g.uniform(-1.0, 0.0, (batch, n)), workloads.complex_normal(g, (batch, n))
+    tV, p = dev(torch, V, psi)
+    cn.step(p, tV, 0.1, dt, out=p)
+    out = p.cpu().numpy()
+    for s in range(0, batch, 29):
+        assert rel(out[s], oracle_mod.cn_step(psi[s], V[s], 0.1, dt)) <= TOL
+    lens = np.concatenate([[1, 4097, 2048, 65_536], g.integers(3000, 20_000, 120)])
+    offs = np.concatenate([[0], np.cumsum(lens)])
+    dx = np.where(np.arange(len(lens)) % 7 == 3, 1e-4, g.uniform(0.05, 0.2, len(lens)))
+    V, psi = g.uniform(-1.0, 0.0, offs[-1]), workloads.complex_normal(g, offs[-1])
+    tV, p, tdx = dev(torch, V, psi, dx)
+    L = cn.Layout.uneven(offs)
+    assert "one pass" in cn.describe_plan(L, cn_mode=True)
+    for _ in range(2):
+        cn.step(p, tV, 0.0, dt, dx_per_system=tdx, out=p, layout=L)
+    out = p.cpu().numpy()
+    for s in range(len(lens)):
+        r = slice(offs[s], offs[s + 1])
+        ref = oracle_mod.cn_step(psi[r], V[r], dx[s], dt)
+        tol = max(TOL, 2 * 64 * dt / (4 * dx[s] ** 2) * 2.0 ** -53)
+        assert rel(out[r], oracle_mod.cn_step(ref, V[r], dx[s], dt)) <= tol, s
+
+
+def test_graph_replays(gpu):
+    torch, cn = gpu
+    a, b, c, d = dev(torch, *system(N, "mixed"))
+    want = cn.solve(a, b, c, d)
+    x = d.clone()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        cn.solve(a, b, c, x, out=x)
+    for _ in range(3):
+        x.copy_(d)
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(x, want)
+        assert torch.equal(cn.solve(a, b, c, d), want)  # eager work between the replays
+
+
+def test_non_finite(gpu):
+    """One NaN makes its whole system NaN and raises the status; other systems of the batch and
+    the next call are clean."""
+    torch, cn = gpu
+    n, batch = 300_001, 4
+    mats = [system(n, "fast", s) for s in range(batch)]
+    a, b, c, d = (torch.stack(t) for t in zip(*(dev(torch, *m) for m in mats)))
+    L = cn.Layout.contiguous(n, batch)
+    want = cn.solve(a, b, c, d, layout=L)
+    bad = d.clone()
+    bad[2, 123_456] = float("nan")
+    x = cn.solve(a, b, c, bad, out=bad, layout=L)
+    assert cn.get_status() == 1
+    assert not torch.isfinite(torch.view_as_real(x[2])).any()
+    for s in (0, 1, 3):
+        assert torch.equal(x[s], want[s])
+    assert torch.equal(cn.solve(a, b, c, d, layout=L), want)
+    assert cn.get_status() == 0
