@@ -18,6 +18,7 @@
 #include "../../include/cntri.h"
 #include "kern_table.hpp"
 #include "nshaped_kernels.hpp"
+#include "nshaped_colstep.hpp"
 #include "nshaped_windows.hpp"
 
 using nsd::cd;
@@ -37,6 +38,7 @@ nsk::Tables& nsk::tables() {
     reg_pers(x);
     reg_mrhs(x);
     reg_link(x);
+    reg_colstep(x);
     reg_aux(x);
     reg_resident(x);
     reg_windows(x);
@@ -193,6 +195,39 @@ struct Launch {
   int64_t o_hout2 = -1;  // second edge-row array of a Crank-Nicolson first pass (PH_FUSE chains)
 };
 
+// Minimum of f over eta in (0, hi) by golden-section search (f has one minimum there).
+template <typename F>
+double min_over(double hi, const F& f) {
+  const double g = 0.6180339887498949;
+  double a = 0.0, b = hi, x1 = b - g * (b - a), x2 = a + g * (b - a), f1 = f(x1), f2 = f(x2);
+  for (int i = 0; i < 48; ++i) {
+    if (f1 < f2) {
+      b = x2;
+      x2 = x1;
+      f2 = f1;
+      x1 = b - g * (b - a);
+      f1 = f(x1);
+    } else {
+      a = x1;
+      x1 = x2;
+      f1 = f2;
+      x2 = a + g * (b - a);
+      f2 = f(x2);
+    }
+  }
+  return std::min(f1, f2);
+}
+double eta_max(double kap) { return kap > 0.0 ? std::min(8.0, std::asinh(0.5 / kap)) : 8.0; }
+
+// Whether two joint lines B rows apart are decoupled to 2^-66 in every real potential: their
+// coupling kappa^2 (T^-1)_{1,m} against a diagonal of real part at least 1.
+bool decoupled(double kap, double B) {
+  return min_over(eta_max(kap), [&](double e) {
+    const double th = std::min(2.0 * kap * std::sinh(e), 1.0 - 1e-12);
+    return 2.0 * std::log(std::max(kap, 1e-30)) - e * (B - 2.0) - std::log(1.0 - th);
+  }) <= -66.0 * M_LN2;
+}
+
 struct Plan {
   std::vector<Launch> L;
   size_t ws_bytes = 0;
@@ -215,11 +250,19 @@ struct Plan {
   size_t link_bytes = 0;
   int* link_hint = nullptr;  // host memory: whether the last pass left a tile
   int link_skip = 0;         // calls to take in two passes before one pass is tried again
+  // steps of an interleaved batch in one pass (k_colstep): its device memory (lines, then words,
+  // marks), or null; the shape; and the tile for the last off-diagonal asked for (-1: none)
+  char* col = nullptr;
+  size_t col_bytes = 0;
+  int64_t col_n = 0, col_batch = 0, col_es = 0, col_tiles = 0;
+  double col_kap = -1.0;
+  int col_cfg = -1;
   std::vector<char> host_tab;  // no-allocation plans: the tables, copied into scratch per call
   ~Plan() {
     if (tables) (void)hipFree(tables);
     if (link) (void)hipFree(link);
     if (link_hint) (void)hipHostFree(link_hint);
+    if (col) (void)hipFree(col);
   }
 };
 
@@ -400,7 +443,7 @@ void plan_level(Builder& B, std::vector<Launch>& L, const BatchDesc& bd, int src
         l.grid = dim3((unsigned)(K * gy));
         l.threads = 64 * kColCfgs[cc].W;
         l.a = a;
-              l.level = level;
+        l.level = level;
         l.src = src;
         l.ph = ph;
         l.cfg = -1;
@@ -730,30 +773,6 @@ bool windows_enabled() {
   return on;
 }
 
-// Minimum of f over eta in (0, hi) by golden-section search (f has one minimum there).
-template <typename F>
-double min_over(double hi, const F& f) {
-  const double g = 0.6180339887498949;
-  double a = 0.0, b = hi, x1 = b - g * (b - a), x2 = a + g * (b - a), f1 = f(x1), f2 = f(x2);
-  for (int i = 0; i < 48; ++i) {
-    if (f1 < f2) {
-      b = x2;
-      x2 = x1;
-      f2 = f1;
-      x1 = b - g * (b - a);
-      f1 = f(x1);
-    } else {
-      a = x1;
-      x1 = x2;
-      f1 = f2;
-      x2 = a + g * (b - a);
-      f2 = f(x2);
-    }
-  }
-  return std::min(f1, f2);
-}
-double eta_max(double kap) { return kap > 0.0 ? std::min(8.0, std::asinh(0.5 / kap)) : 8.0; }
-
 // Rows that a cut of the line has to stay away after s steps (nshaped_windows.hpp): the smallest
 // D with r^s exp(-eta D) / (2 sinh eta) <= 2^-70 for some eta.
 double window_halo(double kap, int64_t s) {
@@ -763,18 +782,11 @@ double window_halo(double kap, int64_t s) {
             std::log(2.0 * std::sinh(e))) / e;
   })) + 1.0;
 }
-// Levels of lane blocks of M rows whose reduced systems are diagonal to 2^-66: the coupling
-// kappa^2 (T^-1)_{1,m} of two joint lines B = M * 2^levels rows apart against a diagonal of real
-// part at least 1.  More than 6 levels would leave the wavefront: -1.
+// Levels of lane blocks of M rows whose reduced systems are diagonal (joints M * 2^levels rows
+// apart).  More than 6 levels would leave the wavefront: -1.
 int window_levels(double kap, int M) {
-  for (int lv = nsk::kWinLevelMin; lv < nsk::kWinLevelMin + nsk::kNumWinLevel; ++lv) {
-    const double B = (double)(M << lv);
-    const double c = min_over(eta_max(kap), [&](double e) {
-      const double th = std::min(2.0 * kap * std::sinh(e), 1.0 - 1e-12);
-      return 2.0 * std::log(std::max(kap, 1e-30)) - e * (B - 2.0) - std::log(1.0 - th);
-    });
-    if (c <= -66.0 * M_LN2) return lv;
-  }
+  for (int lv = nsk::kWinLevelMin; lv < nsk::kWinLevelMin + nsk::kNumWinLevel; ++lv)
+    if (decoupled(kap, (double)(M << lv))) return lv;
   return -1;
 }
 
@@ -1205,13 +1217,13 @@ cn_status plan_link(const cn_layout* L, Plan& P) {
   const Launch& R = P.L[red];
   if (kCfgs[R.cfg].T() < 1024 || !nsk::tables().link[R.cfg][R.src][0]) return CN_OK;
   const int64_t n = (int64_t)R.grid.x * R.grid.y;
-  const size_t bytes = (size_t)n * (2 * 16 * sizeof(double) + sizeof(int)) + 4 * sizeof(int);
+  const size_t lines = (size_t)n * 2 * 16 * sizeof(double);
+  const size_t bytes = lines + (size_t)n * sizeof(int) + 4 * sizeof(int);
   if (hipMalloc((void**)&P.link, bytes) != hipSuccess) {
     (void)hipGetLastError();  // two passes then
     P.link = nullptr;
     return CN_OK;
   }
-  const size_t lines = (size_t)n * 2 * 16 * sizeof(double);
   if (hipMemset(P.link, 0xFF, lines) != hipSuccess ||
       hipMemset(P.link + lines, 0, bytes - lines) != hipSuccess)
     return CN_ERR_HIP;
@@ -1228,6 +1240,38 @@ cn_status plan_link(const cn_layout* L, Plan& P) {
   P.link_red = red;
   P.link_sub = sub;
   P.desc += "one pass over the tiles where their joints decouple; ";
+  return CN_OK;
+}
+
+// Device memory of the one-pass steps of an automatic plan of column tiles: lines for the most
+// tiles (the shortest ones) of all column groups.
+int64_t col_tile_min() {
+  int64_t t = INT64_MAX;
+  for (const Cfg& c : nsk::kColStepCfgs) t = std::min<int64_t>(t, (int64_t)c.M * c.W);
+  return t;
+}
+cn_status plan_colstep(const cn_layout* L, Plan& P) {
+  if (!link_enabled() || L->partition || L->rows_per_thread || L->levels || L->offsets ||
+      P.L.size() < 2 || P.L[0].level != 1 || P.L[0].cfg >= 0 || P.L[0].src != nsd::SRC_CN ||
+      P.L[0].ph != nsd::PH_REDUCE)
+    return CN_OK;
+  const int64_t tiles = (L->n + col_tile_min() - 1) / col_tile_min() * ((L->batch + 63) / 64);
+  const size_t lines = (size_t)tiles * 2 * 512 * sizeof(double);
+  const size_t bytes = lines + (4 + (size_t)tiles + 2 * (size_t)L->batch) * sizeof(int);
+  if (hipMalloc((void**)&P.col, bytes) != hipSuccess) {
+    (void)hipGetLastError();  // two passes then
+    P.col = nullptr;
+    return CN_OK;
+  }
+  if (hipMemset(P.col, 0xFF, lines) != hipSuccess ||
+      hipMemset(P.col + lines, 0, bytes - lines) != hipSuccess)
+    return CN_ERR_HIP;
+  P.col_bytes = bytes;
+  P.col_n = L->n;
+  P.col_batch = L->batch;
+  P.col_es = L->elem_stride;
+  P.col_tiles = tiles;
+  P.desc += "one pass where joints decouple in every potential; ";
   return CN_OK;
 }
 
@@ -1275,6 +1319,7 @@ cn_status get_plan(cn_handle_t h, const cn_layout* L, int src, hipStream_t s, Pl
     }
     bind_tables(*P, (char*)P->tables);
     st = plan_link(L, *P);
+    if (st == CN_OK) st = plan_colstep(L, *P);
     if (st != CN_OK) return st;
     if (log_enabled())
       fprintf(stderr, "cntri: plan for source %d, layout n=%lld batch=%lld%s: %s\n", src,
@@ -1369,10 +1414,90 @@ const char* phase_name(int ph) {
   return "persistent";
 }
 
+// The plan log's events around one launch (cn_profile); on: whether they are recorded.
+struct LogLaunch {
+  cn_handle_t h;
+  hipStream_t s;
+  bool on;
+  cn_handle_s::Rec r;
+  cn_status begin(const char* label) {
+    if (!on) return CN_OK;
+    r.label = label;
+    HIP_TRY(hipEventCreate(&r.e0));
+    HIP_TRY(hipEventCreate(&r.e1));
+    HIP_TRY(hipEventRecord(r.e0, s));
+    return CN_OK;
+  }
+  cn_status end() {
+    if (!on) return CN_OK;
+    HIP_TRY(hipEventRecord(r.e1, s));
+    h->recs.push_back(r);
+    return CN_OK;
+  }
+};
+
+// The tile of a one-pass step of column tiles: the shortest whose joints are decoupled for this
+// off-diagonal in every real potential, or -1.
+int colstep_cfg(Plan* P, double kap) {
+  if (kap != P->col_kap) {
+    P->col_kap = kap;
+    P->col_cfg = -1;
+    if (kap >= 1e-60 && std::isfinite(kap))
+      for (int i = 0; i < nsk::kNumColStepCfg && P->col_cfg < 0; ++i)
+        if (decoupled(kap, (double)(nsk::kColStepCfgs[i].M * nsk::kColStepCfgs[i].W)))
+          P->col_cfg = i;
+  }
+  return P->col_cfg;
+}
+
+cn_status run_colstep(cn_handle_t h, Plan* P, const UserArgs& u, int ci, hipStream_t s) {
+  const Cfg c = nsk::kColStepCfgs[ci];
+  const int64_t T = (int64_t)c.M * c.W, ncg = (P->col_batch + 63) / 64;
+  nsd::ColStepArgs a{};
+  a.in = u.psi;
+  a.out = u.x;
+  a.V = u.V;
+  a.xg = u.xg;
+  a.n = P->col_n;
+  a.es = P->col_es;
+  a.batch = P->col_batch;
+  a.ntiles = (P->col_n + T - 1) / T;
+  a.vscale = u.vscale;
+  a.E = u.E_mat;
+  a.tau = 0.5 * u.dt;
+  a.idx2 = 1.0 / (u.dx * u.dx);
+  a.kap = (0.5 * u.dt) * 0.5 * a.idx2;
+  a.lk = (double*)P->col;
+  a.lk_n = a.ntiles * ncg;
+  a.st = (int*)(a.lk + P->col_tiles * 2 * 512);
+  a.done = a.st + 4;
+  a.bad = a.done + P->col_tiles;
+  a.status = h->status;
+  void* params[] = {&a};
+  LogLaunch log{h, s, h->profiling && !capturing(s), {}};
+  for (int f = 0; f < 2; ++f) {
+    const unsigned grid = (unsigned)(f ? (a.lk_n + 3) / 4 : a.lk_n);
+    char lab[96];
+    snprintf(lab, sizeof(lab), "L1 %s T=%lld(M=%d,W=%d) grid=%ux1 threads=%d",
+             f ? "column-fix" : "column-step", (long long)T, c.M, c.W, grid, 64 * c.W);
+    cn_status st = log.begin(lab);
+    if (st != CN_OK) return st;
+    if (hipLaunchKernel(nsk::tables().colstep[ci][u.xg ? 1 : 0][f], dim3(grid), dim3(64 * c.W),
+                        params, 0, s) != hipSuccess)
+      return CN_ERR_HIP;
+    if ((st = log.end()) != CN_OK) return st;
+  }
+  return CN_OK;
+}
+
 cn_status run_plan(cn_handle_t h, Plan* P, const UserArgs& u, hipStream_t s,
                    void* ws_base = nullptr) {
   char* ws = (char*)(ws_base ? ws_base : h->ws);
-  const bool log = h->profiling && !capturing(s);
+  if (P->col && !ws_base && !u.rhs && !u.acc_pa && !u.dxs) {
+    const int ci = colstep_cfg(P, std::fabs((0.5 * u.dt) * 0.5 * (1.0 / (u.dx * u.dx))));
+    if (ci >= 0) return run_colstep(h, P, u, ci, s);
+  }
+  LogLaunch log{h, s, h->profiling && !capturing(s), {}};
   // One pass over the level-1 tiles.  A matrix whose joints couple makes it a first pass with
   // waits (2^24 rows 532 us against 448 in two passes; 253 where they decouple), so a plan whose
   // last pass left a tile takes 63 calls in two passes before it tries again; the results are the
@@ -1413,23 +1538,17 @@ cn_status run_plan(cn_handle_t h, Plan* P, const UserArgs& u, hipStream_t s,
         l.grid = dim3((unsigned)((P->link_n + 3) / 4));
       }
     }
-    cn_handle_s::Rec r;
-    if (log) {
+    if (log.on) {
       char lab[160];
       snprintf(lab, sizeof(lab), "L%d %s %s grid=%ux%u threads=%d", l.level,
                l.fn == aux_fn(nsk::AUX_RS_SERIAL) ? "serial-RS" : phase_name(l.ph),
                l.cfg >= 0 ? cfg_str(l.cfg).c_str() : "-", l.grid.x, l.grid.y, l.threads);
-      r.label = lab;
-      HIP_TRY(hipEventCreate(&r.e0));
-      HIP_TRY(hipEventCreate(&r.e1));
-      HIP_TRY(hipEventRecord(r.e0, s));
+      const cn_status st = log.begin(lab);
+      if (st != CN_OK) return st;
     }
     cn_status st = launch_k(l.fn, l, a, s);
+    if (st == CN_OK) st = log.end();
     if (st != CN_OK) return st;
-    if (log) {
-      HIP_TRY(hipEventRecord(r.e1, s));
-      h->recs.push_back(r);
-    }
   }
   return CN_OK;
 }
@@ -2865,7 +2984,7 @@ cn_status cn_handle_info(cn_handle_t h, int64_t* device_bytes, int64_t* retired_
   if (device_bytes) {
     size_t b = h->ws_size + h->ws2_size + h->seg2_bytes + h->mat_size + h->rad_size +
                h->rows_cap * sizeof(double);
-    for (const auto& kv : h->plans) b += kv.second->tables_bytes + kv.second->link_bytes;
+    for (const auto& kv : h->plans) b += kv.second->tables_bytes + kv.second->link_bytes + kv.second->col_bytes;
     *device_bytes = (int64_t)b;
   }
   if (retired_buffers) *retired_buffers = (int64_t)h->retired.size();

@@ -23,6 +23,12 @@ constexpr int kNumCfg = sizeof(kCfgs) / sizeof(kCfgs[0]);
 constexpr Cfg kColCfgs[] = {{4, 8}, {8, 4}, {8, 8}, {4, 16}, {16, 4}, {8, 16}};
 constexpr int kNumColCfg = sizeof(kColCfgs) / sizeof(kColCfgs[0]);
 
+// One-pass steps of interleaved batches (k_colstep): T = W M rows of 64 neighbouring systems.  64
+// rows decouple up to kappa = 0.52, 128 up to 1.1 (4096 x 4096: 150 and 176 us; 128 rows as 8 per
+// lane over 16 wavefronts 185).
+constexpr Cfg kColStepCfgs[] = {{8, 8}, {16, 8}};
+constexpr int kNumColStepCfg = sizeof(kColStepCfgs) / sizeof(kColStepCfgs[0]);
+
 // Resident propagations (k_resident): 8 rows per lane, tiles of 512, 1024 and 2048 rows.
 constexpr Cfg kResCfgs[] = {{8, 1}, {8, 2}, {8, 4}};
 constexpr int kNumResCfg = sizeof(kResCfgs) / sizeof(kResCfgs[0]);
@@ -61,6 +67,7 @@ struct Tables {
   // 1: k_tile_fix]
   const void* link[kNumCfg][kNumSrc][2];
   const void* cols[kNumColCfg][kNumSrc][3];
+  const void* colstep[kNumColStepCfg][2][2];  // [.][with a field][0: k_colstep, 1: k_colstep_fix]
   const void* mrhs[kNumCfg][3];  // one matrix, several right-hand sides (explicit source)
   const void* aux[kNumAux];
   const void* win[2][kNumWinCfg][kNumWinLevel][2];  // [with gradient][.][.][with a field]
@@ -83,6 +90,7 @@ void reg_cols(Tables& t);
 void reg_pers(Tables& t);
 void reg_mrhs(Tables& t);
 void reg_link(Tables& t);
+void reg_colstep(Tables& t);
 void reg_aux(Tables& t);
 void reg_windows(Tables& t);
 void reg_windows_grad(Tables& t);

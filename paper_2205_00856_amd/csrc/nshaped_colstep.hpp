@@ -1,0 +1,284 @@
+// A Crank-Nicolson step of an interleaved batch in one pass (gfx950, FP64 complex).
+//
+// As in k_cols, a wavefront's 64 lanes take 64 neighbouring systems (every row one coalesced
+// access) and a workgroup a tile of T = W M rows of them.  As in k_tile<PH_LINK>, a tile takes psi
+// at its two joint lines from its own slots and its neighbours': the host launches this form only
+// when joints T rows apart are decoupled in every real potential (decoupled(): 2^-66 of the
+// diagonal), so no reduced system is solved at all.  As in k_window, the step is T y = psi,
+// psi' = 2 y - psi on rows scaled by i / kappa, so a tile reads its own rows alone (no edge rows),
+// and may store them in place at any time after its loads.
+//
+// Where psi is needed again, for psi' = 2 y - psi, it is taken as T y from the solution's
+// neighbouring rows in registers, and the pivots are formed a second time on the way back: across
+// the exchange a row keeps D and the diagonal, 6 registers.
+//
+// The tile's line (DA, DD, UA, UD of 64 systems) is published word by word, all-ones words marking
+// what has not arrived; lines alternate between two buffers, and a pass clears the one of the
+// next.  A tile whose wait reaches its bound is left to k_colstep_fix, which runs it from the
+// lines, all there by then, with the same bits.  A system with a non-finite result is marked, and
+// k_colstep_fix makes all of it NaN, as exact steps would.
+//
+// Bound by memory: 40 bytes a row and the lines (16 KB written and 4 KB read per tile of 64 rows of
+// 64 systems, 160 KB of rows).  4096 x 4096 rows: 231 us in two passes (64 bytes a row, the second
+// pass at one wavefront per SIMD) -> 150; 1531 systems of 1000 rows 40.5 -> 20.6 us.
+#pragma once
+#include "nshaped_windows.hpp"
+
+namespace nsd {
+
+struct ColStepArgs {
+  const cd* in;
+  cd* out;
+  const double* V;
+  const double* xg;
+  int64_t n, es, batch, ntiles;  // rows and their stride, systems (stride 1), tiles of a system
+  double vscale, E, tau, kap, idx2;
+  double* lk;     // lines: [2][lk_n][8][64]
+  int64_t lk_n;   // tiles of all column groups
+  int* st;        // [buffer of the next pass, of this pass, whether pass of buffer 0, 1 needs a fix]
+  int* done;      // per tile: finished by the pass
+  int* bad;       // [2][batch]: systems with a non-finite result
+  int* status;
+};
+
+template <int W>
+struct ColStepSmem {
+  WBlk b[W][64];      // the blocks' matrix slots; after the elimination (B, C, dl) of joint w
+  WRhs<1> c[W][64];
+  cd jpsi[W + 1][64];  // psi (y) at the tile's joint lines
+  int ok;
+};
+
+// The tile bid of the launch, whose lines are in buffer e.  FIX: the lines are complete, and the
+// lanes of marked systems store NaN.  Returns false when the tile's neighbours did not publish.
+template <int M, int W, bool XG, bool FIX, bool IN>
+__device__ __forceinline__ void colstep_run(const ColStepArgs& A, ColStepSmem<W>& sm, int64_t bid,
+                                            int64_t ncg, int64_t tile, int64_t c0, int e) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool live = c0 + lane < A.batch;
+  const uint32_t ob16 = (uint32_t)((live ? lane : A.batch - 1 - c0) * 16), ob8 = ob16 / 2;
+  const int64_t r0 = tile * (M * W) + (int64_t)wave * M, n = A.n;
+  const double ik = 1.0 / A.kap, ck = -A.tau * ik;
+  const cd zero = czero();
+
+  cd D[M];
+  double va[M];
+  {
+    double v[M], xv[XG ? M : 1];
+    auto row = [&](int j) { return IN ? r0 + j : (r0 + j < n ? r0 + j : n - 1); };
+#pragma unroll
+    for (int j = 0; j < M; ++j) D[j] = col_at(A.in + c0, ob16, row(j), A.es);
+#pragma unroll
+    for (int j = 0; j < M; ++j) v[j] = col_at(A.V + c0, ob8, row(j), A.es);
+    if constexpr (XG) {
+#pragma unroll
+      for (int j = 0; j < M; ++j) xv[j] = col_at(A.xg + c0, ob8, row(j), A.es);
+    }
+#pragma unroll
+    for (int j = 0; j < M; ++j) {
+      D[j] = mk(-ik * D[j].y, ik * D[j].x);
+      va[j] = ck * (A.idx2 + (XG ? fma(xv[XG ? j : 0], A.E, A.vscale * v[j]) : A.vscale * v[j]));
+      if constexpr (!IN) {
+        D[j] = csel(r0 + j < n, D[j], zero);
+        va[j] = r0 + j < n ? va[j] : 0.0;
+      }
+    }
+  }
+  // v where rows r0 + i - 1 and r0 + i are both of the system, else zero
+  auto cpl = [&](int i, cd v) { return IN ? v : csel(r0 + i < n && r0 + i > 0, v, zero); };
+  WBlk b;
+  WRhs<1> c;
+  {
+    cd g = crecip(mk(va[1], ik));
+    cd beta = cpl(1, g);
+    D[1] = cmul(D[1], g);
+    cd fb = beta, fd = D[1];
+#pragma unroll
+    for (int i = 2; i < M; ++i) {
+      g = crecip(csub(mk(va[i], ik), cpl(i, g)));
+      D[i] = cmul(csub(D[i], cpl(i, D[i - 1])), g);
+      fd = cfms(beta, D[i], fd);
+      const cd bi = cpl(i, cneg(cmul(beta, g)));
+      fb = cfms(beta, bi, fb);
+      beta = bi;
+    }
+    b.UA = csub(mk(va[0], ik), fb);
+    b.C = cpl(M, cneg(beta));
+    b.DA = cpl(M, cneg(g));
+    c.UD[0] = csub(D[0], fd);
+    c.DD[0] = cpl(M, cneg(D[M - 1]));
+  }
+  sm.b[wave][lane] = b;
+  sm.c[wave][lane] = c;
+  __syncthreads();
+  if (wave == 0) {
+#pragma unroll 1
+    for (int w = 1; w < W; ++w) {
+      const WBlk o = sm.b[w][lane];
+      const WRhs<1> p = sm.c[w][lane];
+      WNode t;
+      wmerge(b, o, t);
+      cd dl[1];
+      wmerge_rhs<1>(c, p, t.ia, t.rU, t.rD, dl);
+      sm.b[w][lane].UA = t.B;
+      sm.b[w][lane].C = t.C;
+      sm.b[w][lane].DA = dl[0];
+    }
+    // ---- the joint lines of the tile from its own and its neighbours' slots
+    double* mine = A.lk + ((int64_t)e * A.lk_n + bid) * 512 + lane;
+    const bool left = tile > 0, right = tile + 1 < A.ntiles;
+    if constexpr (!FIX) {
+      const double v[8] = {b.DA.x, b.DA.y, c.DD[0].x, c.DD[0].y,
+                           b.UA.x, b.UA.y, c.UD[0].x, c.UD[0].y};
+#pragma unroll
+      for (int f = 0; f < 8; ++f)
+        __hip_atomic_store(mine + 64 * f, v[f], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      double* next = A.lk + ((int64_t)(1 - e) * A.lk_n + bid) * 512 + lane;
+#pragma unroll
+      for (int f = 0; f < 8; ++f) next[64 * f] = __longlong_as_double(-1ll);
+    }
+    const long long* sl = reinterpret_cast<const long long*>(mine - (left ? ncg * 512 : 0));
+    const long long* sr = reinterpret_cast<const long long*>(mine + (right ? ncg * 512 : 0)) + 256;
+    long long q[8];
+    bool in = false;
+    for (int it = 0; it <= kLinkSpin; ++it) {
+#pragma unroll
+      for (int f = 0; f < 4; ++f) {
+        q[f] = left ? __hip_atomic_load(sl + 64 * f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+        q[4 + f] =
+            right ? __hip_atomic_load(sr + 64 * f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+      }
+      if constexpr (FIX) break;
+      in = true;
+#pragma unroll
+      for (int f = 0; f < 8; ++f) in = in && q[f] != -1ll;
+      if (__all(in)) break;
+      __builtin_amdgcn_s_sleep(1);
+    }
+    double d[8];
+#pragma unroll
+    for (int f = 0; f < 8; ++f) d[f] = __longlong_as_double(q[f]);
+    const cd pJ = cmul(cadd(mk(d[2], d[3]), c.UD[0]), crecip(cadd(mk(d[0], d[1]), b.UA)));
+    const cd pM = right ? cmul(cadd(c.DD[0], mk(d[6], d[7])), crecip(cadd(b.DA, mk(d[4], d[5]))))
+                        : zero;
+    sm.jpsi[0][lane] = pJ;
+    sm.jpsi[W][lane] = pM;
+    cd y = pM;
+#pragma unroll 1
+    for (int w = W - 1; w >= 1; --w) {
+      const WBlk t = sm.b[w][lane];
+      y = cfms(t.C, y, cfms(t.UA, pJ, t.DA));
+      sm.jpsi[w][lane] = y;
+    }
+    if constexpr (!FIX) {
+      const bool ok = __all(in);
+      if (lane == 0) {
+        sm.ok = ok;
+        A.done[bid] = ok;
+        if (!ok) A.st[2 + e] = 1;
+        if (bid == 0) {
+          A.st[1] = e;
+          A.st[2 + (1 - e)] = 0;
+        }
+      }
+      if (tile == 0 && live) A.bad[(int64_t)(1 - e) * A.batch + c0 + lane] = 0;
+    }
+  }
+  __syncthreads();
+  if constexpr (!FIX) {
+    if (!sm.ok) return;
+  }
+  // ---- y upwards, psi' = 2 y - T y (row r0's right-hand side is still in D[0])
+  const cd pJ = sm.jpsi[wave][lane];
+  cd hi = sm.jpsi[wave + 1][lane];
+  bool bad = false;
+  bool seen = false;
+  if constexpr (FIX) seen = live && A.bad[(int64_t)e * A.batch + c0 + lane];
+  auto put = [&](int i, cd y, cd s) {
+    cd p = mk(fma(-A.kap, s.y, 2.0 * y.x), fma(A.kap, s.x, 2.0 * y.y));
+    const double nan = __builtin_nan("");
+    if constexpr (FIX) p = csel(seen, mk(nan, nan), p);
+    if (live && (IN || r0 + i < n)) {
+      col_at(A.out + c0, ob16, r0 + i, A.es) = p;
+      bad |= !cfinite(p);
+    }
+  };
+  // the pivots again (the empty asm hides that they are the same), dp_i = D_i - beta_i pJ
+#pragma unroll
+  for (int j = 1; j < M; ++j) asm volatile("" : "+v"(va[j]));
+  cd g[M];
+  g[1] = crecip(mk(va[1], ik));
+  cd beta = cpl(1, g[1]);
+  D[1] = cfms(beta, pJ, D[1]);
+#pragma unroll
+  for (int i = 2; i < M; ++i) {
+    g[i] = crecip(csub(mk(va[i], ik), cpl(i, g[i - 1])));
+    beta = cpl(i, cneg(cmul(beta, g[i])));
+    D[i] = cfms(beta, pJ, D[i]);
+  }
+  cd y = M > 1 ? cfms(g[M - 1], hi, D[M - 1]) : pJ;
+#pragma unroll
+  for (int i = M - 1; i >= 1; --i) {
+    const cd lo = i > 1 ? cfms(g[i > 1 ? i - 1 : 1], y, D[i > 1 ? i - 1 : 1]) : pJ;
+    const cd s = cfma(mk(va[i], ik), y, cadd(lo, hi));
+    put(i, y, s);
+    hi = y;
+    y = lo;
+  }
+  put(0, y, D[0]);
+  if (__any(bad)) {
+    if (lane == 0) {
+      atomicOr(A.status, 1);
+      A.st[2 + e] = 1;
+    }
+    if (!FIX && bad) A.bad[(int64_t)e * A.batch + c0 + lane] = 1;
+  }
+}
+
+template <int M, int W, bool XG, bool FIX>
+__device__ __forceinline__ void colstep_tile(const ColStepArgs& A, ColStepSmem<W>& sm, int64_t bid,
+                                             int e) {
+  // consecutive workgroups take neighbouring column groups of the same rows (long contiguous runs)
+  const int64_t ncg = (A.batch + 63) / 64, tile = bid / ncg, c0 = (bid - tile * ncg) * 64;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t r0 = tile * (M * W) + (int64_t)wave * M;
+  if (r0 >= 1 && r0 + M < A.n)
+    colstep_run<M, W, XG, FIX, true>(A, sm, bid, ncg, tile, c0, e);
+  else
+    colstep_run<M, W, XG, FIX, false>(A, sm, bid, ncg, tile, c0, e);
+}
+
+template <int M, int W, bool XG>
+__global__ __launch_bounds__(64 * W, M == 8 ? 4 : 2) void k_colstep(ColStepArgs A) {
+  __shared__ ColStepSmem<W> sm;
+  colstep_tile<M, W, XG, false>(A, sm, blockIdx.x, A.st[0] & 1);
+}
+
+// After a pass: the tiles it has left, and NaN for the systems it has marked; four tiles per
+// workgroup.  Nothing to do after nearly every pass.
+template <int M, int W, bool XG>
+__global__ __launch_bounds__(64 * W) void k_colstep_fix(ColStepArgs A) {
+  __shared__ ColStepSmem<W> sm;
+  const int e = A.st[1];
+  if (A.st[2 + e]) {
+    const int64_t ncg = (A.batch + 63) / 64;
+    for (int64_t bid = blockIdx.x; bid < A.lk_n; bid += gridDim.x) {
+      if (!A.done[bid]) {
+        colstep_tile<M, W, XG, true>(A, sm, bid, e);
+      } else {
+        const int64_t tile = bid / ncg, sys = (bid - tile * ncg) * 64 + (threadIdx.x & 63);
+        if (sys < A.batch && A.bad[(int64_t)e * A.batch + sys]) {
+          const double nan = __builtin_nan("");
+          for (int64_t r = tile * M * W + (threadIdx.x >> 6); r < (tile + 1) * M * W && r < A.n;
+               r += W)
+            A.out[sys + r * A.es] = mk(nan, nan);
+        }
+      }
+      __syncthreads();
+    }
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) A.st[0] = e ^ 1;
+}
+
+}  // namespace nsd
