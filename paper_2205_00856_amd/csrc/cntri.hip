@@ -19,6 +19,8 @@
 #include "kern_table.hpp"
 #include "nshaped_kernels.hpp"
 #include "nshaped_colstep.hpp"
+#include "nshaped_lstep.hpp"
+#include "nshaped_rowstep.hpp"
 #include "nshaped_windows.hpp"
 
 using nsd::cd;
@@ -39,6 +41,7 @@ nsk::Tables& nsk::tables() {
     reg_mrhs(x);
     reg_link(x);
     reg_colstep(x);
+    reg_rowstep(x);
     reg_aux(x);
     reg_resident(x);
     reg_windows(x);
@@ -257,12 +260,22 @@ struct Plan {
   int64_t col_n = 0, col_batch = 0, col_es = 0, col_tiles = 0;
   double col_kap = -1.0;
   int col_cfg = -1;
+  // steps of a contiguous batch in one pass (k_rowstep): whether the layout takes them, its
+  // shape, and for systems of several tiles the device memory (lines, then words, marks)
+  bool row = false;
+  char* row_mem = nullptr;
+  size_t row_bytes = 0;
+  int64_t row_n = 0, row_batch = 0, row_bs = 0, row_tiles = 0;
+  bool row_shared = false;
+  double row_kap = -1.0;
+  int row_cfg = -1, row_lv = 0;
   std::vector<char> host_tab;  // no-allocation plans: the tables, copied into scratch per call
   ~Plan() {
     if (tables) (void)hipFree(tables);
     if (link) (void)hipFree(link);
     if (link_hint) (void)hipHostFree(link_hint);
     if (col) (void)hipFree(col);
+    if (row_mem) (void)hipFree(row_mem);
   }
 };
 
@@ -1275,6 +1288,38 @@ cn_status plan_colstep(const cn_layout* L, Plan& P) {
   return CN_OK;
 }
 
+// The one-pass steps of contiguous batches: device memory for systems longer than one tile.
+constexpr int64_t kRowTile = 2048;  // of a longer system (2^24 rows 131 us; 1024 rows 134, 4096 141)
+cn_status plan_rowstep(const cn_layout* L, int src, Plan& P) {
+  if (!link_enabled() || src != nsd::SRC_CN || L->partition || L->rows_per_thread || L->levels ||
+      L->offsets || L->elem_stride != 1)
+    return CN_OK;
+  int64_t longest = 0;
+  for (const Cfg& c : nsk::kRowStepCfgs) longest = std::max(longest, c.T());
+  const int64_t tiles = (L->n + kRowTile - 1) / kRowTile * L->batch;
+  if (tiles > INT32_MAX) return CN_OK;
+  P.row_n = L->n;
+  P.row_batch = L->batch;
+  P.row_bs = L->batch_stride;
+  P.row_shared = L->shared_coefficients != 0;
+  if (L->n > longest) {
+    const size_t lines = (size_t)tiles * 2 * 8 * sizeof(double);
+    const size_t bytes = lines + (4 + (size_t)tiles + 2 * (size_t)L->batch) * sizeof(int);
+    if (hipMalloc((void**)&P.row_mem, bytes) != hipSuccess) {
+      (void)hipGetLastError();  // the other forms then
+      P.row_mem = nullptr;
+      return CN_OK;
+    }
+    if (hipMemset(P.row_mem, 0xFF, lines) != hipSuccess ||
+        hipMemset(P.row_mem + lines, 0, bytes - lines) != hipSuccess)
+      return CN_ERR_HIP;
+    P.row_bytes = bytes;
+    P.row_tiles = tiles;
+  }
+  P.row = true;
+  return CN_OK;
+}
+
 cn_status get_plan(cn_handle_t h, const cn_layout* L, int src, hipStream_t s, Plan** out) {
   int64_t rows = 0, span = 0;
   cn_status st = validate(L, rows, span);
@@ -1320,6 +1365,7 @@ cn_status get_plan(cn_handle_t h, const cn_layout* L, int src, hipStream_t s, Pl
     bind_tables(*P, (char*)P->tables);
     st = plan_link(L, *P);
     if (st == CN_OK) st = plan_colstep(L, *P);
+    if (st == CN_OK) st = plan_rowstep(L, src, *P);
     if (st != CN_OK) return st;
     if (log_enabled())
       fprintf(stderr, "cntri: plan for source %d, layout n=%lld batch=%lld%s: %s\n", src,
@@ -1420,9 +1466,13 @@ struct LogLaunch {
   hipStream_t s;
   bool on;
   cn_handle_s::Rec r;
-  cn_status begin(const char* label) {
+  // label(buffer, length) writes the launch's description
+  template <typename Label>
+  cn_status begin(const Label& label) {
     if (!on) return CN_OK;
-    r.label = label;
+    char lab[160];
+    label(lab, sizeof(lab));
+    r.label = lab;
     HIP_TRY(hipEventCreate(&r.e0));
     HIP_TRY(hipEventCreate(&r.e1));
     HIP_TRY(hipEventRecord(r.e0, s));
@@ -1435,6 +1485,10 @@ struct LogLaunch {
     return CN_OK;
   }
 };
+
+// Workgroups of the launch after a one-pass step, which has nothing to do unless a wait reached
+// its bound or a value was not finite (4096 x 4096: 4.9 us with one workgroup per four tiles).
+constexpr int64_t kFixGroups = 64;
 
 // The tile of a one-pass step of column tiles: the shortest whose joints are decoupled for this
 // off-diagonal in every real potential, or -1.
@@ -1476,13 +1530,77 @@ cn_status run_colstep(cn_handle_t h, Plan* P, const UserArgs& u, int ci, hipStre
   void* params[] = {&a};
   LogLaunch log{h, s, h->profiling && !capturing(s), {}};
   for (int f = 0; f < 2; ++f) {
-    const unsigned grid = (unsigned)(f ? (a.lk_n + 3) / 4 : a.lk_n);
-    char lab[96];
-    snprintf(lab, sizeof(lab), "L1 %s T=%lld(M=%d,W=%d) grid=%ux1 threads=%d",
-             f ? "column-fix" : "column-step", (long long)T, c.M, c.W, grid, 64 * c.W);
-    cn_status st = log.begin(lab);
+    const unsigned grid = (unsigned)(f ? std::min<int64_t>(a.lk_n, kFixGroups) : a.lk_n);
+    cn_status st = log.begin([&](char* lab, size_t len) {
+      snprintf(lab, len, "L1 %s T=%lld(M=%d,W=%d) grid=%ux1 threads=%d",
+               f ? "column-fix" : "column-step", (long long)T, c.M, c.W, grid, 64 * c.W);
+    });
     if (st != CN_OK) return st;
     if (hipLaunchKernel(nsk::tables().colstep[ci][u.xg ? 1 : 0][f], dim3(grid), dim3(64 * c.W),
+                        params, 0, s) != hipSuccess)
+      return CN_ERR_HIP;
+    if ((st = log.end()) != CN_OK) return st;
+  }
+  return CN_OK;
+}
+
+// The tile of a one-pass step of contiguous systems, or -1: the shortest that holds a system, for
+// longer ones 2048 rows; the off-diagonal has to decouple within a wavefront.
+int rowstep_cfg(Plan* P, double kap) {
+  if (kap != P->row_kap) {
+    P->row_kap = kap;
+    P->row_cfg = -1;
+    if (kap >= 1e-60 && std::isfinite(kap))
+      for (int i = 0; i < nsk::kNumRowStepCfg; ++i) {
+        const Cfg c = nsk::kRowStepCfgs[i];
+        if (P->row_mem ? c.T() != kRowTile : c.T() < P->row_n) continue;
+        const int lv = window_levels(kap, c.M);
+        if (lv < 0) continue;
+        P->row_cfg = i;
+        P->row_lv = lv;
+        break;
+      }
+  }
+  return P->row_cfg;
+}
+
+// l0, dr: partial waves (RowStepArgs), dr = 0 for none.
+cn_status run_rowstep(cn_handle_t h, Plan* P, const UserArgs& u, int ci, int64_t l0, double dr,
+                      hipStream_t s) {
+  const Cfg c = nsk::kRowStepCfgs[ci];
+  nsd::RowStepArgs a{};
+  a.in = u.psi;
+  a.out = u.x;
+  a.V = u.V;
+  a.xg = u.xg;
+  a.n = P->row_n;
+  a.bs = P->row_bs;
+  a.vbs = P->row_shared || dr > 0.0 ? 0 : P->row_bs;
+  a.ntiles = (P->row_n + c.T() - 1) / c.T();
+  a.lv = P->row_lv;
+  a.vscale = u.vscale;
+  a.E = u.E_mat;
+  a.tau = 0.5 * u.dt;
+  a.idx2 = 1.0 / (u.dx * u.dx);
+  a.kap = (0.5 * u.dt) * 0.5 * a.idx2;
+  a.l0 = l0;
+  a.dr = dr;
+  a.lk_n = a.ntiles * P->row_batch;
+  a.lk = (double*)P->row_mem;
+  a.st = (int*)(a.lk + P->row_tiles * 2 * 8);
+  a.done = a.st + 4;
+  a.bad = a.done + P->row_tiles;
+  a.status = h->status;
+  void* params[] = {&a};
+  LogLaunch log{h, s, h->profiling && !capturing(s), {}};
+  for (int f = 0; f < (a.ntiles > 1 ? 2 : 1); ++f) {
+    const unsigned grid = (unsigned)(f ? std::min<int64_t>(a.lk_n, kFixGroups) : a.lk_n);
+    cn_status st = log.begin([&](char* lab, size_t len) {
+      snprintf(lab, len, "L1 %s T=%lld(M=%d,W=%d) grid=%ux1 threads=%d",
+               f ? "step-fix" : "step", (long long)c.T(), c.M, c.W, grid, 64 * c.W);
+    });
+    if (st != CN_OK) return st;
+    if (hipLaunchKernel(nsk::tables().rowstep[ci][u.xg ? 1 : 0][f], dim3(grid), dim3(64 * c.W),
                         params, 0, s) != hipSuccess)
       return CN_ERR_HIP;
     if ((st = log.end()) != CN_OK) return st;
@@ -1493,9 +1611,13 @@ cn_status run_colstep(cn_handle_t h, Plan* P, const UserArgs& u, int ci, hipStre
 cn_status run_plan(cn_handle_t h, Plan* P, const UserArgs& u, hipStream_t s,
                    void* ws_base = nullptr) {
   char* ws = (char*)(ws_base ? ws_base : h->ws);
-  if (P->col && !ws_base && !u.rhs && !u.acc_pa && !u.dxs) {
-    const int ci = colstep_cfg(P, std::fabs((0.5 * u.dt) * 0.5 * (1.0 / (u.dx * u.dx))));
-    if (ci >= 0) return run_colstep(h, P, u, ci, s);
+  // plain steps in one pass (the lines of several tiles belong to the plan: a run on another
+  // workspace may overlap one on this)
+  if ((P->col || P->row) && !ws_base && !u.rhs && !u.acc_pa && !u.dxs) {
+    const double kap = std::fabs((0.5 * u.dt) * 0.5 * (1.0 / (u.dx * u.dx)));
+    const int ci = P->col ? colstep_cfg(P, kap) : rowstep_cfg(P, kap);
+    if (ci >= 0)
+      return P->col ? run_colstep(h, P, u, ci, s) : run_rowstep(h, P, u, ci, 0, 0.0, s);
   }
   LogLaunch log{h, s, h->profiling && !capturing(s), {}};
   // One pass over the level-1 tiles.  A matrix whose joints couple makes it a first pass with
@@ -1538,15 +1660,12 @@ cn_status run_plan(cn_handle_t h, Plan* P, const UserArgs& u, hipStream_t s,
         l.grid = dim3((unsigned)((P->link_n + 3) / 4));
       }
     }
-    if (log.on) {
-      char lab[160];
-      snprintf(lab, sizeof(lab), "L%d %s %s grid=%ux%u threads=%d", l.level,
+    cn_status st = log.begin([&](char* lab, size_t len) {
+      snprintf(lab, len, "L%d %s %s grid=%ux%u threads=%d", l.level,
                l.fn == aux_fn(nsk::AUX_RS_SERIAL) ? "serial-RS" : phase_name(l.ph),
                l.cfg >= 0 ? cfg_str(l.cfg).c_str() : "-", l.grid.x, l.grid.y, l.threads);
-      const cn_status st = log.begin(lab);
-      if (st != CN_OK) return st;
-    }
-    cn_status st = launch_k(l.fn, l, a, s);
+    });
+    if (st == CN_OK) st = launch_k(l.fn, l, a, s);
     if (st == CN_OK) st = log.end();
     if (st != CN_OK) return st;
   }
@@ -2984,7 +3103,8 @@ cn_status cn_handle_info(cn_handle_t h, int64_t* device_bytes, int64_t* retired_
   if (device_bytes) {
     size_t b = h->ws_size + h->ws2_size + h->seg2_bytes + h->mat_size + h->rad_size +
                h->rows_cap * sizeof(double);
-    for (const auto& kv : h->plans) b += kv.second->tables_bytes + kv.second->link_bytes + kv.second->col_bytes;
+    for (const auto& kv : h->plans) b += kv.second->tables_bytes + kv.second->link_bytes + kv.second->col_bytes +
+           kv.second->row_bytes;
     *device_bytes = (int64_t)b;
   }
   if (retired_buffers) *retired_buffers = (int64_t)h->retired.size();
@@ -3027,6 +3147,24 @@ cn_status cn_radial_step(cn_handle_t h, const cn_radial* op, double E, const voi
   }
   double* veff = (double*)h->rad;
   cd* m = (cd*)((char*)h->rad + vbytes);
+  // the radial part in one pass, the centrifugal potential formed with the rows (k_rowstep), and
+  // the field part of up to 64 waves as a real system (k_lstep)
+  cn_layout Lr{};
+  Lr.n = nr;
+  Lr.batch = nl;
+  Lr.elem_stride = 1;
+  Lr.batch_stride = nr;
+  Plan* Pr = nullptr;
+  cn_status st = get_plan(h, &Lr, nsd::SRC_CN, s, &Pr);
+  if (st != CN_OK) return st;
+  const int ci = Pr->row ? rowstep_cfg(Pr, std::fabs((0.5 * op->dt) * 0.5 *
+                                                     (1.0 / (op->dr * op->dr)))) : -1;
+  UserArgs ur;
+  ur.psi = (const cd*)psi_in;
+  ur.x = (cd*)psi_out;
+  ur.V = op->V;
+  ur.dx = op->dr;
+  ur.dt = op->dt;
   // radial part: V(r) + l(l+1)/(2 r^2) per wave, then the CN step of every wave in r
   nsd::AuxArgs X{};
   X.n = nr;
@@ -3039,20 +3177,36 @@ cn_status cn_radial_step(cn_handle_t h, const cn_radial* op, double E, const voi
   X.vscale = 1.0;
   X.wscale = 1.0;
   X.dV = veff;
-  cn_status st = launch_aux(aux_fn(nsk::AUX_RADIAL_VEFF), tot, X, s);
-  if (st != CN_OK) return st;
-  cn_layout Lr{};
-  Lr.n = nr;
-  Lr.batch = nl;
-  Lr.elem_stride = 1;
-  Lr.batch_stride = nr;
-  cn_operator o{};
-  o.V = veff;
-  o.v_scale = 1.0;
-  o.dx = op->dr;
-  o.dt = op->dt;
-  st = cn_step(h, &Lr, &o, 0.0, psi_in, psi_out, stream);
-  if (st != CN_OK || E == 0.0) return st;
+  if (ci >= 0) {
+    st = run_rowstep(h, Pr, ur, ci, op->l0, op->dr, s);
+    if (st != CN_OK || E == 0.0) return st;
+  } else {
+    st = launch_aux(aux_fn(nsk::AUX_RADIAL_VEFF), tot, X, s);
+    if (st != CN_OK) return st;
+    cn_operator o{};
+    o.V = veff;
+    o.v_scale = 1.0;
+    o.dx = op->dr;
+    o.dt = op->dt;
+    st = cn_step(h, &Lr, &o, 0.0, psi_in, psi_out, stream);
+    if (st != CN_OK || E == 0.0) return st;
+  }
+  if (fused && nl <= nsd::kLRows * nsd::kLWaves) {
+    nsd::LStepArgs a{};
+    a.in = (const cd*)psi_out;
+    a.out = (cd*)psi_out;
+    a.n = nl;
+    a.batch = nr;
+    a.l0 = op->l0;
+    a.s0 = 0.5 * op->dt * E * op->dr;
+    a.status = h->status;
+    void* params[] = {&a};
+    const int W = (int)((nl + nsd::kLRows - 1) / nsd::kLRows);
+    if (hipLaunchKernel(aux_fn(nsk::AUX_LSTEP), dim3((unsigned)((nr + 63) / 64)), dim3(64 * W),
+                        params, 0, s) != hipSuccess)
+      return CN_ERR_HIP;
+    return CN_OK;
+  }
   if (fused) {
     UserArgs u;
     u.psi = (const cd*)psi_out;

@@ -29,6 +29,10 @@ constexpr int kNumColCfg = sizeof(kColCfgs) / sizeof(kColCfgs[0]);
 constexpr Cfg kColStepCfgs[] = {{8, 8}, {16, 8}};
 constexpr int kNumColStepCfg = sizeof(kColStepCfgs) / sizeof(kColStepCfgs[0]);
 
+// One-pass steps of contiguous systems (k_rowstep): tiles of 64 W M rows.
+constexpr Cfg kRowStepCfgs[] = {{4, 1}, {6, 1}, {8, 1}, {6, 2}, {8, 2}, {6, 4}, {8, 4}, {6, 8}, {8, 8}};
+constexpr int kNumRowStepCfg = sizeof(kRowStepCfgs) / sizeof(kRowStepCfgs[0]);
+
 // Resident propagations (k_resident): 8 rows per lane, tiles of 512, 1024 and 2048 rows.
 constexpr Cfg kResCfgs[] = {{8, 1}, {8, 2}, {8, 4}};
 constexpr int kNumResCfg = sizeof(kResCfgs) / sizeof(kResCfgs[0]);
@@ -57,6 +61,7 @@ enum AuxKernel : int {
   AUX_RADIAL_VEFF,
   AUX_RADIAL_COUPLING,
   AUX_WINDOW_END,
+  AUX_LSTEP,
   kNumAux
 };
 
@@ -67,6 +72,7 @@ struct Tables {
   // 1: k_tile_fix]
   const void* link[kNumCfg][kNumSrc][2];
   const void* cols[kNumColCfg][kNumSrc][3];
+  const void* rowstep[kNumRowStepCfg][2][2];  // [.][with a field][0: k_rowstep, 1: k_rowstep_fix]
   const void* colstep[kNumColStepCfg][2][2];  // [.][with a field][0: k_colstep, 1: k_colstep_fix]
   const void* mrhs[kNumCfg][3];  // one matrix, several right-hand sides (explicit source)
   const void* aux[kNumAux];
@@ -91,6 +97,7 @@ void reg_pers(Tables& t);
 void reg_mrhs(Tables& t);
 void reg_link(Tables& t);
 void reg_colstep(Tables& t);
+void reg_rowstep(Tables& t);
 void reg_aux(Tables& t);
 void reg_windows(Tables& t);
 void reg_windows_grad(Tables& t);

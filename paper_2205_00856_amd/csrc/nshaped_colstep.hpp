@@ -255,13 +255,13 @@ __global__ __launch_bounds__(64 * W, M == 8 ? 4 : 2) void k_colstep(ColStepArgs 
   colstep_tile<M, W, XG, false>(A, sm, blockIdx.x, A.st[0] & 1);
 }
 
-// After a pass: the tiles it has left, and NaN for the systems it has marked; four tiles per
-// workgroup.  Nothing to do after nearly every pass.
+// After a pass: the tiles it has left, and NaN for the systems it has marked.  Nothing to do after
+// nearly every pass, so a few workgroups.
 template <int M, int W, bool XG>
 __global__ __launch_bounds__(64 * W) void k_colstep_fix(ColStepArgs A) {
   __shared__ ColStepSmem<W> sm;
-  const int e = A.st[1];
-  if (A.st[2 + e]) {
+  const int e = A.st[1], ask[2] = {A.st[2], A.st[3]};
+  if (ask[e]) {
     const int64_t ncg = (A.batch + 63) / 64;
     for (int64_t bid = blockIdx.x; bid < A.lk_n; bid += gridDim.x) {
       if (!A.done[bid]) {
