@@ -242,7 +242,9 @@ cn_status cn_step(cn_handle_t handle, const cn_layout* layout, const cn_operator
  * partition run on independent windows instead where that is faster (off-diagonals kappa up to
  * about 4): a window of up to 4096 rows, cut off from its line, takes up to 128 steps in one
  * launch with its rows in registers, and only its rows beyond the reach of the cut (below 2^-70
- * of the state for any real potential) are stored.  A non-finite value makes its whole line
+ * of the state for any real potential) are stored.  Sequences whose single steps run in one pass
+ * over the tiles (see cn_tridiag_solve; from 2^20 rows on, kappa up to 500 or a dx per system) run
+ * as such steps instead of chained passes.  A non-finite value makes its whole line
  * non-finite, as in single steps.  CN_WINDOWS=0 in the environment turns the windows off. */
 cn_status cn_propagate(cn_handle_t handle, const cn_layout* layout, const cn_operator* op,
                        int64_t nsteps, const double* E, void* psi, void* ckpt, int64_t K,

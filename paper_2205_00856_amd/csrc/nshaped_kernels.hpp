@@ -1062,7 +1062,7 @@ __device__ __forceinline__ void tile_finish(const KArgs& A, const Geo& G, TileSm
 // register above the budget of 3 wavefronts; the others keep the compiler's choice.
 template <int M, int PH, int SRC = SRC_CN>
 constexpr int tile_min_waves() {
-  return (PH == PH_FUSE && M == 8 && cn_src(SRC)) ? 3 : (PH == PH_LINK && M == 8 && SRC == SRC_CN) ? 4 : 1;
+  return (PH == PH_FUSE && M == 8 && cn_src(SRC)) ? 3 : (PH == PH_LINK && M == 8 && cn_src(SRC)) ? 4 : 1;
 }
 
 // The reduced system of a PH_FUSE pass over one system, solved in the same launch: every
