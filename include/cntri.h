@@ -177,7 +177,8 @@ cn_status cn_reserve(cn_handle_t handle, const cn_layout* layout);
  * where the tiles' joint lines couple to the next ones by less than 2^-66 of their diagonal (the
  * couplings fall exponentially with the tile's rows; decided tile by tile on the device): such a
  * joint takes its own row of the reduced system alone.  The other tiles are solved by the launches
- * that follow, with the whole reduced system.  cn_step and the adjoint solves run the same way.
+ * that follow, with the whole reduced system.  One matrix with several right-hand sides, cn_step
+ * and the adjoint solves run the same way.
  * CN_LINK=0 in the environment turns it off. */
 cn_status cn_tridiag_solve(cn_handle_t handle, const cn_layout* layout, const void* a,
                            const void* b, const void* c, const void* d, void* x,

@@ -248,7 +248,9 @@ struct Plan {
   // one pass instead of two for the level-1 tiles (k_tile<PH_LINK>): the launches it stands for,
   // the tiles, and the device memory of lines, marks and words; -1 / null without
   int link_red = -1, link_sub = -1;
-  int64_t link_n = 0;
+  int64_t link_n = 0, link_words = 0;
+  const void* link_fn[2] = {};
+  int link_rhs = 0;  // several right-hand sides of one matrix: those per workgroup
   char* link = nullptr;
   size_t link_bytes = 0;
   int* link_hint = nullptr;  // host memory: whether the last pass left a tile
@@ -1219,18 +1221,29 @@ bool link_enabled() {
 cn_status plan_link(const cn_layout* L, Plan& P) {
   if (!link_enabled() || L->partition || L->rows_per_thread || L->levels) return CN_OK;
   int red = -1, sub = -1;
+  bool mrhs = false;
   for (int i = 0; i < (int)P.L.size(); ++i) {
     const Launch& l = P.L[i];
     if (l.level != 1) continue;
     if (l.cfg < 0 || l.ph < 0) return CN_OK;
-    if (l.ph == nsd::PH_REDUCE && l.fn == g_kern[l.cfg][l.src][nsd::PH_REDUCE]) red = i;
-    if (l.ph == nsd::PH_SUBST && l.fn == g_kern[l.cfg][l.src][nsd::PH_SUBST]) sub = i;
+    if (l.ph == nsd::PH_REDUCE || l.ph == nsd::PH_SUBST) {
+      if (l.fn == g_mrhs[l.cfg][l.ph])
+        mrhs = true;
+      else if (l.fn != g_kern[l.cfg][l.src][l.ph])
+        return CN_OK;
+      (l.ph == nsd::PH_REDUCE ? red : sub) = i;
+    }
   }
   if (red < 0 || sub < 0 || P.L[red].cfg != P.L[sub].cfg) return CN_OK;
   const Launch& R = P.L[red];
-  if (kCfgs[R.cfg].T() < 1024 || !nsk::tables().link[R.cfg][R.src][0]) return CN_OK;
-  const int64_t n = (int64_t)R.grid.x * R.grid.y;
-  const size_t lines = (size_t)n * 2 * 16 * sizeof(double);
+  const void* const* fn = mrhs ? nsk::tables().mrhs_link[R.cfg] : nsk::tables().link[R.cfg][R.src];
+  if (kCfgs[R.cfg].T() < 1024 || !fn[0]) return CN_OK;
+  // (several right-hand sides: one workgroup for as many as it has wavefronts)
+  const int W = kCfgs[R.cfg].W;
+  const int64_t line = mrhs ? 8 + 4 * W : 16;
+  const int64_t n = mrhs ? R.a.ntiles * ((R.a.batch + W - 1) / W) : (int64_t)R.grid.x * R.grid.y;
+  if (n > INT32_MAX) return CN_OK;
+  const size_t lines = (size_t)n * 2 * line * sizeof(double);
   const size_t bytes = lines + (size_t)n * sizeof(int) + 4 * sizeof(int);
   if (hipMalloc((void**)&P.link, bytes) != hipSuccess) {
     (void)hipGetLastError();  // two passes then
@@ -1250,8 +1263,12 @@ cn_status plan_link(const cn_layout* L, Plan& P) {
   *P.link_hint = 0;
   P.link_bytes = bytes;
   P.link_n = n;
+  P.link_words = 2 * n * line;
+  P.link_fn[0] = fn[0];
+  P.link_fn[1] = fn[1];
   P.link_red = red;
   P.link_sub = sub;
+  P.link_rhs = mrhs ? W : 0;
   P.desc += "one pass over the tiles where their joints decouple; ";
   return CN_OK;
 }
@@ -1648,15 +1665,20 @@ cn_status run_plan(cn_handle_t h, Plan* P, const UserArgs& u, hipStream_t s,
     }
     if (link && (i == P->link_red || i == P->link_sub || l.level > 1)) {
       a.lk = (double*)P->link;
-      a.lk_done = (int*)(a.lk + 2 * 16 * P->link_n);
+      a.lk_done = (int*)(a.lk + P->link_words);
       a.lk_st = a.lk_done + P->link_n;
       a.lk_n = P->link_n;
       a.lk_hint = P->link_hint;
       if (i == P->link_red) {
-        l.fn = nsk::tables().link[l.cfg][l.src][0];
+        l.fn = P->link_fn[0];
+        if (P->link_rhs) {
+          l.grid = dim3((unsigned)P->link_n);
+          a.nrhs = P->link_rhs;
+        }
         l.ph = nsd::PH_LINK;
       } else if (i == P->link_sub) {
-        l.fn = nsk::tables().link[l.cfg][l.src][1];
+        l.fn = P->link_fn[1];
+        if (P->link_rhs) a.nrhs = P->link_rhs;
         l.grid = dim3((unsigned)((P->link_n + 3) / 4));
       }
     }

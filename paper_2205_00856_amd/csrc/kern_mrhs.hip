@@ -24,6 +24,9 @@ void reg_mrhs(Tables& t) {
   reg_one<4, 4>(t);
   reg_one<4, 8>(t);
   reg_one<8, 4>(t);
+  constexpr int I = cfg_index<4, 4>();  // the tile of automatic plans from 2^20 rows on
+  t.mrhs_link[I][0] = (const void*)&nsd::k_mrhs_link<4, 4>;
+  t.mrhs_link[I][1] = (const void*)&nsd::k_mrhs_fix<4, 4>;
 }
 
 }  // namespace nsk

@@ -98,8 +98,8 @@ struct KArgs {
   const double* Wabs;
   double wscale;
   int64_t l0;  // SRC_LCOUP: partial wave of row 0
-  // PH_LINK and the launches after it: a line of 16 values per tile in each of two buffers of
-  // lk_n lines, words [buffer of the next pass, buffer of this one, whether the pass
+  // PH_LINK and the launches after it: a line per tile (16 values; k_mrhs_link: of a tile and its
+  // right-hand sides) in each of two buffers of lk_n lines, words [buffer of the next pass, buffer of this one, whether the pass
   // of buffer 0, 1 left a tile], and per tile whether the pass has finished it
   double* lk;
   int* lk_st;
@@ -865,8 +865,9 @@ __device__ __forceinline__ void tile_core(const KArgs& A, const Geo& G, SM& sm, 
       pJ = A.psi_if[G.gt];
       const cd nxt = A.psi_if[(G.tile + 1 < G.ntile) ? G.gt + 1 : G.gt];
       pM = csel(G.tile + 1 < G.ntile, nxt, czero());
-      if (SRC != SRC_SLOTS && A.lk_n) {
-        // the joints that a PH_LINK pass takes, where they decouple
+      if (SRC != SRC_SLOTS && A.lk_n && cfinite(pJ) && cfinite(pM)) {
+        // the joints that a PH_LINK pass takes, where they decouple (a joint that is not finite
+        // makes the whole system so)
         const bool lf = G.tile > 0, rt = G.tile + 1 < G.ntile;
         const cd* l = A.oD + 3 * (lf ? G.gt - 1 : G.gt);
         const cd* r = A.oU + 3 * (rt ? G.gt + 1 : G.gt);
@@ -1548,6 +1549,22 @@ __device__ __forceinline__ bool mrhs_step(const KArgs& A, const Geo& G0, MrhsSme
     } else {
       pJ = qJ;
       pM = csel(G.tile + 1 < G.ntile, qM, zero);
+      if (A.lk_n && cfinite(pJ) && cfinite(pM)) {
+        // the joints that a linked pass takes, where they decouple
+        Blk b = top;
+        b.UD = UD;
+        b.DD = DD;
+        const bool lf = G.tile > 0, rt = G.tile + 1 < G.ntile;
+        const cd* l = A.oD + 3 * (lf ? G.gt - 1 : G.gt);
+        const cd* rr = A.oU + 3 * (rt ? G.gt + 1 : G.gt);
+        cd jJ, jM;
+        if (link_joints(b, csel(lf, l[1], zero), csel(lf, l[2], zero), lf ? cmag(l[0]) : 0.0,
+                        csel(rt, rr[0], zero), csel(rt, rr[2], zero), rt ? cmag(rr[1]) : 0.0, rt,
+                        jJ, jM)) {
+          pJ = jJ;
+          pM = jM;
+        }
+      }
     }
   }
   if constexpr (PH != PH_REDUCE) {
@@ -1575,18 +1592,15 @@ __device__ __forceinline__ bool mrhs_step(const KArgs& A, const Geo& G0, MrhsSme
   return true;
 }
 
-template <int M, int W, int PH, bool IN>
-__device__ __forceinline__ void tile_run_mrhs(const KArgs& A, const Geo& G0, MrhsSmem<M, W>& sm,
-                                              int64_t w0, int64_t J, int lane, int wave) {
+// The matrix of a tile, loaded and factored: F, the factors of the nesting levels in sm, and the
+// matrix part of the whole tile's block in top (wavefront 0, lane 0).
+template <int M, int W, bool IN>
+__device__ __forceinline__ void mrhs_factor(const KArgs& A, const Geo& G0, MrhsSmem<M, W>& sm,
+                                            cd* buf, BlkFac<M>& F, Blk& top, int64_t w0, int64_t J,
+                                            int lane, int wave) {
   constexpr int LW = Log2<W>::v;
   const int64_t n = G0.n;
   const cd one = mk(1.0, 0.0), zero = czero();
-  cd* buf = sm.t.lds[wave];
-  cd* wdl = buf;
-  cd* xdl = reinterpret_cast<cd*>(sm.t.xnode);
-  static_assert(sizeof(cd) * 64 <= sizeof(Node) * 64, "node values fit the node space");
-  BlkFac<M> F;
-  Blk top;  // wavefront 0, lane 0: the matrix part of the whole tile's block
   {
     cd va[M + 2], vb[M + 2], vc[M + 2];
     {
@@ -1624,15 +1638,30 @@ __device__ __forceinline__ void tile_run_mrhs(const KArgs& A, const Geo& G0, Mrh
     }
     __syncthreads();  // the partial blocks' space is the right-hand sides' from here on
   }
+}
+
+// r0: the first right-hand side to take (those before it are done).
+template <int M, int W, int PH, bool IN>
+__device__ __forceinline__ void tile_run_mrhs(const KArgs& A, const Geo& G0, MrhsSmem<M, W>& sm,
+                                              int64_t w0, int64_t J, int lane, int wave,
+                                              int r0 = 0) {
+  const int64_t n = G0.n;
+  cd* buf = sm.t.lds[wave];
+  cd* wdl = buf;
+  cd* xdl = reinterpret_cast<cd*>(sm.t.xnode);
+  static_assert(sizeof(cd) * 64 <= sizeof(Node) * 64, "node values fit the node space");
+  BlkFac<M> F;
+  Blk top;  // wavefront 0, lane 0: the matrix part of the whole tile's block
+  mrhs_factor<M, W, IN>(A, G0, sm, buf, F, top, w0, J, lane, wave);
 
   const int64_t s0 = G0.sys * A.nrhs;
   // d of the next two right-hand sides is in flight while one is eliminated: two register
   // buffers, each refilled as soon as its rows are in LDS
   cd rdA[M], rdB[M];
-  if (s0 < A.batch) rhs_fetch<M, IN>(A.d + s0 * A.bs, G0.es, w0, n, lane, rdA);
-  if (A.nrhs > 1 && s0 + 1 < A.batch)
-    rhs_fetch<M, IN>(A.d + (s0 + 1) * A.bs, G0.es, w0, n, lane, rdB);
-  for (int r = 0; r < A.nrhs; r += 2) {
+  if (s0 + r0 < A.batch) rhs_fetch<M, IN>(A.d + (s0 + r0) * A.bs, G0.es, w0, n, lane, rdA);
+  if (A.nrhs > r0 + 1 && s0 + r0 + 1 < A.batch)
+    rhs_fetch<M, IN>(A.d + (s0 + r0 + 1) * A.bs, G0.es, w0, n, lane, rdB);
+  for (int r = r0; r < A.nrhs; r += 2) {
     if (!mrhs_step<M, W, PH, IN>(A, G0, sm, buf, wdl, xdl, F, top, w0, J, lane, wave, s0, r, rdA))
       break;
     if (!mrhs_step<M, W, PH, IN>(A, G0, sm, buf, wdl, xdl, F, top, w0, J, lane, wave, s0, r + 1,
@@ -1654,6 +1683,239 @@ __global__ __launch_bounds__(64 * W) void k_tile_mrhs(KArgs A) {
     tile_run_mrhs<M, W, PH, true>(A, G, sm, w0, J, lane, wave);
   else
     tile_run_mrhs<M, W, PH, false>(A, G, sm, w0, J, lane, wave);
+}
+
+// The same in one pass (as k_tile<PH_LINK>), W right-hand sides per workgroup: the rows of all of
+// them stay in registers across one exchange with the neighbouring tiles.  Every wavefront reduces
+// its rows of every right-hand side; then wavefront r takes right-hand side r through the levels
+// across the wavefronts, publishes it, polls for its neighbours' and goes down again, so the W
+// chains run side by side.  The matrix is loaded and factored once per W right-hand sides: the
+// groups of one tile go to one XCD, whose L2 serves all but the first.  The slots go to oU, oD as
+// well, for the launches that follow; done holds a bit per right-hand side that is finished (none
+// where the tile's joints couple).
+//   2^22 rows x 16: 812 us in two passes (3.6 GB) -> 703 (2.35 GB), two workgroups per CU at 188
+// registers and 79 KB of LDS.  All 16 right-hand sides in turn in one workgroup, one exchange each,
+// took 910 us (each right-hand side waits for a round trip to memory); a workgroup per right-hand
+// side, the matrix from L2, 814.
+template <int M, int W>
+struct MrhsLinkSmem {
+  MrhsSmem<M, W> m;
+  cd wdl[W][W][64], xdl[W][64];  // node values per right-hand side
+  cd part[W][64][2];             // per right-hand side: UD, DD of the partial blocks, then their psi
+  Blk top;
+  double lkv[W][16];
+  int go[W];
+};
+
+template <int M, int W, bool IN>
+__device__ __forceinline__ void mrhs_link_run(const KArgs& A, const Geo& G0, MrhsLinkSmem<M, W>& sm,
+                                              int64_t w0, int64_t J, int lane, int wave) {
+  constexpr int LW = Log2<W>::v;
+  const int64_t n = G0.n;
+  const cd zero = czero();
+  cd* buf = sm.m.t.lds[wave];
+  const int64_t s0 = G0.sys * W;
+  const int nr = (int)(A.batch - s0 < W ? A.batch - s0 : W);
+  const int e = A.lk_st[0] & 1;
+  const int64_t gl = G0.sys * A.ntiles + G0.tile;
+  constexpr int kLen = 8 + 4 * W;  // of a line: DA, |DB|, UA, |UC|; then DD, UD of each
+  double* mine = A.lk + ((int64_t)e * A.lk_n + gl) * kLen;
+  const bool left = G0.tile > 0, right = G0.tile + 1 < G0.ntile;
+
+  cd D[W][M];
+#pragma unroll
+  for (int r = 0; r < W; ++r)
+    if (r < nr) rhs_fetch<M, IN>(A.d + (s0 + r) * A.bs, G0.es, w0, n, lane, D[r]);
+  BlkFac<M> F;
+  Blk top;
+  mrhs_factor<M, W, IN>(A, G0, sm.m, buf, F, top, w0, J, lane, wave);
+  if (wave == 0) {
+    double* next = A.lk + ((int64_t)(1 - e) * A.lk_n + gl) * kLen;
+    if (lane < kLen) next[lane] = __longlong_as_double(-1ll);
+    if (lane == 0) {
+      sm.top = top;
+      sm.lkv[0][0] = top.DA.x;
+      sm.lkv[0][1] = top.DA.y;
+      sm.lkv[0][2] = cmag(top.DB);
+      sm.lkv[0][3] = top.UA.x;
+      sm.lkv[0][4] = top.UA.y;
+      sm.lkv[0][5] = cmag(top.UC);
+    }
+    wave_sync();
+    if (lane < 6)
+      __hip_atomic_store(mine + lane, sm.lkv[0][lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+#pragma unroll
+  for (int r = 0; r < W; ++r) {
+    if (r >= nr) break;
+    cd vd[M + 2];
+    transpose_in<M>(buf, lane, D[r], zero, vd);
+#pragma unroll
+    for (int j = 0; j < M; ++j) D[r][j] = csel(row_in<IN>(J + j, n), vd[j + 1], zero);
+    cd UD, DD;
+    reduce_block_rhs<M>(F, D[r], UD, DD);
+    tree_up_rhs<LW>(UD, DD, sm.m.wfac[wave], sm.wdl[r][wave], lane);
+    if ((lane & (W - 1)) == 0) {
+      sm.part[r][wave * (64 / W) + (lane >> LW)][0] = UD;
+      sm.part[r][wave * (64 / W) + (lane >> LW)][1] = DD;
+    }
+  }
+  __syncthreads();
+  if (wave < nr) {
+    const int r = wave;
+    cd UD = sm.part[r][lane][0], DD = sm.part[r][lane][1];
+    tree_up_rhs<6>(UD, DD, sm.m.xfac, sm.xdl[r], lane);
+    const Blk t = sm.top;
+    if (lane == 0) {
+      const int64_t gt = (s0 + r) * A.ntiles + G0.tile;
+      A.oU[3 * gt] = t.UA;
+      A.oU[3 * gt + 1] = t.UC;
+      A.oU[3 * gt + 2] = UD;
+      A.oD[3 * gt] = t.DB;
+      A.oD[3 * gt + 1] = t.DA;
+      A.oD[3 * gt + 2] = DD;
+    }
+    const double v[4] = {DD.x, DD.y, UD.x, UD.y};
+    double w = 0.0;
+#pragma unroll
+    for (int f = 0; f < 4; ++f) {
+      const double q = __shfl(v[f], 0, 64);
+      w = lane == f ? q : w;
+    }
+    if (lane < 4)
+      __hip_atomic_store(mine + 8 + 4 * r + lane, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // lanes 0 .. 4: DA, |DB|, DD of the tile before; 8 .. 12: UA, |UC|, UD of the tile after
+    const int f = lane & 7;
+    const bool act = lane < 16 && f < 5 && (lane < 8 ? left : right);
+    const int word = f < 3 ? (lane < 8 ? f : 3 + f) : 8 + 4 * r + (lane < 8 ? f - 3 : f - 1);
+    const long long* src =
+        reinterpret_cast<const long long*>(mine) + (act ? (lane < 8 ? -kLen : kLen) + word : 0);
+    long long q = act ? -1ll : 0ll;
+    for (int it = 0;; ++it) {
+      if (q == -1ll) q = __hip_atomic_load(src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (__all(q != -1ll) || it >= kLinkSpin) break;
+      __builtin_amdgcn_s_sleep(1);
+    }
+    bool ok = __all(q != -1ll);
+    wave_sync();
+    if (lane < 16) sm.lkv[r][lane] = __longlong_as_double(q);
+    wave_sync();
+    const double* k = sm.lkv[r];
+    Blk b = t;
+    b.UD = UD;
+    b.DD = DD;
+    cd pJ, pM;
+    const bool dec = link_joints(b, mk(k[0], k[1]), mk(k[3], k[4]), k[2], mk(k[8], k[9]),
+                                 mk(k[11], k[12]), k[10], right, pJ, pM);
+    ok = ok && __builtin_amdgcn_readfirstlane(dec);
+    tree_down_fac<6>(pJ, pM, sm.m.xfac, sm.xdl[r], lane);
+    sm.part[r][lane][0] = pJ;
+    sm.part[r][lane][1] = pM;
+    if (lane == 0) sm.go[r] = ok;
+  }
+  __syncthreads();
+  int done = 0;
+#pragma unroll
+  for (int r = 0; r < W; ++r) {
+    if (r >= nr) break;
+    if (!sm.go[r]) continue;
+    done |= 1 << r;
+    const cd* p = sm.part[r][wave * (64 / W) + (lane >> LW)];
+    cd pJ = p[0], pM = p[1];
+    tree_down_fac<LW>(pJ, pM, sm.m.wfac[wave], sm.wdl[r][wave], lane);
+    cd xo[M];
+    ss_block<M>(F.Bt, F.Ct, D[r], pJ, pM, xo);
+    Geo G = G0;
+    G.sys = s0 + r;
+    G.base = G.sys * A.bs;
+    check_rows<M, IN>(A, G, J, lane, xo);
+    store_tile<M, W, SRC_EXPL, IN>(A, G, sm.m.t, buf, w0, lane, wave, xo);
+  }
+  if (threadIdx.x == 0) {
+    A.lk_done[gl] = done;
+    if (done != (1 << nr) - 1) A.lk_st[2 + e] = 1;
+    if (gl == 0) {
+      A.lk_st[1] = e;
+      A.lk_st[2 + (1 - e)] = 0;
+    }
+  }
+}
+
+// Workgroup id of a grid of ntiles * groups: groups of a tile, and neighbouring tiles, in rounds of
+// 8 tiles, so that the groups of a tile have ids equal mod 8 (one XCD).
+__device__ __forceinline__ void mrhs_link_item(int64_t id, int64_t ntiles, int64_t groups,
+                                               int64_t& tile, int64_t& group) {
+  const int64_t full = ntiles / 8 * 8;
+  if (id < full * groups) {
+    const int64_t q = id / (8 * groups), m = id - q * 8 * groups;
+    tile = q * 8 + (m & 7);
+    group = m >> 3;
+  } else {
+    const int64_t m = id - full * groups, rest = ntiles - full;
+    tile = full + m % rest;
+    group = m / rest;
+  }
+}
+
+template <int M, int W>
+__global__ __launch_bounds__(64 * W, 2) void k_mrhs_link(KArgs A) {
+  static_assert(W > 1, "levels across wavefronts");
+  __shared__ MrhsLinkSmem<M, W> sm;
+  int64_t tile, group;
+  mrhs_link_item(blockIdx.x, A.ntiles, (A.batch + W - 1) / W, tile, group);
+  const Geo G = geometry<PH_REDUCE>(A, (unsigned)tile, (unsigned)group);
+  constexpr int64_t T = 64 * W * M;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t w0 = G.tile * T + (int64_t)wave * 64 * M;
+  const int64_t J = w0 + (int64_t)lane * M;
+  if (w0 >= 1 && G.n >= w0 + 64 * M + 1)
+    mrhs_link_run<M, W, true>(A, G, sm, w0, J, lane, wave);
+  else
+    mrhs_link_run<M, W, false>(A, G, sm, w0, J, lane, wave);
+}
+
+// k_tile_fix for several right-hand sides: those that a tile has not finished, from the first of
+// them to the last (A.nrhs = W, as the pass).
+template <int M, int W>
+__global__ __launch_bounds__(64 * W) void k_mrhs_fix(KArgs A) {
+  __shared__ MrhsSmem<M, W> sm;
+  constexpr int64_t T = 64 * W * M;
+  const int lane = threadIdx.x & 63;
+  const int wave = threadIdx.x >> 6;
+  const int cur = A.lk_st[1];
+  if (!link_idle(A)) {
+    for (int64_t i = blockIdx.x; i < A.lk_n; i += gridDim.x) {
+      const Geo G = geometry<PH_REDUCE>(A, (unsigned)(i % A.ntiles), (unsigned)(i / A.ntiles));
+      const int done = A.lk_done[i];
+      const int64_t s0 = G.sys * W;
+      const int64_t w0 = G.tile * T + (int64_t)wave * 64 * M;
+      const int64_t J = w0 + (int64_t)lane * M;
+      for (int r = 0; r < W && s0 + r < A.batch; ++r) {
+        if (!((done >> r) & 1)) {
+          // right-hand side r alone: a batch of r + 1 that starts there
+          KArgs B = A;
+          B.batch = s0 + r + 1;
+          __syncthreads();
+          if (w0 >= 1 && G.n >= w0 + 64 * M + 1)
+            tile_run_mrhs<M, W, PH_SUBST, true>(B, G, sm, w0, J, lane, wave, r);
+          else
+            tile_run_mrhs<M, W, PH_SUBST, false>(B, G, sm, w0, J, lane, wave, r);
+          continue;
+        }
+        const int64_t gt = (s0 + r) * A.ntiles + G.tile;
+        if (cfinite(A.psi_if[gt]) && (G.tile + 1 >= G.ntile || cfinite(A.psi_if[gt + 1]))) continue;
+        const double nan = __builtin_nan("");
+        for (int64_t q = G.tile * T + threadIdx.x; q < (G.tile + 1) * T && q < G.n; q += 64 * W)
+          A.x[(s0 + r) * A.bs + q * G.es] = mk(nan, nan);
+      }
+      __syncthreads();
+    }
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    A.lk_st[0] = cur ^ 1;
+    __hip_atomic_store(A.lk_hint, A.lk_st[2 + cur], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
 }
 
 // ------------------------------------------------------------------ interleaved batches

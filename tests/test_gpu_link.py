@@ -189,3 +189,31 @@ def test_non_finite(gpu):
         assert torch.equal(x[s], want[s])
     assert torch.equal(cn.solve(a, b, c, d, layout=L), want)
     assert cn.get_status() == 0
+
+
+@pytest.mark.parametrize("n,batch", [(N, 1 + 15), (1 << 20, 2), (N, 5)])
+@pytest.mark.parametrize("kind", ["fast", "slow", "mixed"])
+def test_several_right_hand_sides(gpu, oracle_mod, kind, n, batch):
+    """One matrix with an even and an odd number of right-hand sides, in place."""
+    torch, cn = gpu
+    a, b, c, _ = system(n, kind)
+    d = np.stack([system(n, "fast", s)[3] for s in range(batch)])
+    ta, tb, tc, td = dev(torch, a, b, c, d)
+    L = cn.Layout.contiguous(n, batch, shared_coefficients=True)
+    assert "one pass" in cn.describe_plan(L) and "rhs/wg=" in cn.describe_plan(L)
+    x = cn.solve(ta, tb, tc, td, layout=L)
+    for s in {0, batch // 2, batch - 1}:
+        check(torch, cn, oracle_mod, kind, (a, b, c, d[s]), x[s])
+    for _ in range(2):
+        y = td.clone()
+        cn.solve(ta, tb, tc, y, out=y, layout=L)
+        assert torch.equal(x, y)
+    bad = td.clone()
+    bad[batch - 1, n // 2] = float("inf")
+    cn.get_status() if kind == "fast" else None
+    cn.solve(ta, tb, tc, bad, out=bad, layout=L)
+    assert cn.get_status() == 1
+    assert not torch.isfinite(torch.view_as_real(bad[batch - 1])).any()
+    assert torch.equal(bad[:-1], x[:-1])
+    assert torch.equal(cn.solve(ta, tb, tc, td, layout=L), x)
+    assert cn.get_status() == 0
