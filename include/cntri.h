@@ -173,7 +173,7 @@ cn_status cn_reserve(cn_handle_t handle, const cn_layout* layout);
  * Table 1) -- partition-local RD+JD and RU+JU sweeps, the reduced system on the joint
  * lines solved by nesting the same method (Sec. 4.1.6, Eq. (6)) and, at the top, the RS
  * stage; then SS back-substitution on every level.  x may alias d; a, b, c are read only.
- * From 2^20 rows on, automatic plans of systems in several tiles run in one pass over memory
+ * From 2^16 rows on, automatic plans of systems in several tiles run in one pass over memory
  * where the tiles' joint lines couple to the next ones by less than 2^-66 of their diagonal (the
  * couplings fall exponentially with the tile's rows; decided tile by tile on the device): such a
  * joint takes its own row of the reduced system alone.  The other tiles are solved by the launches

@@ -321,6 +321,11 @@ struct BatchDesc {
   std::vector<int64_t> offs;
 };
 
+// Shortest tile of a solve in one pass (plan_link).  From 2^16 rows on such tiles replace those of
+// 256 rows: 2^19 rows 28 -> 17 us, 10^5 rows x 16 right-hand sides 51 -> 27 us, 2^16 rows 17.4 ->
+// 15.4 us (18.4 in two passes, where the joints couple).
+constexpr int64_t kLinkTile = 512;
+
 int multi_cfg(int64_t n, int64_t batch, const Knobs& k, int level, int src) {
   if (level == 1 && k.partition > 0) {
     int M = k.rpt > 0 ? k.rpt : (k.partition >= 512 ? 8 : 4);
@@ -339,7 +344,10 @@ int multi_cfg(int64_t n, int64_t batch, const Knobs& k, int level, int src) {
   // enough tiles to fill the chip (>= 4 workgroups per CU when the system allows it)
   const int64_t target = 1024;
   int64_t T = 1024;
-  while (T > 256 && batch * ((n + T - 1) / T) < target) T /= 2;
+  // a solve of 2^16 rows or more: tiles whose joints may decouple (plan_link)
+  const bool expl = level == 1 && (src == nsd::SRC_EXPL || src == nsd::SRC_EXPL_CT) &&
+                    n * batch >= ((int64_t)1 << 16);
+  while (T > (expl ? kLinkTile : 256) && batch * ((n + T - 1) / T) < target) T /= 2;
   int M = (level == 1 && k.rpt > 0) ? k.rpt : 4;
   int ci = find_cfg(T, M);
   if (ci < 0) ci = find_cfg(T, 4);
@@ -494,7 +502,10 @@ void plan_level(Builder& B, std::vector<Launch>& L, const BatchDesc& bd, int src
     int ci_single = -1;
     if (level == 1 && kn.partition > 0) {
       if (n <= kn.partition) ci_single = multi_cfg(n, batch, kn, level, src);
-    } else if (n <= kSingleMax && (batch >= 64 || n <= 1024 || level > 1)) {
+    } else if (n <= kSingleMax &&
+               (batch >= 64 || n <= 1024 || level > 1 ||
+                (n <= 2048 && (src == nsd::SRC_EXPL || src == nsd::SRC_EXPL_CT)))) {
+      // (a few solves of 1025 to 2048 rows: one launch 12 us, two passes 17)
       ci_single = single_cfg(n);
       // reduced systems of up to 64 joints: one row per lane, no idle lanes (the ADI y-sweep's
       // 4096 systems of 64 joints: 0.5 % of the step faster than 2 rows on half the lanes)
@@ -1215,9 +1226,9 @@ bool link_enabled() {
 }
 
 // Whether the level-1 tiles of an automatic plan are taken in one pass, and its device memory.
-// Tiles of at least 1024 rows: their joints decouple when the inverse falls faster than 0.956 a
-// row (a Crank-Nicolson matrix with kappa = 50 in a potential near zero: 0.904), and the launches
-// of plans with smaller tiles (below 2^20 rows) are bound by latency, not by their passes.
+// The joints of kLinkTile rows decouple when the inverse falls faster than 0.914 a row (a
+// Crank-Nicolson matrix with kappa = 50 in a potential near zero: 0.904), those of 1024 rows (from
+// 2^20 rows on) faster than 0.956.
 cn_status plan_link(const cn_layout* L, Plan& P) {
   if (!link_enabled() || L->partition || L->rows_per_thread || L->levels) return CN_OK;
   int red = -1, sub = -1;
@@ -1237,7 +1248,7 @@ cn_status plan_link(const cn_layout* L, Plan& P) {
   if (red < 0 || sub < 0 || P.L[red].cfg != P.L[sub].cfg) return CN_OK;
   const Launch& R = P.L[red];
   const void* const* fn = mrhs ? nsk::tables().mrhs_link[R.cfg] : nsk::tables().link[R.cfg][R.src];
-  if (kCfgs[R.cfg].T() < 1024 || !fn[0]) return CN_OK;
+  if (kCfgs[R.cfg].T() < kLinkTile || !fn[0]) return CN_OK;
   // (several right-hand sides: one workgroup for as many as it has wavefronts)
   const int W = kCfgs[R.cfg].W;
   const int64_t line = mrhs ? 8 + 4 * W : 16;

@@ -15,9 +15,9 @@ void reg_one(Tables& t) {
 }  // namespace
 
 void reg_link(Tables& t) {
+  reg_one<4, 2, nsd::SRC_EXPL>(t);
   reg_one<4, 4, nsd::SRC_EXPL>(t);
-  reg_one<4, 8, nsd::SRC_EXPL>(t);
-  reg_one<8, 4, nsd::SRC_EXPL>(t);
+  reg_one<4, 2, nsd::SRC_EXPL_CT>(t);
   reg_one<4, 4, nsd::SRC_EXPL_CT>(t);
   reg_one<8, 4, nsd::SRC_CN>(t);
   reg_one<8, 4, nsd::SRC_CNW>(t);

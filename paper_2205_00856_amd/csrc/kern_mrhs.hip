@@ -13,6 +13,14 @@ void reg_one(Tables& t) {
   t.mrhs[I][nsd::PH_REDUCE] = (const void*)&nsd::k_tile_mrhs<M, W, nsd::PH_REDUCE>;
   t.mrhs[I][nsd::PH_SUBST] = (const void*)&nsd::k_tile_mrhs<M, W, nsd::PH_SUBST>;
 }
+// the tiles of automatic plans
+template <int M, int W>
+void reg_link_one(Tables& t) {
+  constexpr int I = cfg_index<M, W>();
+  static_assert(I >= 0, "a configuration of the row-tile table");
+  t.mrhs_link[I][0] = (const void*)&nsd::k_mrhs_link<M, W>;
+  t.mrhs_link[I][1] = (const void*)&nsd::k_mrhs_fix<M, W>;
+}
 }  // namespace
 
 void reg_mrhs(Tables& t) {
@@ -24,9 +32,8 @@ void reg_mrhs(Tables& t) {
   reg_one<4, 4>(t);
   reg_one<4, 8>(t);
   reg_one<8, 4>(t);
-  constexpr int I = cfg_index<4, 4>();  // the tile of automatic plans from 2^20 rows on
-  t.mrhs_link[I][0] = (const void*)&nsd::k_mrhs_link<4, 4>;
-  t.mrhs_link[I][1] = (const void*)&nsd::k_mrhs_fix<4, 4>;
+  reg_link_one<4, 2>(t);
+  reg_link_one<4, 4>(t);
 }
 
 }  // namespace nsk

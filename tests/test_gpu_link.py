@@ -217,3 +217,26 @@ def test_several_right_hand_sides(gpu, oracle_mod, kind, n, batch):
     assert torch.equal(bad[:-1], x[:-1])
     assert torch.equal(cn.solve(ta, tb, tc, td, layout=L), x)
     assert cn.get_status() == 0
+
+
+@pytest.mark.parametrize("n,batch", [(1025, 3), (2048, 1), (65_536, 1), (100_003, 2), (9001, 40)])
+@pytest.mark.parametrize("shared", [False, True])
+def test_smaller_solves(gpu, oracle_mod, n, batch, shared):
+    """512-row tiles (from 2^16 rows on) and whole systems of 1025 to 2048 rows, forward and
+    transposed, one matrix each and one for all."""
+    torch, cn = gpu
+    mats = [system(n, "fast", s) for s in range(1 if shared else batch)]
+    d = np.stack([system(n, "fast", 50 + s)[3] for s in range(batch)])
+    a, b, c = (torch.stack(dev(torch, *t)) for t in list(zip(*mats))[:3])
+    (td,) = dev(torch, d)
+    L = cn.Layout.contiguous(n, batch, shared_coefficients=shared)
+    x = cn.solve(a, b, c, td, layout=L)
+    for s in range(batch):
+        m = mats[0 if shared else s]
+        assert rel(x[s].cpu().numpy(), oracle_mod.thomas(*m[:3], d[s])) <= TOL
+    if not shared:
+        lam = cn.solve_adjoint(a, b, c, x, td, need_abc=False, layout=L)[0].cpu().numpy()
+        for s in range(batch):
+            ref = oracle_mod.thomas_adjoint(*mats[s][:3], x[s].cpu().numpy(), d[s])[0]
+            assert rel(lam[s], ref) <= TOL
+    assert cn.get_status() == 0
