@@ -4,13 +4,14 @@
 // access) and a workgroup a tile of T = W M rows of them.  As in k_tile<PH_LINK>, a tile takes psi
 // at its two joint lines from its own slots and its neighbours': the host launches this form only
 // when joints T rows apart are decoupled in every real potential (decoupled(): 2^-66 of the
-// diagonal), so no reduced system is solved at all.  As in k_window, the step is T y = psi,
-// psi' = 2 y - psi on rows scaled by i / kappa, so a tile reads its own rows alone (no edge rows),
-// and may store them in place at any time after its loads.
+// diagonal), so no reduced system is solved at all.  The step is T y = psi, psi' = 2 y - psi on
+// rows scaled by i / kappa, so a tile reads its own rows alone (no edge rows), and may store them
+// in place at any time after its loads.
 //
-// Where psi is needed again, for psi' = 2 y - psi, it is taken as T y from the solution's
-// neighbouring rows in registers, and the pivots are formed a second time on the way back: across
-// the exchange a row keeps D and the diagonal, 6 registers.
+// Where psi is needed again it is T y from the solution's neighbouring rows in registers: psi' =
+// y - i tau H y, whose large part is y itself (the first row of a block has psi at hand and takes
+// 2 y - psi).  The pivots are formed a second time on the way back: across the exchange a row
+// keeps D and the diagonal, 6 registers.
 //
 // The tile's line (DA, DD, UA, UD of 64 systems) is published word by word, all-ones words marking
 // what has not arrived; lines alternate between two buffers, and a pass clears the one of the
@@ -59,7 +60,7 @@ __device__ __forceinline__ void colstep_run(const ColStepArgs& A, ColStepSmem<W>
   const bool live = c0 + lane < A.batch;
   const uint32_t ob16 = (uint32_t)((live ? lane : A.batch - 1 - c0) * 16), ob8 = ob16 / 2;
   const int64_t r0 = tile * (M * W) + (int64_t)wave * M, n = A.n;
-  const double ik = 1.0 / A.kap, ck = -A.tau * ik;
+  const double ik = 1.0 / A.kap;
   const cd zero = czero();
 
   cd D[M];
@@ -78,7 +79,8 @@ __device__ __forceinline__ void colstep_run(const ColStepArgs& A, ColStepSmem<W>
 #pragma unroll
     for (int j = 0; j < M; ++j) {
       D[j] = mk(-ik * D[j].y, ik * D[j].x);
-      va[j] = ck * (A.idx2 + (XG ? fma(xv[XG ? j : 0], A.E, A.vscale * v[j]) : A.vscale * v[j]));
+      va[j] = wdiag(A.tau * (A.idx2 + (XG ? fma(xv[XG ? j : 0], A.E, A.vscale * v[j])
+                                          : A.vscale * v[j])), A.kap, ik);
       if constexpr (!IN) {
         D[j] = csel(r0 + j < n, D[j], zero);
         va[j] = r0 + j < n ? va[j] : 0.0;
@@ -195,8 +197,7 @@ __device__ __forceinline__ void colstep_run(const ColStepArgs& A, ColStepSmem<W>
   bool bad = false;
   bool seen = false;
   if constexpr (FIX) seen = live && A.bad[(int64_t)e * A.batch + c0 + lane];
-  auto put = [&](int i, cd y, cd s) {
-    cd p = mk(fma(-A.kap, s.y, 2.0 * y.x), fma(A.kap, s.x, 2.0 * y.y));
+  auto put = [&](int i, cd p) {
     const double nan = __builtin_nan("");
     if constexpr (FIX) p = csel(seen, mk(nan, nan), p);
     if (live && (IN || r0 + i < n)) {
@@ -221,12 +222,12 @@ __device__ __forceinline__ void colstep_run(const ColStepArgs& A, ColStepSmem<W>
 #pragma unroll
   for (int i = M - 1; i >= 1; --i) {
     const cd lo = i > 1 ? cfms(g[i > 1 ? i - 1 : 1], y, D[i > 1 ? i - 1 : 1]) : pJ;
-    const cd s = cfma(mk(va[i], ik), y, cadd(lo, hi));
-    put(i, y, s);
+    const cd s = mk(fma(va[i], y.x, lo.x + hi.x), fma(va[i], y.y, lo.y + hi.y));
+    put(i, mk(fma(-A.kap, s.y, y.x), fma(A.kap, s.x, y.y)));
     hi = y;
     y = lo;
   }
-  put(0, y, D[0]);
+  put(0, mk(fma(-A.kap, D[0].y, 2.0 * y.x), fma(A.kap, D[0].x, 2.0 * y.y)));
   if (__any(bad)) {
     if (lane == 0) {
       atomicOr(A.status, 1);

@@ -1,8 +1,10 @@
 // A Crank-Nicolson step of a batch of contiguous systems in one pass (gfx950, FP64 complex).
 //
 // A workgroup takes a tile of T = 64 W M rows of one system: a whole system, or one of its tiles.
-// The step is that of k_window (T y = psi on rows scaled by i / kappa, psi' = 2 y - psi), its solve
-// that of one step there: every lane reduces its M rows, lv binary levels join 2^lv lanes, after
+// The step solves T y = psi on rows scaled by i / kappa (those of k_window) and takes psi' =
+// 2 y - T y = y - i tau H y, whose large part is y itself (as 2 y - T y in one product the error
+// after 60 steps, kappa = 0.33, was 7.7e-15 instead of 4.3e-15; exact half-steps and solves leave
+// 3.8e-15).  Its solve is that of k_window: every lane reduces its M rows, lv binary levels join 2^lv lanes, after
 // which the joint lines are decoupled in every real potential (the host takes lv from the bound),
 // and each joint takes its own two slots, those across wavefronts through LDS.  Against k_tile
 // (levels over the whole workgroup, the upper six in one wavefront between two barriers) a tile
@@ -125,7 +127,7 @@ __device__ __forceinline__ void rowstep_run(const RowStepArgs& A, RowStepSmem<M,
   cd* buf = sm.buf[wave];
   double* bufd = reinterpret_cast<double*>(buf);
   RowNode* nodes = reinterpret_cast<RowNode*>(buf);
-  const double ik = 1.0 / A.kap, ck = -A.tau * ik;
+  const double ik = 1.0 / A.kap;
   const cd zero = czero();
   const bool multi = A.ntiles > 1;
 
@@ -170,7 +172,7 @@ __device__ __forceinline__ void rowstep_run(const RowStepArgs& A, RowStepSmem<M,
         const double l = (double)(A.l0 + sys);
         v += l * (l + 1.0) / (2.0 * r * r);
       }
-      bufd[S::addr(1 + 64 * k + lane)] = ck * (A.idx2 + v);
+      bufd[S::addr(1 + 64 * k + lane)] = wdiag(A.tau * (A.idx2 + v), A.kap, ik);
     }
     wave_sync();
 #pragma unroll
@@ -287,7 +289,7 @@ __device__ __forceinline__ void rowstep_run(const RowStepArgs& A, RowStepSmem<M,
   rlevel_down<1>(pJ, pM, nodes, lane);
 
   // ---- the pivots again (the empty asm hides that they are the same), y upwards and
-  // psi' = 2 y - T y (row J's right-hand side is still in D[0])
+  // psi' = 2 y - T y = y - i tau H y; row J's right-hand side is still in D[0]
 #pragma unroll
   for (int j = 1; j < M; ++j) asm volatile("" : "+v"(va[j]));
   {
@@ -301,18 +303,16 @@ __device__ __forceinline__ void rowstep_run(const RowStepArgs& A, RowStepSmem<M,
       beta = cpl(i, cneg(cmul(beta, g[i])));
       D[i] = cfms(beta, pJ, D[i]);
     }
-    auto next = [&](cd y, cd s) {
-      return mk(fma(-A.kap, s.y, 2.0 * y.x), fma(A.kap, s.x, 2.0 * y.y));
-    };
     cd hi = pM, y = cfms(g[M - 1], pM, D[M - 1]);
 #pragma unroll
     for (int i = M - 1; i >= 1; --i) {
       const cd lo = i > 1 ? cfms(g[i > 1 ? i - 1 : 1], y, D[i > 1 ? i - 1 : 1]) : pJ;
-      D[i] = next(y, cfma(mk(va[i], ik), y, cadd(lo, hi)));
+      const cd s = mk(fma(va[i], y.x, lo.x + hi.x), fma(va[i], y.y, lo.y + hi.y));
+      D[i] = mk(fma(-A.kap, s.y, y.x), fma(A.kap, s.x, y.y));
       hi = y;
       y = lo;
     }
-    D[0] = next(y, D[0]);
+    D[0] = mk(fma(-A.kap, D[0].y, 2.0 * y.x), fma(A.kap, D[0].x, 2.0 * y.y));
   }
   if (FIX) bad = A.bad[(int64_t)e * (A.lk_n / A.ntiles) + sys] != 0;
   bool inf = false;

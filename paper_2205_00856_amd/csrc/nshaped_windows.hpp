@@ -89,6 +89,11 @@ template <int NR>
 struct WRhs {
   cd UD[NR], DD[NR];
 };
+// Re(a') = -v / kappa, ik = 1 / kappa, to the last bit: its error is that of every step.
+__device__ __forceinline__ double wdiag(double v, double kap, double ik) {
+  const double q = v * ik;
+  return -fma(fma(-q, kap, v), ik, q);
+}
 // An eliminated joint line: the reciprocal of its pivot, its couplings to the left and right
 // neighbours and the scaled row (B, C) that the way down applies.
 struct WNode {
