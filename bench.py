@@ -298,9 +298,9 @@ def main():
             "peak": HBM_PEAK_GBS,
             "unit": "GB/s",
             "frac": achieved / HBM_PEAK_GBS,
-            "traffic": measured_traffic("adi_4096sq_xsweep_k_tile_cn_single.md"),
-            "kernel": "k_tile<M=8,W=8,SRC_CN,PH_SINGLE>: the x-sweep (fused explicit half-step "
-                      "+ N-shaped solve of 4096 lines of 4096)",
+            "traffic": measured_traffic("adi_4096sq_steps_one_pass.md"),
+            "kernel": "k_rowstep<M=8,W=8>: the x-sweep (N-shaped solve and step of 4096 "
+                      "lines of 4096 in one pass)",
             "algorithmic_bytes_per_launch": algo_bytes,
             "launch_ms": launch_ms,
             "launch_ms_source": launch_src,
