@@ -340,8 +340,14 @@ int multi_cfg(int64_t n, int64_t batch, const Knobs& k, int level, int src) {
   }
   // Crank-Nicolson lines with enough rows for 512 tiles of 2048: 8 rows per lane, whose
   // substitution runs along the RD rows (measured 10% faster per step at 2^20 and 2^24 rows;
-  // with an absorbing potential 20% faster at 2^24 than 1024-row tiles of 4 rows per lane)
-  if (level == 1 && nsd::cn_src(src) && k.rpt == 0 && batch * ((n + 2047) / 2048) >= 512)
+  // with an absorbing potential 20% faster at 2^24 than 1024-row tiles of 4 rows per lane).  With
+  // an absorbing potential also from 128 tiles of long systems on, which step in one pass: per step
+  // 21.1 -> 16.4 us at 2^18 rows, 39 -> 20 at 10^6; where large kappas keep the chain 21.0 -> 19.6
+  // and 39 -> 27.  Shorter sums lose there (2^16 rows 16.2 -> 18.5 us), as do many short systems,
+  // whose last tiles are partly empty (100 of 4100 rows 19.0 -> 24.3).
+  const int64_t tiles8 = batch * ((n + 2047) / 2048);
+  const bool absorb = src == nsd::SRC_CNW && n >= (1 << 15) && tiles8 >= 128;
+  if (level == 1 && nsd::cn_src(src) && k.rpt == 0 && (absorb || tiles8 >= 512))
     return find_cfg(2048, 8);
   // enough tiles to fill the chip (>= 4 workgroups per CU when the system allows it)
   const int64_t target = 1024;

@@ -125,6 +125,30 @@ def test_step(gpu, oracle_mod, kap, absorb):
     assert rel(out.cpu().numpy(), oracle_mod.cn_step(psi, V, dx, dt, W=W)) <= tol
 
 
+@pytest.mark.parametrize("n,batch,linked", [((1 << 18) - 2048, 1, False),
+                                            ((1 << 18) - 2047, 1, True), (1 << 15, 8, True),
+                                            ((1 << 15) - 1, 8, False), (400_003, 1, True)])
+def test_absorbing_sequences(gpu, oracle_mod, n, batch, linked):
+    """Absorbing steps on both sides of the rule that takes them in one pass: chained steps
+    (propagate) and single ones against the oracle, which steps system by system."""
+    torch, cn = gpu
+    dx, dt, steps = 0.1, 0.012, 3
+    g = np.random.default_rng(n)
+    V, W = g.uniform(-1.0, 0.0, n * batch), g.uniform(0.0, 1.0, n * batch)
+    psi = workloads.complex_normal(g, n * batch)
+    L = cn.Layout.contiguous(n, batch)
+    assert ("one pass over the tiles" in cn.describe_plan(L, absorbing=True)) == linked
+    tV, tW, p, q = dev(torch, V, W, psi, psi)
+    cn.propagate(p, tV, dx, dt, steps, W=tW, layout=L)
+    for _ in range(steps):
+        cn.step(q, tV, dx, dt, out=q, W=tW, layout=L)
+    ref = np.concatenate([oracle_mod.cn_propagate(psi[i * n:(i + 1) * n], V[i * n:(i + 1) * n], dx,
+                                                  dt, steps, W=W[i * n:(i + 1) * n])
+                          for i in range(batch)])
+    assert rel(p.cpu().numpy(), ref) <= TOL
+    assert rel(q.cpu().numpy(), ref) <= TOL
+
+
 def test_batches(gpu, oracle_mod):
     """A uniform batch of several tiles each, and an uneven one with a spacing per system (some
     systems coupled, some not)."""
