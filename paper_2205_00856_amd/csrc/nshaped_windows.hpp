@@ -22,6 +22,9 @@
 // of w, the change of the state, and not of the state itself: against T y = psi and
 // psi' = 2 y - psi, which saves 4 of 24 operations per row (200 steps of 65536 rows: 260 us, here
 // 277), the error after 175 steps of 5806 rows at kappa = 0.33 is 4.8e-15 instead of 2.4e-14.
+// With a field a row's diagonal is rounded as a' - (tau / kappa) x E, not as tau (1/dx^2 + V +
+// x E): against the coefficients before their rounding both forms leave the same errors (5.7e-14
+// and 6.0e-14 after 150 steps at kappa = 1.25, nearly all from the rounding of 1/dx^2).
 // Inside the window the solve is the nested partition (Sec. 4): every lane reduces its M rows in
 // the RD form (reduce_block_rd), and LV binary levels join 2^LV lane blocks.  Blocks of M * 2^LV
 // rows couple their two joint lines by less than 2^-66 of the diagonal (the host takes LV from
