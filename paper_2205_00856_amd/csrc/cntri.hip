@@ -257,11 +257,14 @@ struct Plan {
   size_t link_bytes = 0;
   int* link_hint = nullptr;  // host memory: whether the last pass left a tile
   int link_skip = 0;         // calls to take in two passes before one pass is tried again
-  // steps of an interleaved batch in one pass (k_colstep): its device memory (lines, then words,
-  // marks), or null; the shape; and the tile for the last off-diagonal asked for (-1: none)
+  // steps of an interleaved batch in one pass (k_colstep): its device memory, or null, in which
+  // every tile size has lines, words and marks of its own (at col_at), since the two line buffers
+  // and the words that say whose turn it is hold for one number of tiles, and calls with other
+  // time steps take other tiles; the shape; and the tile for the last off-diagonal asked for (-1:
+  // none)
   char* col = nullptr;
-  size_t col_bytes = 0;
-  int64_t col_n = 0, col_batch = 0, col_es = 0, col_tiles = 0;
+  size_t col_bytes = 0, col_at[nsk::kNumColStepCfg] = {};
+  int64_t col_n = 0, col_batch = 0, col_es = 0;
   double col_kap = -1.0;
   int col_cfg = -1;
   // steps of a contiguous batch in one pass (k_rowstep): whether the layout takes them, its
@@ -1296,34 +1299,36 @@ cn_status plan_link(const cn_layout* L, Plan& P) {
   return CN_OK;
 }
 
-// Device memory of the one-pass steps of an automatic plan of column tiles: lines for the most
-// tiles (the shortest ones) of all column groups.
-int64_t col_tile_min() {
-  int64_t t = INT64_MAX;
-  for (const Cfg& c : nsk::kColStepCfgs) t = std::min<int64_t>(t, (int64_t)c.M * c.W);
-  return t;
+// Device memory of the one-pass steps of an automatic plan of column tiles.
+int64_t col_tiles(int64_t n, int64_t batch, int ci) {
+  const int64_t T = (int64_t)nsk::kColStepCfgs[ci].M * nsk::kColStepCfgs[ci].W;
+  return (n + T - 1) / T * ((batch + 63) / 64);
 }
 cn_status plan_colstep(const cn_layout* L, Plan& P) {
   if (!link_enabled() || L->partition || L->rows_per_thread || L->levels || L->offsets ||
       P.L.size() < 2 || P.L[0].level != 1 || P.L[0].cfg >= 0 || P.L[0].src != nsd::SRC_CN ||
       P.L[0].ph != nsd::PH_REDUCE)
     return CN_OK;
-  const int64_t tiles = (L->n + col_tile_min() - 1) / col_tile_min() * ((L->batch + 63) / 64);
-  const size_t lines = (size_t)tiles * 2 * 512 * sizeof(double);
-  const size_t bytes = lines + (4 + (size_t)tiles + 2 * (size_t)L->batch) * sizeof(int);
+  size_t bytes = 0, lines[nsk::kNumColStepCfg];
+  for (int i = 0; i < nsk::kNumColStepCfg; ++i) {
+    const size_t tiles = (size_t)col_tiles(L->n, L->batch, i);
+    P.col_at[i] = bytes;
+    lines[i] = tiles * 2 * 512 * sizeof(double);
+    bytes += lines[i] + (4 + tiles + 2 * (size_t)L->batch) * sizeof(int);
+    bytes = (bytes + 511) & ~size_t(511);
+  }
   if (hipMalloc((void**)&P.col, bytes) != hipSuccess) {
     (void)hipGetLastError();  // two passes then
     P.col = nullptr;
     return CN_OK;
   }
-  if (hipMemset(P.col, 0xFF, lines) != hipSuccess ||
-      hipMemset(P.col + lines, 0, bytes - lines) != hipSuccess)
-    return CN_ERR_HIP;
+  if (hipMemset(P.col, 0, bytes) != hipSuccess) return CN_ERR_HIP;
+  for (int i = 0; i < nsk::kNumColStepCfg; ++i)
+    if (hipMemset(P.col + P.col_at[i], 0xFF, lines[i]) != hipSuccess) return CN_ERR_HIP;
   P.col_bytes = bytes;
   P.col_n = L->n;
   P.col_batch = L->batch;
   P.col_es = L->elem_stride;
-  P.col_tiles = tiles;
   P.desc += "one pass where joints decouple in every potential; ";
   return CN_OK;
 }
@@ -1571,7 +1576,7 @@ int colstep_cfg(Plan* P, double kap) {
 
 cn_status run_colstep(cn_handle_t h, Plan* P, const UserArgs& u, int ci, hipStream_t s) {
   const Cfg c = nsk::kColStepCfgs[ci];
-  const int64_t T = (int64_t)c.M * c.W, ncg = (P->col_batch + 63) / 64;
+  const int64_t T = (int64_t)c.M * c.W;
   nsd::ColStepArgs a{};
   a.in = u.psi;
   a.out = u.x;
@@ -1586,11 +1591,11 @@ cn_status run_colstep(cn_handle_t h, Plan* P, const UserArgs& u, int ci, hipStre
   a.tau = 0.5 * u.dt;
   a.idx2 = 1.0 / (u.dx * u.dx);
   a.kap = (0.5 * u.dt) * 0.5 * a.idx2;
-  a.lk = (double*)P->col;
-  a.lk_n = a.ntiles * ncg;
-  a.st = (int*)(a.lk + P->col_tiles * 2 * 512);
+  a.lk = (double*)(P->col + P->col_at[ci]);
+  a.lk_n = col_tiles(P->col_n, P->col_batch, ci);
+  a.st = (int*)(a.lk + a.lk_n * 2 * 512);
   a.done = a.st + 4;
-  a.bad = a.done + P->col_tiles;
+  a.bad = a.done + a.lk_n;
   a.status = h->status;
   void* params[] = {&a};
   LogLaunch log{h, s, h->profiling && !capturing(s), {}};
