@@ -1013,6 +1013,13 @@ cn_status regrow(cn_handle_t h, void** p, size_t* bytes, size_t need) {
   return CN_OK;
 }
 
+// Device memory set before any stream uses it.  A host wait of its own: HIP does not promise that
+// hipMemset of device memory has finished when it returns, and a non-blocking stream of the caller
+// does not wait for the null stream.
+bool set_memory(void* p, int value, size_t bytes) {
+  return hipMemset(p, value, bytes) == hipSuccess && hipStreamSynchronize(nullptr) == hipSuccess;
+}
+
 cn_status validate(const cn_layout* L, int64_t& rows, int64_t& span) {
   if (!L) return CN_ERR_INVALID_ARG;
   if (L->batch < 1) return CN_ERR_INVALID_ARG;
@@ -1276,8 +1283,7 @@ cn_status plan_link(const cn_layout* L, Plan& P) {
     P.link = nullptr;
     return CN_OK;
   }
-  if (hipMemset(P.link, 0xFF, lines) != hipSuccess ||
-      hipMemset(P.link + lines, 0, bytes - lines) != hipSuccess)
+  if (!set_memory(P.link, 0xFF, lines) || !set_memory(P.link + lines, 0, bytes - lines))
     return CN_ERR_HIP;
   if (hipHostMalloc((void**)&P.link_hint, 64, hipHostMallocMapped) != hipSuccess) {
     (void)hipGetLastError();
@@ -1322,9 +1328,9 @@ cn_status plan_colstep(const cn_layout* L, Plan& P) {
     P.col = nullptr;
     return CN_OK;
   }
-  if (hipMemset(P.col, 0, bytes) != hipSuccess) return CN_ERR_HIP;
+  if (!set_memory(P.col, 0, bytes)) return CN_ERR_HIP;
   for (int i = 0; i < nsk::kNumColStepCfg; ++i)
-    if (hipMemset(P.col + P.col_at[i], 0xFF, lines[i]) != hipSuccess) return CN_ERR_HIP;
+    if (!set_memory(P.col + P.col_at[i], 0xFF, lines[i])) return CN_ERR_HIP;
   P.col_bytes = bytes;
   P.col_n = L->n;
   P.col_batch = L->batch;
@@ -1355,8 +1361,7 @@ cn_status plan_rowstep(const cn_layout* L, int src, Plan& P) {
       P.row_mem = nullptr;
       return CN_OK;
     }
-    if (hipMemset(P.row_mem, 0xFF, lines) != hipSuccess ||
-        hipMemset(P.row_mem + lines, 0, bytes - lines) != hipSuccess)
+    if (!set_memory(P.row_mem, 0xFF, lines) || !set_memory(P.row_mem + lines, 0, bytes - lines))
       return CN_ERR_HIP;
     P.row_bytes = bytes;
     P.row_tiles = tiles;
@@ -2338,7 +2343,7 @@ cn_status cn_create(cn_handle_t* handle, int device) {
     return CN_ERR_NO_MEMORY;
   }
   h->sync = h->status + 64;
-  if (hipMemset(h->status, 0, 128 * sizeof(int)) != hipSuccess ||
+  if (!set_memory(h->status, 0, 128 * sizeof(int)) ||
       scratch_setup(device, &h->scratch) != CN_OK) {
     (void)hipFree(h->status);
     delete h;
@@ -2682,7 +2687,7 @@ cn_status grow_resident(cn_handle_t h, size_t need) {
   if (need <= h->res_size) return CN_OK;
   const cn_status st = regrow(h, &h->res, &h->res_size, need);
   if (st != CN_OK) return st;
-  HIP_TRY(hipMemset(h->res, 0, need));  // the flags start at zero (never inside a capture)
+  if (!set_memory(h->res, 0, need)) return CN_ERR_HIP;  // the flags (never inside a capture)
   return CN_OK;
 }
 
@@ -3357,7 +3362,7 @@ cn_status cn_get_status(cn_handle_t h, cn_stream_t stream) {
   int v = 0;
   HIP_TRY(hipMemcpy(&v, h->status, sizeof(int), hipMemcpyDeviceToHost));
   if (v) {
-    HIP_TRY(hipMemset(h->status, 0, sizeof(int)));
+    if (!set_memory(h->status, 0, sizeof(int))) return CN_ERR_HIP;
     return (v & 4) ? CN_ERR_WAIT_TIMEOUT : CN_NUMERICAL_BREAKDOWN;
   }
   return CN_OK;
