@@ -1247,6 +1247,17 @@ bool link_enabled() {
   return on;
 }
 
+// Polls of a neighbour's line before a one-pass form leaves the tile to the launch after it.
+// (CN_LINK_SPIN sets another bound, 0 leaves every tile: tests of those launches.)
+int link_spin() {
+  const char* e = getenv("CN_LINK_SPIN");
+  if (e && *e) {
+    const long v = strtol(e, nullptr, 10);
+    if (v >= 0 && v <= 65536) return (int)v;
+  }
+  return nsd::kLinkSpin;
+}
+
 // Whether the level-1 tiles of an automatic plan are taken in one pass, and its device memory.
 // The joints of kLinkTile rows decouple when the inverse falls faster than 0.914 a row (a
 // Crank-Nicolson matrix with kappa = 50 in a potential near zero: 0.904), those of 1024 rows (from
@@ -1602,6 +1613,7 @@ cn_status run_colstep(cn_handle_t h, Plan* P, const UserArgs& u, int ci, hipStre
   a.done = a.st + 4;
   a.bad = a.done + a.lk_n;
   a.status = h->status;
+  a.spin = link_spin();
   void* params[] = {&a};
   LogLaunch log{h, s, h->profiling && !capturing(s), {}};
   for (int f = 0; f < 2; ++f) {
@@ -1666,6 +1678,7 @@ cn_status run_rowstep(cn_handle_t h, Plan* P, const UserArgs& u, int ci, int64_t
   a.done = a.st + 4;
   a.bad = a.done + P->row_tiles;
   a.status = h->status;
+  a.spin = a.ntiles > 1 ? link_spin() : 0;
   void* params[] = {&a};
   LogLaunch log{h, s, h->profiling && !capturing(s), {}};
   for (int f = 0; f < (a.ntiles > 1 ? 2 : 1); ++f) {
@@ -1727,6 +1740,7 @@ cn_status run_plan(cn_handle_t h, Plan* P, const UserArgs& u, hipStream_t s,
       a.lk_st = a.lk_done + P->link_n;
       a.lk_n = P->link_n;
       a.lk_hint = P->link_hint;
+      a.lk_spin = link_spin();
       if (i == P->link_red) {
         l.fn = P->link_fn[0];
         if (P->link_rhs) {

@@ -40,6 +40,7 @@ struct ColStepArgs {
   int* done;      // per tile: finished by the pass
   int* bad;       // [2][batch]: systems with a non-finite result
   int* status;
+  int spin;       // polls of a line before its tile is left
 };
 
 template <int W>
@@ -143,8 +144,10 @@ __device__ __forceinline__ void colstep_run(const ColStepArgs& A, ColStepSmem<W>
     const long long* sl = reinterpret_cast<const long long*>(mine - (left ? ncg * 512 : 0));
     const long long* sr = reinterpret_cast<const long long*>(mine + (right ? ncg * 512 : 0)) + 256;
     long long q[8];
+#pragma unroll
+    for (int f = 0; f < 8; ++f) q[f] = (f < 4 ? left : right) ? -1ll : 0ll;
     bool in = false;
-    for (int it = 0; it <= kLinkSpin; ++it) {
+    for (int it = 0; it < (FIX ? 1 : A.spin); ++it) {
 #pragma unroll
       for (int f = 0; f < 4; ++f) {
         q[f] = left ? __hip_atomic_load(sl + 64 * f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;

@@ -106,6 +106,7 @@ struct KArgs {
   int* lk_done;
   int64_t lk_n;  // second passes: nonzero where a joint that decouples is taken as PH_LINK takes it
   int* lk_hint;  // host memory: whether the last pass left a tile
+  int lk_spin;   // polls of a line before its tile is left
   // PH_FUSE of one system: the reduced system of the tile joints is solved by the pass's last
   // workgroup (count of workgroups done, zero between launches), or null (a launch of its own)
   int* inl_sync;
@@ -696,7 +697,7 @@ struct NoMid {
 // passes read the matrix twice), 2^24 rows 446 -> 253 us, an uneven step of 10^4 systems 1.59 ->
 // 1.08 ms.  Larger tiles are slower (2^28: 2048 rows of 4 per lane 4.05 ms, of 8 per lane 3.81).
 constexpr double kLinkEps = 0x1p-66;
-constexpr int kLinkSpin = 256;
+constexpr int kLinkSpin = 256;  // polls of a wait (the host's default for lk_spin)
 
 __device__ __forceinline__ double cmag(cd v) { return fmax(fabs(v.x), fabs(v.y)); }
 
@@ -743,9 +744,9 @@ __device__ __forceinline__ bool link_exchange(const KArgs& A, const Geo& G, SM& 
   const long long* src =
       reinterpret_cast<const long long*>(mine + (act ? (lane < 8 ? -16 : 16) : 0) + (slot ? lane : 0));
   long long v = act ? -1ll : 0ll;
-  for (int it = 0;; ++it) {
+  for (int it = 0; it < A.lk_spin; ++it) {
     if (v == -1ll) v = __hip_atomic_load(src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (__all(v != -1ll) || it >= kLinkSpin) break;
+    if (__all(v != -1ll)) break;
     __builtin_amdgcn_s_sleep(1);
   }
   bool ok = __all(v != -1ll);
@@ -1791,9 +1792,9 @@ __device__ __forceinline__ void mrhs_link_run(const KArgs& A, const Geo& G0, Mrh
     const long long* src =
         reinterpret_cast<const long long*>(mine) + (act ? (lane < 8 ? -kLen : kLen) + word : 0);
     long long q = act ? -1ll : 0ll;
-    for (int it = 0;; ++it) {
+    for (int it = 0; it < A.lk_spin; ++it) {
       if (q == -1ll) q = __hip_atomic_load(src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (__all(q != -1ll) || it >= kLinkSpin) break;
+      if (__all(q != -1ll)) break;
       __builtin_amdgcn_s_sleep(1);
     }
     bool ok = __all(q != -1ll);

@@ -39,6 +39,7 @@ struct RowStepArgs {
   int64_t lk_n;
   int *st, *done, *bad;  // as in k_colstep
   int* status;
+  int spin;  // polls of a line before its tile is left
 };
 
 struct RowNode {
@@ -100,10 +101,10 @@ __device__ __forceinline__ void line_put(double* line, cd a, cd d, int src, int 
 }
 // False when the line did not arrive within the bound of the wait.
 template <bool FIX>
-__device__ __forceinline__ bool line_get(const double* line, cd& a, cd& d, int lane) {
+__device__ __forceinline__ bool line_get(const double* line, cd& a, cd& d, int lane, int spin) {
   const long long* src = reinterpret_cast<const long long*>(line) + (lane & 3);
   long long v = -1ll;
-  for (int it = 0; it <= kLinkSpin; ++it) {
+  for (int it = 0; it < (FIX ? 1 : spin); ++it) {
     v = __hip_atomic_load(src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (FIX || __all(v != -1ll)) break;
     __builtin_amdgcn_s_sleep(1);
@@ -246,14 +247,14 @@ __device__ __forceinline__ void rowstep_run(const RowStepArgs& A, RowStepSmem<M,
     lA = sm.da[wave - 1];
     lD = sm.dd[wave - 1];
   } else if (tile > 0) {
-    have = line_get<FIX>(mine - 8 + 4, lA, lD, lane);
+    have = line_get<FIX>(mine - 8 + 4, lA, lD, lane, A.spin);
   }
   const bool past = wave == W - 1 && tile + 1 >= A.ntiles;  // the system's end
   if (wave + 1 < W) {
     rA = sm.ua[wave + 1];
     rD = sm.ud[wave + 1];
   } else if (!past) {
-    const bool h = line_get<FIX>(mine + 8, rA, rD, lane);
+    const bool h = line_get<FIX>(mine + 8, rA, rD, lane, A.spin);
     have = have && h;
   }
   if (multi && !FIX) {
