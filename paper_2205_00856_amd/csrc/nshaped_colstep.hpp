@@ -16,7 +16,7 @@
 // The tile's line (DA, DD, UA, UD of 64 systems) is published word by word, all-ones words marking
 // what has not arrived; lines alternate between two buffers, and a pass clears the one of the
 // next.  A tile whose wait reaches its bound is left to k_colstep_fix, which runs it from the
-// lines, all there by then, with the same bits.  A system with a non-finite result is marked, and
+// lines, all there by then, with the same bits.  A system with a non-finite row is marked, and
 // k_colstep_fix makes all of it NaN, as exact steps would.
 //
 // Bound by memory: 40 bytes a row and the lines (16 KB written and 4 KB read per tile of 64 rows of
@@ -38,7 +38,7 @@ struct ColStepArgs {
   int64_t lk_n;   // tiles of all column groups
   int* st;        // [buffer of the next pass, of this pass, whether pass of buffer 0, 1 needs a fix]
   int* done;      // per tile: finished by the pass
-  int* bad;       // [2][batch]: systems with a non-finite result
+  int* bad;       // [2][batch]: systems with a non-finite row
   int* status;
   int spin;       // polls of a line before its tile is left
 };
@@ -114,6 +114,13 @@ __device__ __forceinline__ void colstep_run(const ColStepArgs& A, ColStepSmem<W>
   }
   sm.b[wave][lane] = b;
   sm.c[wave][lane] = c;
+  if constexpr (!FIX) {
+    // a non-finite row of the block shows in its U slot; marked before the wait, so whether or not
+    // this pass finishes the tile
+    const bool nf = live && !(cfinite(b.UA) && cfinite(c.UD[0]));
+    if (nf) A.bad[(int64_t)e * A.batch + c0 + lane] = 1;
+    if (__any(nf) && lane == 0) A.st[2 + e] = 1;
+  }
   __syncthreads();
   if (wave == 0) {
 #pragma unroll 1
@@ -231,13 +238,7 @@ __device__ __forceinline__ void colstep_run(const ColStepArgs& A, ColStepSmem<W>
     y = lo;
   }
   put(0, mk(fma(-A.kap, D[0].y, 2.0 * y.x), fma(A.kap, D[0].x, 2.0 * y.y)));
-  if (__any(bad)) {
-    if (lane == 0) {
-      atomicOr(A.status, 1);
-      A.st[2 + e] = 1;
-    }
-    if (!FIX && bad) A.bad[(int64_t)e * A.batch + c0 + lane] = 1;
-  }
+  if (__any(bad) && lane == 0) atomicOr(A.status, 1);
 }
 
 template <int M, int W, bool XG, bool FIX>

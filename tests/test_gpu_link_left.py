@@ -13,8 +13,7 @@ import workloads
 
 pytestmark = pytest.mark.gpu
 OPS = ["solve", "adjoint", "mrhs", "rows", "columns", "columns128"]
-CASES = [c for c in itertools.product(OPS, [0, 1], [False, True], [False, True])
-         if not (c[0].startswith("columns") and c[3])]
+CASES = list(itertools.product(OPS, [0, 1], [False, True], [False, True]))
 
 
 def same(torch, a, b):
