@@ -251,7 +251,8 @@ struct Plan {
   // the tiles, and the device memory of lines, marks and words; -1 / null without
   int link_red = -1, link_sub = -1;
   int64_t link_n = 0, link_words = 0;
-  const void* link_fn[2] = {};
+  // k_tile<PH_LINK>, k_tile_fix, -, the second of two passes (PH_SUBST_LK)
+  const void* link_fn[4] = {};
   int link_rhs = 0;  // several right-hand sides of one matrix: those per workgroup
   char* link = nullptr;
   size_t link_bytes = 0;
@@ -1307,8 +1308,7 @@ cn_status plan_link(const cn_layout* L, Plan& P) {
   P.link_bytes = bytes;
   P.link_n = n;
   P.link_words = 2 * n * line;
-  P.link_fn[0] = fn[0];
-  P.link_fn[1] = fn[1];
+  for (int i = 0; i < 4; ++i) P.link_fn[i] = fn[i];
   P.link_red = red;
   P.link_sub = sub;
   P.link_rhs = mrhs ? W : 0;
@@ -1730,7 +1730,7 @@ cn_status run_plan(cn_handle_t h, Plan* P, const UserArgs& u, hipStream_t s,
     const int i = (int)(&lp - P->L.data());
     if (P->link && i == P->link_sub) {
       const Launch& R = P->L[P->link_red];
-      a.lk_n = P->link_n;
+      l.fn = P->link_fn[3];
       a.oU = (cd*)(ws + R.o_oU);
       a.oD = (cd*)(ws + R.o_oD);
     }

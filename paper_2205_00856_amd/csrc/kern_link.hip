@@ -11,6 +11,7 @@ void reg_one(Tables& t) {
   static_assert(I >= 0, "a configuration of the row-tile table");
   t.link[I][S][0] = (const void*)&nsd::k_tile<M, W, S, nsd::PH_LINK>;
   t.link[I][S][1] = (const void*)&nsd::k_tile_fix<M, W, S>;
+  t.link[I][S][3] = (const void*)&nsd::k_tile<M, W, S, nsd::PH_SUBST_LK>;
 }
 }  // namespace
 

@@ -20,6 +20,7 @@ void reg_link_one(Tables& t) {
   static_assert(I >= 0, "a configuration of the row-tile table");
   t.mrhs_link[I][0] = (const void*)&nsd::k_mrhs_link<M, W>;
   t.mrhs_link[I][1] = (const void*)&nsd::k_mrhs_fix<M, W>;
+  t.mrhs_link[I][3] = (const void*)&nsd::k_tile_mrhs<M, W, nsd::PH_SUBST_LK>;
 }
 }  // namespace
 

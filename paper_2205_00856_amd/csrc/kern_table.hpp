@@ -69,9 +69,10 @@ struct Tables {
   const void* tile[kNumCfg][kNumSrc][kNumPh];
   const void* pers[kNumCfg][kNumSrc];
   // a multi-tile system in one pass, and the launch for the tiles it leaves: [0: k_tile<PH_LINK>,
-  // 1: k_tile_fix]
-  const void* link[kNumCfg][kNumSrc][2];
-  const void* mrhs_link[kNumCfg][2];  // [0: k_mrhs_link, 1: k_mrhs_fix]
+  // 1: k_tile_fix, 3: k_tile<PH_SUBST_LK>]
+  const void* link[kNumCfg][kNumSrc][4];
+  // [0: k_mrhs_link, 1: k_mrhs_fix, 3: k_tile_mrhs<PH_SUBST_LK>]
+  const void* mrhs_link[kNumCfg][4];
   const void* cols[kNumColCfg][kNumSrc][3];
   const void* rowstep[kNumRowStepCfg][2][2];  // [.][with a field][0: k_rowstep, 1: k_rowstep_fix]
   const void* colstep[kNumColStepCfg][2][2];  // [.][with a field][0: k_colstep, 1: k_colstep_fix]

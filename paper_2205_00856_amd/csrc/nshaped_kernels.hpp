@@ -34,9 +34,13 @@ enum Phase : int {
   PH_RES = 4,     // a step of the resident propagation (k_resident): PH_REDUCE's hand-over,
                   // then, once the reduced system is solved in the same launch, PH_SUBST's
                   // substitution (not a phase of the kernel tables)
-  PH_LINK = 5     // a multi-tile system in one pass: PH_REDUCE's hand-over, then the tile's joint
+  PH_LINK = 5,    // a multi-tile system in one pass: PH_REDUCE's hand-over, then the tile's joint
                   // lines from its neighbours' slots where those decouple (link_exchange), then
                   // PH_SUBST's substitution
+  PH_SUBST_LK = 7 // PH_SUBST of plans that take such passes, and of the tiles that one leaves:
+                  // joints that decouple are taken as PH_LINK takes them.  A phase of its own, since the check
+                  // costs other second passes a wavefront per SIMD (8 rows per lane: 128 -> 129
+                  // registers, 2^24 rows 74 -> 85 us)
 };
 
 struct KArgs {
@@ -104,7 +108,7 @@ struct KArgs {
   double* lk;
   int* lk_st;
   int* lk_done;
-  int64_t lk_n;  // second passes: nonzero where a joint that decouples is taken as PH_LINK takes it
+  int64_t lk_n;
   int* lk_hint;  // host memory: whether the last pass left a tile
   int lk_spin;   // polls of a line before its tile is left
   // PH_FUSE of one system: the reduced system of the tile joints is solved by the pass's last
@@ -130,7 +134,7 @@ template <int PH>
 __device__ __forceinline__ Geo geometry(const KArgs& A, unsigned bx, unsigned by) {
   Geo g;
   // second passes only (PH_SUBST, PH_FUSE); the host sets rev for one-dimensional grids
-  if constexpr (PH == PH_SUBST || PH == PH_FUSE) {
+  if constexpr (PH == PH_SUBST || PH == PH_SUBST_LK || PH == PH_FUSE) {
     if (A.rev) bx = rev_linear(bx, gridDim.x);
   }
   if (A.wg_sys) {
@@ -506,8 +510,6 @@ struct TileSmem {
   Node xnode[64];
   double wsum[W];
   cd wedge[W];  // PH_FUSE: last new-state row of every wavefront
-  double lkv[16];  // PH_LINK: the tile's line, then its neighbours' values
-  int lkf;         // PH_LINK: the tile is done in this pass
   __device__ __forceinline__ Blk* part(int w, int k) {
     if constexpr (kInStage)
       return reinterpret_cast<Blk*>(reinterpret_cast<char*>(lds[w]) + kOff) + k;
@@ -631,7 +633,8 @@ __device__ __forceinline__ void tile_run(const KArgs& A, const Geo& G, TileSmem<
 
   cd Ar[M], Br[M], Cr[M], Dr[M], bK, fst, lst;
   // the rows are those of a PH_SUBST pass, or (PH_LINK) of a first pass
-  constexpr int PL = (PH == PH_FUSE) ? PH_SUBST : (PH == PH_LINK) ? PH_REDUCE : PH;
+  constexpr int PL = (PH == PH_FUSE || PH == PH_SUBST_LK) ? PH_SUBST
+                     : (PH == PH_LINK) ? PH_REDUCE : PH;
   // PH_FUSE: diagonal of the next step, from this pass's loads of V and xgrid (imaginary parts)
   double ayn[M];
   double* ayp = (PH == PH_FUSE) ? ayn : nullptr;
@@ -714,28 +717,38 @@ __device__ __forceinline__ bool link_joints(const Blk& b, cd lDA, cd lDD, double
   return ok && cfinite(pJ) && cfinite(pM);
 }
 
+// LDS of a PH_LINK tile beside TileSmem: one variable for all instantiations (the wavefronts of a
+// tile may run different ones).
+struct LinkSmem {
+  double v[16];  // the tile's line, then its neighbours' values
+  int done;      // in this pass
+};
+__device__ __forceinline__ LinkSmem& link_smem() {
+  __shared__ LinkSmem sm;
+  return sm;
+}
+
 // Wavefront 0 of a PH_LINK tile; b, pJ and pM count in lane 0.  Returns whether the tile is done.
-template <typename SM>
-__device__ __forceinline__ bool link_exchange(const KArgs& A, const Geo& G, SM& sm, const Blk& b,
-                                              int lane, cd& pJ, cd& pM) {
+__device__ __forceinline__ bool link_exchange(const KArgs& A, const Geo& G, LinkSmem& sm,
+                                              const Blk& b, int lane, cd& pJ, cd& pM) {
   const int e = A.lk_st[0] & 1;
   double* mine = A.lk + ((int64_t)e * A.lk_n + G.gt) * 16;
   if (lane == 0) {
-    sm.lkv[0] = b.DA.x;
-    sm.lkv[1] = b.DA.y;
-    sm.lkv[2] = b.DD.x;
-    sm.lkv[3] = b.DD.y;
-    sm.lkv[4] = cmag(b.DB);
-    sm.lkv[8] = b.UA.x;
-    sm.lkv[9] = b.UA.y;
-    sm.lkv[10] = b.UD.x;
-    sm.lkv[11] = b.UD.y;
-    sm.lkv[12] = cmag(b.UC);
+    sm.v[0] = b.DA.x;
+    sm.v[1] = b.DA.y;
+    sm.v[2] = b.DD.x;
+    sm.v[3] = b.DD.y;
+    sm.v[4] = cmag(b.DB);
+    sm.v[8] = b.UA.x;
+    sm.v[9] = b.UA.y;
+    sm.v[10] = b.UD.x;
+    sm.v[11] = b.UD.y;
+    sm.v[12] = cmag(b.UC);
   }
   wave_sync();
   const bool slot = lane < 5 || (lane >= 8 && lane < 13);
   if (slot) {
-    __hip_atomic_store(mine + lane, sm.lkv[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(mine + lane, sm.v[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     A.lk[((int64_t)(1 - e) * A.lk_n + G.gt) * 16 + lane] = __longlong_as_double(-1ll);
   }
   wave_sync();
@@ -750,9 +763,9 @@ __device__ __forceinline__ bool link_exchange(const KArgs& A, const Geo& G, SM& 
     __builtin_amdgcn_s_sleep(1);
   }
   bool ok = __all(v != -1ll);
-  if (lane < 16) sm.lkv[lane] = __longlong_as_double(v);
+  if (lane < 16) sm.v[lane] = __longlong_as_double(v);
   wave_sync();
-  const double* q = sm.lkv;
+  const double* q = sm.v;
   const bool dec = link_joints(b, mk(q[0], q[1]), mk(q[2], q[3]), q[4], mk(q[8], q[9]),
                                mk(q[10], q[11]), q[12], right, pJ, pM);
   ok = ok && __builtin_amdgcn_readfirstlane(dec);
@@ -763,7 +776,7 @@ __device__ __forceinline__ bool link_exchange(const KArgs& A, const Geo& G, SM& 
       A.lk_st[1] = e;
       A.lk_st[2 + (1 - e)] = 0;
     }
-    sm.lkf = ok;
+    sm.done = ok;
   }
   return ok;
 }
@@ -866,7 +879,7 @@ __device__ __forceinline__ void tile_core(const KArgs& A, const Geo& G, SM& sm, 
       pJ = A.psi_if[G.gt];
       const cd nxt = A.psi_if[(G.tile + 1 < G.ntile) ? G.gt + 1 : G.gt];
       pM = csel(G.tile + 1 < G.ntile, nxt, czero());
-      if (SRC != SRC_SLOTS && A.lk_n && cfinite(pJ) && cfinite(pM)) {
+      if (PH == PH_SUBST_LK && cfinite(pJ) && cfinite(pM)) {
         // the joints that a PH_LINK pass takes, where they decouple (a joint that is not finite
         // makes the whole system so)
         const bool lf = G.tile > 0, rt = G.tile + 1 < G.ntile;
@@ -1035,12 +1048,13 @@ __device__ __forceinline__ void tile_finish(const KArgs& A, const Geo& G, TileSm
     for (int j = 0; j < M; ++j) arn[j] = Ar[j].x;
   }
   if constexpr (PH == PH_LINK) {
+    LinkSmem& lk = link_smem();
     auto mid = [&](const Blk& b, cd& pj, cd& pm) {
-      if (wave == 0) link_exchange(A, G, sm, b, lane, pj, pm);
+      if (wave == 0) link_exchange(A, G, lk, b, lane, pj, pm);
     };
     tile_core<M, W, SRC, PS, IN>(A, G, sm, wnode, keep, kap, J, lane, wave, Ar, Br, Cr, Dr, bK,
                                  fst, lst, xo, nullptr, mid);
-    if (!sm.lkf) return;  // (the same in every wavefront: written before tile_core's barriers)
+    if (!lk.done) return;  // (the same in every wavefront: written before tile_core's barriers)
   } else {
     tile_core<M, W, SRC, PS, IN>(A, G, sm, wnode, keep, kap, J, lane, wave, Ar, Br, Cr, Dr, bK,
                                  fst, lst, xo, PH == PH_FUSE ? &pM : nullptr);
@@ -1062,9 +1076,11 @@ __device__ __forceinline__ void tile_finish(const KArgs& A, const Geo& G, TileSm
 // Waves per SIMD that the register allocation of a tile kernel must allow: the fused pass of
 // 8 rows per lane carries the next step's diagonal through its first half and sits one
 // register above the budget of 3 wavefronts; the others keep the compiler's choice.
+// PH_LINK and, of real potentials, PH_SUBST_LK sit as close to the budget of 4.
 template <int M, int PH, int SRC = SRC_CN>
 constexpr int tile_min_waves() {
-  return (PH == PH_FUSE && M == 8 && cn_src(SRC)) ? 3 : (PH == PH_LINK && M == 8 && cn_src(SRC)) ? 4 : 1;
+  if (M != 8 || !cn_src(SRC)) return 1;
+  return PH == PH_FUSE ? 3 : PH == PH_LINK || (PH == PH_SUBST_LK && SRC == SRC_CN) ? 4 : 1;
 }
 
 // The reduced system of a PH_FUSE pass over one system, solved in the same launch: every
@@ -1139,7 +1155,7 @@ __global__ __launch_bounds__(64 * W, M == 4 ? 4 : 1) void k_tile_fix(KArgs A) {
                              : geometry<PH_REDUCE>(A, (unsigned)(i % A.ntiles),
                                                    (unsigned)(i / A.ntiles));
       if (!A.lk_done[G.gt]) {
-        tile_run<M, W, SRC, PH_SUBST>(A, G, sm);
+        tile_run<M, W, SRC, PH_SUBST_LK>(A, G, sm);
       } else if (!cfinite(A.psi_if[G.gt]) ||
                  (G.tile + 1 < G.ntile && !cfinite(A.psi_if[G.gt + 1]))) {
         const double nan = __builtin_nan("");
@@ -1500,7 +1516,7 @@ __device__ __forceinline__ bool mrhs_step(const KArgs& A, const Geo& G0, MrhsSme
   // psi at the tile's two joint lines, loaded before this right-hand side's elimination so
   // that the top of the tile does not wait for memory
   cd qJ = zero, qM = zero;
-  if constexpr (PH == PH_SUBST) {
+  if constexpr (PH == PH_SUBST || PH == PH_SUBST_LK) {
     qJ = A.psi_if[G.gt];
     qM = A.psi_if[(G.tile + 1 < G.ntile) ? G.gt + 1 : G.gt];
   }
@@ -1550,7 +1566,7 @@ __device__ __forceinline__ bool mrhs_step(const KArgs& A, const Geo& G0, MrhsSme
     } else {
       pJ = qJ;
       pM = csel(G.tile + 1 < G.ntile, qM, zero);
-      if (A.lk_n && cfinite(pJ) && cfinite(pM)) {
+      if (PH == PH_SUBST_LK && cfinite(pJ) && cfinite(pM)) {
         // the joints that a linked pass takes, where they decouple
         Blk b = top;
         b.UD = UD;
@@ -1899,9 +1915,9 @@ __global__ __launch_bounds__(64 * W) void k_mrhs_fix(KArgs A) {
           B.batch = s0 + r + 1;
           __syncthreads();
           if (w0 >= 1 && G.n >= w0 + 64 * M + 1)
-            tile_run_mrhs<M, W, PH_SUBST, true>(B, G, sm, w0, J, lane, wave, r);
+            tile_run_mrhs<M, W, PH_SUBST_LK, true>(B, G, sm, w0, J, lane, wave, r);
           else
-            tile_run_mrhs<M, W, PH_SUBST, false>(B, G, sm, w0, J, lane, wave, r);
+            tile_run_mrhs<M, W, PH_SUBST_LK, false>(B, G, sm, w0, J, lane, wave, r);
           continue;
         }
         const int64_t gt = (s0 + r) * A.ntiles + G.tile;
