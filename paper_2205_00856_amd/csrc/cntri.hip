@@ -251,7 +251,7 @@ struct Plan {
   // the tiles, and the device memory of lines, marks and words; -1 / null without
   int link_red = -1, link_sub = -1;
   int64_t link_n = 0, link_words = 0;
-  // k_tile<PH_LINK>, k_tile_fix, -, the second of two passes (PH_SUBST_LK)
+  // k_tile<PH_LINK>, k_tile_fix, and the two passes: PH_HAND (null: the plan's own), PH_SUBST_LK
   const void* link_fn[4] = {};
   int link_rhs = 0;  // several right-hand sides of one matrix: those per workgroup
   char* link = nullptr;
@@ -1711,8 +1711,9 @@ cn_status run_plan(cn_handle_t h, Plan* P, const UserArgs& u, hipStream_t s,
   // One pass over the level-1 tiles.  A matrix whose joints couple makes it a first pass with
   // waits (2^24 rows 532 us against 448 in two passes; 253 where they decouple), so a plan whose
   // last pass left a tile takes 63 calls in two passes before it tries again; the results are the
-  // same bits.  (The lines belong to the plan: a run on another workspace may overlap one on
-  // this.)
+  // same bits (a first pass of Crank-Nicolson rows is PH_HAND then: with the slots of PH_REDUCE 43
+  // of 2^18 rows differed in the last bit).  (The lines belong to the plan: a run on another
+  // workspace may overlap one on this.)
   bool link = P->link && !ws_base;
   if (link) {
     if (*(volatile int*)P->link_hint) {
@@ -1728,6 +1729,7 @@ cn_status run_plan(cn_handle_t h, Plan* P, const UserArgs& u, hipStream_t s,
     Launch l = lp;
     KArgs a = plan_args(h, l, u, ws);
     const int i = (int)(&lp - P->L.data());
+    if (P->link && i == P->link_red && P->link_fn[2]) l.fn = P->link_fn[2];
     if (P->link && i == P->link_sub) {
       const Launch& R = P->L[P->link_red];
       l.fn = P->link_fn[3];

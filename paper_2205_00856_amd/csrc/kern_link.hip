@@ -12,6 +12,7 @@ void reg_one(Tables& t) {
   t.link[I][S][0] = (const void*)&nsd::k_tile<M, W, S, nsd::PH_LINK>;
   t.link[I][S][1] = (const void*)&nsd::k_tile_fix<M, W, S>;
   t.link[I][S][3] = (const void*)&nsd::k_tile<M, W, S, nsd::PH_SUBST_LK>;
+  if constexpr (nsd::cn_src(S)) t.link[I][S][2] = (const void*)&nsd::k_tile<M, W, S, nsd::PH_HAND>;
 }
 }  // namespace
 

@@ -43,8 +43,16 @@ __device__ __forceinline__ cd mk(double r, double i) {
   return z;
 }
 __device__ __forceinline__ cd czero() { return mk(0.0, 0.0); }
-__device__ __forceinline__ cd cadd(cd a, cd b) { return mk(a.x + b.x, a.y + b.y); }
-__device__ __forceinline__ cd csub(cd a, cd b) { return mk(a.x - b.x, a.y - b.y); }
+// Sums are never contracted with a product that feeds them (the compiler would do so in one kernel
+// and not in another): the passes of one solve take the same bits from the same rows.
+__device__ __forceinline__ cd cadd(cd a, cd b) {
+#pragma clang fp contract(off)
+  return mk(a.x + b.x, a.y + b.y);
+}
+__device__ __forceinline__ cd csub(cd a, cd b) {
+#pragma clang fp contract(off)
+  return mk(a.x - b.x, a.y - b.y);
+}
 __device__ __forceinline__ cd cneg(cd a) { return mk(-a.x, -a.y); }
 __device__ __forceinline__ cd cconj(cd a) { return mk(a.x, -a.y); }
 __device__ __forceinline__ cd cmul(cd a, cd b) {
@@ -89,6 +97,10 @@ struct Node {
 // ---------------------------------------------------------------- level 1: one lane's block
 // (i b) z for a pure imaginary i b
 __device__ __forceinline__ cd cimul(double b, cd z) { return mk(-b * z.y, b * z.x); }
+// acc - (i b) z
+__device__ __forceinline__ cd cims(double b, cd z, cd acc) {
+  return mk(fma(b, z.y, acc.x), fma(-b, z.x, acc.y));
+}
 
 // Input rows J .. J+M-1 (local 0 .. M-1) as (a, b, c, d) in (A, Bt, Ct, D); bK is the
 // sub-diagonal of the next joint line K = J+M.  On return rows 1..M-1 hold the scaled reduced
@@ -99,6 +111,9 @@ template <int M, bool IMAG = false>
 __device__ __forceinline__ void reduce_block(cd (&A)[M], cd (&Bt)[M], cd (&Ct)[M], cd (&D)[M],
                                              cd bK, Blk& o) {
   auto bmul = [](cd b, cd z) { return IMAG ? cimul(b.y, z) : cmul(b, z); };
+  auto bsub = [](cd acc, cd b, cd z) {
+    return IMAG ? cims(b.y, z, acc) : csub(acc, cmul(b, z));
+  };
   if constexpr (M == 1) {
     // a block without interior rows: its two joint lines are coupled directly
     o.UA = A[0];
@@ -118,8 +133,8 @@ __device__ __forceinline__ void reduce_block(cd (&A)[M], cd (&Bt)[M], cd (&Ct)[M
     // RD: i = J+2 .. K-1 with row i-1 scaled: r = -b_i
 #pragma unroll
     for (int i = 2; i < M; ++i) {
-      cd a = csub(A[i], bmul(Bt[i], Ct[i - 1]));  // a_i - b_i gamma_{i-1}
-      cd d = csub(D[i], bmul(Bt[i], D[i - 1]));   // d_i - b_i delta_{i-1}
+      cd a = bsub(A[i], Bt[i], Ct[i - 1]);  // a_i - b_i gamma_{i-1}
+      cd d = bsub(D[i], Bt[i], D[i - 1]);   // d_i - b_i delta_{i-1}
       cd b = cneg(bmul(Bt[i], Bt[i - 1]));        // -b_i beta_{i-1}
       cd ia = crecip(a);
       Bt[i] = cmul(b, ia);
@@ -139,8 +154,8 @@ __device__ __forceinline__ void reduce_block(cd (&A)[M], cd (&Bt)[M], cd (&Ct)[M
       Ct[i] = cneg(cmul(g, Ct[i + 1]));
     }
     // JU at J: r = -c_J (row J+1 final)
-    o.UA = csub(A[0], bmul(Ct[0], Bt[1]));
-    o.UD = csub(D[0], bmul(Ct[0], D[1]));
+    o.UA = bsub(A[0], Ct[0], Bt[1]);
+    o.UD = bsub(D[0], Ct[0], D[1]);
     o.UC = cneg(bmul(Ct[0], Ct[1]));
   }
 }
@@ -191,8 +206,8 @@ __device__ __forceinline__ void reduce_block_rd_g(const double (&ar)[M], const d
 #pragma unroll
   for (int i = 2; i < M; ++i) {
     const double bi = e.b(i);
-    const cd a = csub(dg(i), cimul(bi, gam));
-    const cd d = csub(D[i], cimul(bi, D[i - 1]));
+    const cd a = cims(bi, gam, dg(i));
+    const cd d = cims(bi, D[i - 1], D[i]);
     const cd b = cneg(cimul(bi, beta));
     const cd ia = crecip(a);
     beta = cmul(b, ia);
@@ -208,8 +223,8 @@ __device__ __forceinline__ void reduce_block_rd_g(const double (&ar)[M], const d
   o.DD = cneg(cimul(bK, D[M - 1]));
   // JU at J with row J+1 final: beta = fb, gamma = -P, delta = fd
   const double c0 = e.c(0);
-  o.UA = csub(dg(0), cimul(c0, fb));
-  o.UD = csub(D[0], cimul(c0, fd));
+  o.UA = cims(c0, fb, dg(0));
+  o.UD = cims(c0, fd, D[0]);
   o.UC = cimul(c0, P);
 }
 template <int M, typename E>
@@ -237,7 +252,7 @@ __device__ __forceinline__ void ss_block_rd_g(const double (&ar)[M], const doubl
 #pragma unroll
   for (int i = 2; i < M; ++i) {
     const double bi = e.b(i);
-    const cd a = csub(dg(i), cimul(bi, gam[i - 1]));
+    const cd a = cims(bi, gam[i - 1], dg(i));
     const cd ia = crecip(a);
     beta = cmul(cneg(cimul(bi, beta)), ia);
     gam[i] = cimul(e.c(i), ia);

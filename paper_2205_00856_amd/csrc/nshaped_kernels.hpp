@@ -37,8 +37,10 @@ enum Phase : int {
   PH_LINK = 5,    // a multi-tile system in one pass: PH_REDUCE's hand-over, then the tile's joint
                   // lines from its neighbours' slots where those decouple (link_exchange), then
                   // PH_SUBST's substitution
-  PH_SUBST_LK = 7 // PH_SUBST of plans that take such passes, and of the tiles that one leaves:
-                  // joints that decouple are taken as PH_LINK takes them.  A phase of its own, since the check
+  PH_HAND = 6,    // PH_REDUCE with the slots of a PH_LINK pass to the last bit: Crank-Nicolson
+                  // blocks reduced in the RD form, for plans that go back to two passes
+  PH_SUBST_LK = 7 // PH_SUBST of such plans and of the tiles that a PH_LINK pass leaves: joints that
+                  // decouple are taken as PH_LINK takes them.  A phase of its own, since the check
                   // costs other second passes a wavefront per SIMD (8 rows per lane: 128 -> 129
                   // registers, 2^24 rows 74 -> 85 us)
 };
@@ -632,9 +634,9 @@ __device__ __forceinline__ void tile_run(const KArgs& A, const Geo& G, TileSmem<
   cd* buf = sm.lds[wave];
 
   cd Ar[M], Br[M], Cr[M], Dr[M], bK, fst, lst;
-  // the rows are those of a PH_SUBST pass, or (PH_LINK) of a first pass
+  // the rows are those of a PH_SUBST pass, or (PH_LINK, PH_HAND) of a first pass
   constexpr int PL = (PH == PH_FUSE || PH == PH_SUBST_LK) ? PH_SUBST
-                     : (PH == PH_LINK) ? PH_REDUCE : PH;
+                     : (PH == PH_LINK || PH == PH_HAND) ? PH_REDUCE : PH;
   // PH_FUSE: diagonal of the next step, from this pass's loads of V and xgrid (imaginary parts)
   double ayn[M];
   double* ayp = (PH == PH_FUSE) ? ayn : nullptr;
@@ -1027,14 +1029,15 @@ __device__ __forceinline__ void tile_finish(const KArgs& A, const Geo& G, TileSm
   // the staging buffer is idle between the loads and the stores: it holds the nodes and, for
   // substitution along the RD rows, the diagonals after them
   // the solve that ends in this pass
-  constexpr int PS = (PH == PH_FUSE) ? PH_SUBST : (PH == PH_LINK) ? PH_RES : PH;
+  constexpr int PS = (PH == PH_FUSE) ? PH_SUBST
+                     : (PH == PH_LINK) ? PH_RES : (PH == PH_HAND) ? PH_REDUCE : PH;
   Node* wnode = reinterpret_cast<Node*>(buf);
   double* keep = reinterpret_cast<double*>(wnode + 64);
   static_assert(!RdSubst<M, W, SRC, PS>::on ||
                     sizeof(Node) * 64 + sizeof(double) * 64 * M <= sizeof(cd) * Stage<M>::QS,
                 "nodes and diagonals fit the stage buffer");
   double kap = 0.0;
-  if constexpr (RdSubst<M, W, SRC, PS>::on) {
+  if constexpr (RdSubst<M, W, SRC, PS>::on || PH == PH_HAND) {
     const double dx = A.dxs ? A.dxs[G.sys] : A.dx;
     kap = cn_kappa(A.dt, dx);
   }
@@ -1056,8 +1059,9 @@ __device__ __forceinline__ void tile_finish(const KArgs& A, const Geo& G, TileSm
                                  fst, lst, xo, nullptr, mid);
     if (!lk.done) return;  // (the same in every wavefront: written before tile_core's barriers)
   } else {
-    tile_core<M, W, SRC, PS, IN>(A, G, sm, wnode, keep, kap, J, lane, wave, Ar, Br, Cr, Dr, bK,
-                                 fst, lst, xo, PH == PH_FUSE ? &pM : nullptr);
+    tile_core<M, W, SRC, PS, IN, PH == PH_HAND>(A, G, sm, wnode, keep, kap, J, lane, wave, Ar, Br,
+                                                Cr, Dr, bK, fst, lst, xo,
+                                                PH == PH_FUSE ? &pM : nullptr);
   }
   if constexpr (PS != PH_REDUCE) {
     check_rows<M, IN>(A, G, J, lane, xo);

@@ -12,7 +12,7 @@ import pytest
 import workloads
 
 pytestmark = pytest.mark.gpu
-OPS = ["solve", "adjoint", "mrhs", "rows", "columns", "columns128"]
+OPS = ["solve", "adjoint", "mrhs", "absorbing", "uneven", "rows", "columns", "columns128"]
 CASES = list(itertools.product(OPS, [0, 1], [False, True], [False, True]))
 
 
@@ -80,3 +80,6 @@ def test_left_tiles(monkeypatch, op, spin, inplace, nan):
     torch.cuda.synchronize()
     assert same(torch, got, want)
     assert cn.get_status() == (1 if nan else 0)
+    monkeypatch.delenv("CN_LINK_SPIN")
+    assert same(torch, call(psi, torch.empty_like(psi)), want)  # the next call
+    cn.get_status()
