@@ -1696,6 +1696,19 @@ cn_status run_rowstep(cn_handle_t h, Plan* P, const UserArgs& u, int ci, int64_t
   return CN_OK;
 }
 
+// Whether the next call on a linked plan takes one pass: not within 63 calls of a pass that left a
+// tile, as far as its report has arrived.
+bool link_turn(Plan* P) {
+  volatile int* hint = (volatile int*)P->link_hint;
+  if (*hint) {
+    *hint = 0;
+    P->link_skip = 63;
+  }
+  if (P->link_skip == 0) return true;
+  --P->link_skip;
+  return false;
+}
+
 cn_status run_plan(cn_handle_t h, Plan* P, const UserArgs& u, hipStream_t s,
                    void* ws_base = nullptr) {
   char* ws = (char*)(ws_base ? ws_base : h->ws);
@@ -1714,17 +1727,7 @@ cn_status run_plan(cn_handle_t h, Plan* P, const UserArgs& u, hipStream_t s,
   // same bits (a first pass of Crank-Nicolson rows is PH_HAND then: with the slots of PH_REDUCE 43
   // of 2^18 rows differed in the last bit).  (The lines belong to the plan: a run on another
   // workspace may overlap one on this.)
-  bool link = P->link && !ws_base;
-  if (link) {
-    if (*(volatile int*)P->link_hint) {
-      *(volatile int*)P->link_hint = 0;
-      P->link_skip = 63;
-    }
-    if (P->link_skip > 0) {
-      --P->link_skip;
-      link = false;
-    }
-  }
+  const bool link = P->link && !ws_base && link_turn(P);
   for (const Launch& lp : P->L) {
     Launch l = lp;
     KArgs a = plan_args(h, l, u, ws);
@@ -2046,11 +2049,15 @@ cn_status cn_plan(cn_handle_t h, const cn_layout* L, const cn_operator* op, hipS
 // fused passes: per step 176 us against 221 at 2^24 rows with an absorbing potential, 49 against
 // 72 at 2^22, 1.08 ms against 1.41 on 10^4 uneven systems.  The joints of 2048-row tiles decouple
 // up to kappa = 1000 in a potential near zero (the inverse falls by exp(-1 / sqrt(2 kappa)) a row);
-// with larger ones the chain is the faster form.
-bool step_by_step(const Plan* P, const cn_operator* op) {
+// with larger ones the chain is the faster form, as it is where a deep potential makes the joints
+// couple (kappa = 250, V = -1 / dx^2: 190 us a step against 234 in two passes): a sequence that
+// follows a pass which left tiles is chained, once in 64 it tries again.
+bool step_by_step(Plan* P, const cn_operator* op) {
   if (!P->link) return false;
-  if (op->dx_per_system) return true;
-  return std::fabs(0.5 * op->dt * 0.5 * (1.0 / (op->dx * op->dx))) <= 500.0;
+  if (!op->dx_per_system &&
+      !(std::fabs(0.5 * op->dt * 0.5 * (1.0 / (op->dx * op->dx))) <= 500.0))
+    return false;
+  return link_turn(P);
 }
 
 // Step arguments of a Crank-Nicolson operator (state in, state out, field E on both sides).
