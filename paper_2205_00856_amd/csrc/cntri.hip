@@ -1329,6 +1329,8 @@ cn_status plan_colstep(const cn_layout* L, Plan& P) {
   size_t bytes = 0, lines[nsk::kNumColStepCfg];
   for (int i = 0; i < nsk::kNumColStepCfg; ++i) {
     const size_t tiles = (size_t)col_tiles(L->n, L->batch, i);
+    // (a launch holds less than 2^32 threads of a dimension)
+    if (tiles * 64 * nsk::kColStepCfgs[i].W > (size_t)UINT32_MAX) return CN_OK;
     P.col_at[i] = bytes;
     lines[i] = tiles * 2 * 512 * sizeof(double);
     bytes += lines[i] + (4 + tiles + 2 * (size_t)L->batch) * sizeof(int);
@@ -1574,7 +1576,7 @@ struct LogLaunch {
 
 // Workgroups of the launch after a one-pass step, which has nothing to do unless a wait reached
 // its bound or a value was not finite (4096 x 4096: 4.9 us with one workgroup per four tiles).
-constexpr int64_t kFixGroups = 64;
+constexpr int64_t kFixGroups = 1024;
 
 // The tile of a one-pass step of column tiles: the shortest whose joints are decoupled for this
 // off-diagonal in every real potential, or -1.

@@ -19,6 +19,11 @@
 // lines, all there by then, with the same bits.  A system with a non-finite row is marked, and
 // k_colstep_fix makes all of it NaN, as exact steps would.
 //
+// Workgroups are numbered in bands of kColBand column groups, tile by tile: a wait is for the
+// workgroup kColBand ids later, which has to be resident beside this one (tiles of 16 rows per lane:
+// 256 at a time), and 4096 neighbouring systems keep the accesses long.  Numbered over all groups
+// of a wider batch the waits ran to their bound and every tile was left.
+//
 // Bound by memory: 40 bytes a row and the lines (16 KB written and 4 KB read per tile of 64 rows of
 // 64 systems, 160 KB of rows).  4096 x 4096 rows: 231 us in two passes (64 bytes a row, the second
 // pass at one wavefront per SIMD) -> 150; 1531 systems of 1000 rows 40.5 -> 20.6 us.
@@ -26,6 +31,8 @@
 #include "nshaped_windows.hpp"
 
 namespace nsd {
+
+constexpr uint32_t kColBand = 64;
 
 struct ColStepArgs {
   const cd* in;
@@ -51,10 +58,10 @@ struct ColStepSmem {
   int ok;
 };
 
-// The tile bid of the launch, whose lines are in buffer e.  FIX: the lines are complete, and the
-// lanes of marked systems store NaN.  Returns false when the tile's neighbours did not publish.
+// Tile gt = tile * (column groups) + group, whose lines are in buffer e.  FIX: the lines are
+// complete, and the lanes of marked systems store NaN.
 template <int M, int W, bool XG, bool FIX, bool IN>
-__device__ __forceinline__ void colstep_run(const ColStepArgs& A, ColStepSmem<W>& sm, int64_t bid,
+__device__ __forceinline__ void colstep_run(const ColStepArgs& A, ColStepSmem<W>& sm, int64_t gt,
                                             int64_t ncg, int64_t tile, int64_t c0, int e) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -136,7 +143,7 @@ __device__ __forceinline__ void colstep_run(const ColStepArgs& A, ColStepSmem<W>
       sm.b[w][lane].DA = dl[0];
     }
     // ---- the joint lines of the tile from its own and its neighbours' slots
-    double* mine = A.lk + ((int64_t)e * A.lk_n + bid) * 512 + lane;
+    double* mine = A.lk + ((int64_t)e * A.lk_n + gt) * 512 + lane;
     const bool left = tile > 0, right = tile + 1 < A.ntiles;
     if constexpr (!FIX) {
       const double v[8] = {b.DA.x, b.DA.y, c.DD[0].x, c.DD[0].y,
@@ -144,7 +151,7 @@ __device__ __forceinline__ void colstep_run(const ColStepArgs& A, ColStepSmem<W>
 #pragma unroll
       for (int f = 0; f < 8; ++f)
         __hip_atomic_store(mine + 64 * f, v[f], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      double* next = A.lk + ((int64_t)(1 - e) * A.lk_n + bid) * 512 + lane;
+      double* next = A.lk + ((int64_t)(1 - e) * A.lk_n + gt) * 512 + lane;
 #pragma unroll
       for (int f = 0; f < 8; ++f) next[64 * f] = __longlong_as_double(-1ll);
     }
@@ -187,9 +194,9 @@ __device__ __forceinline__ void colstep_run(const ColStepArgs& A, ColStepSmem<W>
       const bool ok = __all(in);
       if (lane == 0) {
         sm.ok = ok;
-        A.done[bid] = ok;
+        A.done[gt] = ok;
         if (!ok) A.st[2 + e] = 1;
-        if (bid == 0) {
+        if (gt == 0) {
           A.st[1] = e;
           A.st[2 + (1 - e)] = 0;
         }
@@ -242,22 +249,26 @@ __device__ __forceinline__ void colstep_run(const ColStepArgs& A, ColStepSmem<W>
 }
 
 template <int M, int W, bool XG, bool FIX>
-__device__ __forceinline__ void colstep_tile(const ColStepArgs& A, ColStepSmem<W>& sm, int64_t bid,
-                                             int e) {
-  // consecutive workgroups take neighbouring column groups of the same rows (long contiguous runs)
-  const int64_t ncg = (A.batch + 63) / 64, tile = bid / ncg, c0 = (bid - tile * ncg) * 64;
+__device__ __forceinline__ void colstep_tile(const ColStepArgs& A, ColStepSmem<W>& sm,
+                                             uint32_t tile, uint32_t cg, int e) {
+  const int64_t ncg = (A.batch + 63) / 64, gt = tile * ncg + cg, c0 = (int64_t)cg * 64;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t r0 = tile * (M * W) + (int64_t)wave * M;
+  const int64_t r0 = (int64_t)tile * (M * W) + (int64_t)wave * M;
   if (r0 >= 1 && r0 + M < A.n)
-    colstep_run<M, W, XG, FIX, true>(A, sm, bid, ncg, tile, c0, e);
+    colstep_run<M, W, XG, FIX, true>(A, sm, gt, ncg, tile, c0, e);
   else
-    colstep_run<M, W, XG, FIX, false>(A, sm, bid, ncg, tile, c0, e);
+    colstep_run<M, W, XG, FIX, false>(A, sm, gt, ncg, tile, c0, e);
 }
 
 template <int M, int W, bool XG>
 __global__ __launch_bounds__(64 * W, M == 8 ? 4 : 2) void k_colstep(ColStepArgs A) {
   __shared__ ColStepSmem<W> sm;
-  colstep_tile<M, W, XG, false>(A, sm, blockIdx.x, A.st[0] & 1);
+  // (the host launches fewer than 2^31 workgroups)
+  const uint32_t ncg = (uint32_t)((A.batch + 63) / 64), nt = (uint32_t)A.ntiles;
+  const uint32_t band = blockIdx.x / (kColBand * nt), g0 = band * kColBand;
+  const uint32_t width = ncg - g0 < kColBand ? ncg - g0 : kColBand;
+  const uint32_t rest = blockIdx.x - g0 * nt, tile = rest / width;
+  colstep_tile<M, W, XG, false>(A, sm, tile, g0 + (rest - tile * width), A.st[0] & 1);
 }
 
 // After a pass: the tiles it has left, and NaN for the systems it has marked.  Nothing to do after
@@ -268,11 +279,12 @@ __global__ __launch_bounds__(64 * W) void k_colstep_fix(ColStepArgs A) {
   const int e = A.st[1], ask[2] = {A.st[2], A.st[3]};
   if (ask[e]) {
     const int64_t ncg = (A.batch + 63) / 64;
-    for (int64_t bid = blockIdx.x; bid < A.lk_n; bid += gridDim.x) {
-      if (!A.done[bid]) {
-        colstep_tile<M, W, XG, true>(A, sm, bid, e);
+    for (int64_t gt = blockIdx.x; gt < A.lk_n; gt += gridDim.x) {
+      const int64_t tile = gt / ncg, cg = gt - tile * ncg;
+      if (!A.done[gt]) {
+        colstep_tile<M, W, XG, true>(A, sm, (uint32_t)tile, (uint32_t)cg, e);
       } else {
-        const int64_t tile = bid / ncg, sys = (bid - tile * ncg) * 64 + (threadIdx.x & 63);
+        const int64_t sys = cg * 64 + (threadIdx.x & 63);
         if (sys < A.batch && A.bad[(int64_t)e * A.batch + sys]) {
           const double nan = __builtin_nan("");
           for (int64_t r = tile * M * W + (threadIdx.x >> 6); r < (tile + 1) * M * W && r < A.n;

@@ -1,0 +1,60 @@
+"""Batches so wide that the column groups of one row of tiles outnumber the workgroups that run at
+once: the tiles of a group are started close together, so the waits for a neighbour's line end and
+the launch for left tiles finds nothing to do (else it repeats the whole step).  Rows against the CPU oracle on a sample of systems, relative L2 <= 1e-11,
+and against the contiguous form of the same step on all of them.
+"""
+import numpy as np
+import pytest
+
+import workloads
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-11
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2205_00856_amd as cn
+
+    cn.handle(0)
+    return torch, cn
+
+
+def times(cn, call):
+    """Milliseconds of the labelled launches of one call, after two others."""
+    import torch
+
+    call()
+    call()
+    torch.cuda.synchronize()
+    cn.profile(True)
+    try:
+        call()
+        torch.cuda.synchronize()
+        return {label.split()[1]: ms for label, ms in cn.profile_report()}
+    finally:
+        cn.profile(False)
+
+
+@pytest.mark.parametrize("batch", [4097, 33025])  # 65 and 517 column groups
+@pytest.mark.parametrize("dx", [0.1, 0.05])  # kappa 0.25 and 1.0: tiles of 64 and 128 rows
+def test_interleaved(gpu, oracle_mod, dx, batch):
+    torch, cn = gpu
+    n, dt = 300, 0.01
+    g = torch.Generator(device="cuda").manual_seed(batch)
+    V = -torch.rand(n, batch, dtype=torch.float64, device="cuda", generator=g)
+    psi = torch.randn(n, batch, dtype=torch.complex128, device="cuda", generator=g)
+    L = cn.Layout.interleaved(n, batch)
+    out = cn.step(psi, V, dx, dt, layout=L)
+    rows = cn.step(psi.t().contiguous(), V.t().contiguous(), dx, dt)
+    err = (out.t() - rows).norm(dim=1) / rows.norm(dim=1)
+    assert err.max().item() <= TOL
+    for s in (0, 63, 64, 4095, 4096, batch - 1, *range(100, batch, 1501)):
+        ref = oracle_mod.cn_step(psi[:, s].cpu().numpy(), V[:, s].cpu().numpy(), dx, dt)
+        assert np.linalg.norm(out[:, s].cpu().numpy() - ref) <= TOL * np.linalg.norm(ref), s
+    if batch > 32768:
+        t = times(cn, lambda: cn.step(psi, V, dx, dt, out=out, layout=L))
+        assert t["column-fix"] < 0.5 * t["column-step"], t
