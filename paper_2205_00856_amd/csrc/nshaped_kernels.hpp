@@ -1863,9 +1863,15 @@ __device__ __forceinline__ void mrhs_link_run(const KArgs& A, const Geo& G0, Mrh
 }
 
 // Workgroup id of a grid of ntiles * groups: groups of a tile, and neighbouring tiles, in rounds of
-// 8 tiles, so that the groups of a tile have ids equal mod 8 (one XCD).
-__device__ __forceinline__ void mrhs_link_item(int64_t id, int64_t ntiles, int64_t groups,
+// 8 tiles, so that the groups of a tile have ids equal mod 8 (one XCD).  More than kMrhsBand groups
+// run band after band: a tile waits for one at most 8 kMrhsBand ids later, which has to be resident
+// beside it (512 workgroups at a time).
+constexpr int64_t kMrhsBand = 16;
+__device__ __forceinline__ void mrhs_link_item(int64_t id, int64_t ntiles, int64_t all,
                                                int64_t& tile, int64_t& group) {
+  const int64_t band = id / (kMrhsBand * ntiles), g0 = band * kMrhsBand;
+  const int64_t groups = all - g0 < kMrhsBand ? all - g0 : kMrhsBand;
+  id -= g0 * ntiles;
   const int64_t full = ntiles / 8 * 8;
   if (id < full * groups) {
     const int64_t q = id / (8 * groups), m = id - q * 8 * groups;
@@ -1876,6 +1882,7 @@ __device__ __forceinline__ void mrhs_link_item(int64_t id, int64_t ntiles, int64
     tile = full + m % rest;
     group = m / rest;
   }
+  group += g0;
 }
 
 template <int M, int W>

@@ -1,7 +1,8 @@
-"""Batches so wide that the column groups of one row of tiles outnumber the workgroups that run at
-once: the tiles of a group are started close together, so the waits for a neighbour's line end and
-the launch for left tiles finds nothing to do (else it repeats the whole step).  Rows against the CPU oracle on a sample of systems, relative L2 <= 1e-11,
-and against the contiguous form of the same step on all of them.
+"""Batches so wide that the column groups of one row of tiles, or the groups of right-hand sides of
+a round of tiles, outnumber the workgroups that run at once: the tiles of a group are started close
+together, so the waits for a neighbour's line end and the launch for left tiles finds nothing to do
+(else it repeats the whole call).  Against the CPU oracle on a sample of systems, relative
+L2 <= 1e-11; interleaved steps also against the contiguous form on all of them.
 """
 import numpy as np
 import pytest
@@ -58,3 +59,21 @@ def test_interleaved(gpu, oracle_mod, dx, batch):
     if batch > 32768:
         t = times(cn, lambda: cn.step(psi, V, dx, dt, out=out, layout=L))
         assert t["column-fix"] < 0.5 * t["column-step"], t
+
+
+@pytest.mark.parametrize("k", [33, 1203])
+def test_right_hand_sides(gpu, oracle_mod, k):
+    torch, cn = gpu
+    n = 20_011  # 40 tiles of 512 rows
+    g = np.random.default_rng(k)
+    abc = 2.0 + 0.1j * g.standard_normal(n), np.full(n, -0.3 + 0.1j), np.full(n, -0.2 - 0.1j)
+    ta, tb, tc = (torch.from_numpy(t).cuda() for t in abc)
+    d = torch.randn(k, n, dtype=torch.complex128, device="cuda")
+    L = cn.Layout.contiguous(n, k, shared_coefficients=True)
+    x = cn.solve(ta, tb, tc, d, layout=L)
+    for s in (0, 1, 31, 32, k - 1, *range(3, k, 101)):
+        ref = oracle_mod.thomas(*abc, d[s].cpu().numpy())
+        assert np.linalg.norm(x[s].cpu().numpy() - ref) <= TOL * np.linalg.norm(ref), s
+    if k > 1024:
+        t = times(cn, lambda: cn.solve(ta, tb, tc, d, out=x, layout=L))
+        assert "link" in t and t["subst"] < 0.5 * t["link"], t
