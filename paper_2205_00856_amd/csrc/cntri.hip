@@ -1333,7 +1333,7 @@ cn_status plan_colstep(const cn_layout* L, Plan& P) {
     if (tiles * 64 * nsk::kColStepCfgs[i].W > (size_t)UINT32_MAX) return CN_OK;
     P.col_at[i] = bytes;
     lines[i] = tiles * 2 * 512 * sizeof(double);
-    bytes += lines[i] + (4 + tiles + 2 * (size_t)L->batch) * sizeof(int);
+    bytes += lines[i] + tiles * 64 * sizeof(cd) + (4 + tiles + 2 * (size_t)L->batch) * sizeof(int);
     bytes = (bytes + 511) & ~size_t(511);
   }
   if (hipMalloc((void**)&P.col, bytes) != hipSuccess) {
@@ -1368,7 +1368,8 @@ cn_status plan_rowstep(const cn_layout* L, int src, Plan& P) {
   P.row_shared = L->shared_coefficients != 0;
   if (L->n > longest) {
     const size_t lines = (size_t)tiles * 2 * 8 * sizeof(double);
-    const size_t bytes = lines + (4 + (size_t)tiles + 2 * (size_t)L->batch) * sizeof(int);
+    const size_t bytes = lines + (size_t)tiles * sizeof(cd) +
+                         (4 + (size_t)tiles + 2 * (size_t)L->batch) * sizeof(int);
     if (hipMalloc((void**)&P.row_mem, bytes) != hipSuccess) {
       (void)hipGetLastError();  // the other forms then
       P.row_mem = nullptr;
@@ -1611,7 +1612,8 @@ cn_status run_colstep(cn_handle_t h, Plan* P, const UserArgs& u, int ci, hipStre
   a.kap = (0.5 * u.dt) * 0.5 * a.idx2;
   a.lk = (double*)(P->col + P->col_at[ci]);
   a.lk_n = col_tiles(P->col_n, P->col_batch, ci);
-  a.st = (int*)(a.lk + a.lk_n * 2 * 512);
+  a.edge = (cd*)(a.lk + a.lk_n * 2 * 512);
+  a.st = (int*)(a.edge + a.lk_n * 64);
   a.done = a.st + 4;
   a.bad = a.done + a.lk_n;
   a.status = h->status;
@@ -1676,7 +1678,8 @@ cn_status run_rowstep(cn_handle_t h, Plan* P, const UserArgs& u, int ci, int64_t
   a.dr = dr;
   a.lk_n = a.ntiles * P->row_batch;
   a.lk = (double*)P->row_mem;
-  a.st = (int*)(a.lk + P->row_tiles * 2 * 8);
+  a.edge = (cd*)(a.lk + P->row_tiles * 2 * 8);
+  a.st = (int*)(a.edge + P->row_tiles);
   a.done = a.st + 4;
   a.bad = a.done + P->row_tiles;
   a.status = h->status;
@@ -2283,9 +2286,9 @@ cn_status run_windows_adjoint(cn_handle_t h, const Plan* P, const cn_layout* L,
     a.later = 1;
   }
   a.dV = dV;
-  a.acc_dV = op->v_scale * op->dt;
-  // the kernel's terms carry -(tau / kappa) x = -2 dx^2 x
-  a.acc_dE = -0.5 * op->dt * a.idx2;
+  // the kernel's terms are products of two sums, each twice the mean it stands for
+  a.acc_dV = 0.25 * op->v_scale * op->dt;
+  a.acc_dE = 0.25 * op->dt;
   a.nparts = -nparts;  // steps go backwards through a segment's rows
   const bool xg = E || dE;
   auto launches = [&](int64_t sg) {

@@ -4,14 +4,11 @@
 // access) and a workgroup a tile of T = W M rows of them.  As in k_tile<PH_LINK>, a tile takes psi
 // at its two joint lines from its own slots and its neighbours': the host launches this form only
 // when joints T rows apart are decoupled in every real potential (decoupled(): 2^-66 of the
-// diagonal), so no reduced system is solved at all.  The step is T y = psi, psi' = 2 y - psi on
-// rows scaled by i / kappa, so a tile reads its own rows alone (no edge rows), and may store them
-// in place at any time after its loads.
-//
-// Where psi is needed again it is T y from the solution's neighbouring rows in registers: psi' =
-// y - i tau H y, whose large part is y itself (the first row of a block has psi at hand and takes
-// 2 y - psi).  The pivots are formed a second time on the way back: across the exchange a row
-// keeps D and the diagonal, 6 registers.
+// diagonal), so no reduced system is solved at all.  The rows are those of k_window; a wavefront
+// loads the row after its block as well, mostly from the L2 that its neighbour fills.  In place: as
+// in k_rowstep a tile stores once both neighbours have published, and a tile that is left keeps the
+// edge row that it has loaded.  The pivots are formed a second time on the way back: across the
+// exchange a row keeps D and the diagonal, 6 registers.
 //
 // The tile's line (DA, DD, UA, UD of 64 systems) is published word by word, all-ones words marking
 // what has not arrived; lines alternate between two buffers, and a pass clears the one of the
@@ -24,9 +21,9 @@
 // 256 at a time), and 4096 neighbouring systems keep the accesses long.  Numbered over all groups
 // of a wider batch the waits ran to their bound and every tile was left.
 //
-// Bound by memory: 40 bytes a row and the lines (16 KB written and 4 KB read per tile of 64 rows of
+// Bound by memory: 40 bytes a row and the lines (8 KB written and 4 KB read per tile of 64 rows of
 // 64 systems, 160 KB of rows).  4096 x 4096 rows: 231 us in two passes (64 bytes a row, the second
-// pass at one wavefront per SIMD) -> 150; 1531 systems of 1000 rows 40.5 -> 20.6 us.
+// pass at one wavefront per SIMD) -> 148; 1531 systems of 1000 rows 40.5 -> 17.7 us.
 #pragma once
 #include "nshaped_windows.hpp"
 
@@ -46,6 +43,7 @@ struct ColStepArgs {
   int* st;        // [buffer of the next pass, of this pass, whether pass of buffer 0, 1 needs a fix]
   int* done;      // per tile: finished by the pass
   int* bad;       // [2][batch]: systems with a non-finite row
+  cd* edge;       // [lk_n][64]: of a tile left to the fix, psi of the row after its last one
   int* status;
   int spin;       // polls of a line before its tile is left
 };
@@ -54,7 +52,8 @@ template <int W>
 struct ColStepSmem {
   WBlk b[W][64];      // the blocks' matrix slots; after the elimination (B, C, dl) of joint w
   WRhs<1> c[W][64];
-  cd jpsi[W + 1][64];  // psi (y) at the tile's joint lines
+  cd jpsi[W + 1][64];  // the solution at the tile's joint lines
+  cd edge[64];         // psi of the row after the tile
   int ok;
 };
 
@@ -68,27 +67,33 @@ __device__ __forceinline__ void colstep_run(const ColStepArgs& A, ColStepSmem<W>
   const bool live = c0 + lane < A.batch;
   const uint32_t ob16 = (uint32_t)((live ? lane : A.batch - 1 - c0) * 16), ob8 = ob16 / 2;
   const int64_t r0 = tile * (M * W) + (int64_t)wave * M, n = A.n;
-  const double ik = 1.0 / A.kap;
+  const double kap = A.kap;
   const cd zero = czero();
 
-  cd D[M];
+  cd D[M], zM;  // psi; its row r0 + M
   double va[M];
   {
     double v[M], xv[XG ? M : 1];
     auto row = [&](int j) { return IN ? r0 + j : (r0 + j < n ? r0 + j : n - 1); };
 #pragma unroll
     for (int j = 0; j < M; ++j) D[j] = col_at(A.in + c0, ob16, row(j), A.es);
+    zM = col_at(A.in + c0, ob16, row(M), A.es);
 #pragma unroll
     for (int j = 0; j < M; ++j) v[j] = col_at(A.V + c0, ob8, row(j), A.es);
     if constexpr (XG) {
 #pragma unroll
       for (int j = 0; j < M; ++j) xv[j] = col_at(A.xg + c0, ob8, row(j), A.es);
     }
+    if (wave == W - 1 && tile + 1 < A.ntiles) {
+      // (in place, the next tile may have stored by the time of the fix)
+      if constexpr (FIX) zM = A.edge[gt * 64 + lane];
+      else sm.edge[lane] = zM;
+    }
+    if constexpr (!IN) zM = csel(r0 + M < n, zM, zero);
 #pragma unroll
     for (int j = 0; j < M; ++j) {
-      D[j] = mk(-ik * D[j].y, ik * D[j].x);
-      va[j] = wdiag(A.tau * (A.idx2 + (XG ? fma(xv[XG ? j : 0], A.E, A.vscale * v[j])
-                                          : A.vscale * v[j])), A.kap, ik);
+      va[j] = wdiag(A.tau, A.idx2, XG ? fma(xv[XG ? j : 0], A.E, A.vscale * v[j])
+                                      : A.vscale * v[j]);
       if constexpr (!IN) {
         D[j] = csel(r0 + j < n, D[j], zero);
         va[j] = r0 + j < n ? va[j] : 0.0;
@@ -100,24 +105,36 @@ __device__ __forceinline__ void colstep_run(const ColStepArgs& A, ColStepSmem<W>
   WBlk b;
   WRhs<1> c;
   {
-    cd g = crecip(mk(va[1], ik));
-    cd beta = cpl(1, g);
-    D[1] = cmul(D[1], g);
-    cd fb = beta, fd = D[1];
+    cd p = D[0];  // psi of the row before (rows past the end hold zero and have no right-hand side)
+    D[0] = wrhs(va[0], kap, p, D[1]);
+    if constexpr (!IN) D[0] = csel(r0 < n, D[0], zero);
+    cd h = zero, beta = zero, fb = zero, fd = zero;
 #pragma unroll
-    for (int i = 2; i < M; ++i) {
-      g = crecip(csub(mk(va[i], ik), cpl(i, g)));
-      D[i] = cmul(csub(D[i], cpl(i, D[i - 1])), g);
-      fd = cfms(beta, D[i], fd);
-      const cd bi = cpl(i, cneg(cmul(beta, g)));
-      fb = cfms(beta, bi, fb);
-      beta = bi;
+    for (int i = 1; i < M; ++i) {
+      cd d = wrhs(va[i], kap, D[i], cadd(p, i + 1 < M ? D[i + 1 < M ? i + 1 : i] : zM));
+      if constexpr (!IN) d = csel(r0 + i < n, d, zero);
+      p = D[i];
+      if (i == 1) {
+        const cd g = crecip(mk(-va[1], 1.0));
+        h = rmul(kap, g);
+        D[1] = cmul(d, g);
+        fb = beta = cpl(1, h);
+        fd = D[1];
+      } else {
+        const cd g = crecip(rfms(kap, cpl(i, h), mk(-va[i], 1.0)));
+        h = rmul(kap, g);
+        D[i] = cmul(rfms(kap, cpl(i, D[i - 1]), d), g);
+        fd = cfms(beta, D[i], fd);
+        const cd bi = cpl(i, cneg(cmul(beta, h)));
+        fb = cfms(beta, bi, fb);
+        beta = bi;
+      }
     }
-    b.UA = csub(mk(va[0], ik), fb);
-    b.C = cpl(M, cneg(beta));
-    b.DA = cpl(M, cneg(g));
-    c.UD[0] = csub(D[0], fd);
-    c.DD[0] = cpl(M, cneg(D[M - 1]));
+    b.UA = rfms(kap, fb, mk(-va[0], 1.0));
+    b.C = cpl(M, rmul(-kap, beta));
+    b.DA = cpl(M, rmul(-kap, h));
+    c.UD[0] = rfms(kap, fd, D[0]);
+    c.DD[0] = cpl(M, rmul(-kap, cadd(p, D[M - 1])));
   }
   sm.b[wave][lane] = b;
   sm.c[wave][lane] = c;
@@ -206,11 +223,14 @@ __device__ __forceinline__ void colstep_run(const ColStepArgs& A, ColStepSmem<W>
   }
   __syncthreads();
   if constexpr (!FIX) {
-    if (!sm.ok) return;
+    if (!sm.ok) {
+      if (wave == W - 1) A.edge[gt * 64 + lane] = sm.edge[lane];
+      return;
+    }
   }
-  // ---- y upwards, psi' = 2 y - T y (row r0's right-hand side is still in D[0])
+  // ---- psi' upwards
   const cd pJ = sm.jpsi[wave][lane];
-  cd hi = sm.jpsi[wave + 1][lane];
+  const cd pM = sm.jpsi[wave + 1][lane];
   bool bad = false;
   bool seen = false;
   if constexpr (FIX) seen = live && A.bad[(int64_t)e * A.batch + c0 + lane];
@@ -225,26 +245,23 @@ __device__ __forceinline__ void colstep_run(const ColStepArgs& A, ColStepSmem<W>
   // the pivots again (the empty asm hides that they are the same), dp_i = D_i - beta_i pJ
 #pragma unroll
   for (int j = 1; j < M; ++j) asm volatile("" : "+v"(va[j]));
-  cd g[M];
-  g[1] = crecip(mk(va[1], ik));
-  cd beta = cpl(1, g[1]);
+  cd h[M];
+  h[1] = rmul(kap, crecip(mk(-va[1], 1.0)));
+  cd beta = cpl(1, h[1]);
   D[1] = cfms(beta, pJ, D[1]);
 #pragma unroll
   for (int i = 2; i < M; ++i) {
-    g[i] = crecip(csub(mk(va[i], ik), cpl(i, g[i - 1])));
-    beta = cpl(i, cneg(cmul(beta, g[i])));
+    h[i] = rmul(kap, crecip(rfms(kap, cpl(i, h[i - 1]), mk(-va[i], 1.0))));
+    beta = cpl(i, cneg(cmul(beta, h[i])));
     D[i] = cfms(beta, pJ, D[i]);
   }
-  cd y = M > 1 ? cfms(g[M - 1], hi, D[M - 1]) : pJ;
+  cd y = pM;
 #pragma unroll
   for (int i = M - 1; i >= 1; --i) {
-    const cd lo = i > 1 ? cfms(g[i > 1 ? i - 1 : 1], y, D[i > 1 ? i - 1 : 1]) : pJ;
-    const cd s = mk(fma(va[i], y.x, lo.x + hi.x), fma(va[i], y.y, lo.y + hi.y));
-    put(i, mk(fma(-A.kap, s.y, y.x), fma(A.kap, s.x, y.y)));
-    hi = y;
-    y = lo;
+    y = cfms(h[i], y, D[i]);
+    put(i, y);
   }
-  put(0, mk(fma(-A.kap, D[0].y, 2.0 * y.x), fma(A.kap, D[0].x, 2.0 * y.y)));
+  put(0, pJ);
   if (__any(bad) && lane == 0) atomicOr(A.status, 1);
 }
 

@@ -66,6 +66,14 @@ __device__ __forceinline__ cd cfma(cd a, cd b, cd acc) {
 __device__ __forceinline__ cd cfms(cd a, cd b, cd acc) {
   return mk(fma(-a.x, b.x, fma(a.y, b.y, acc.x)), fma(-a.x, b.y, fma(-a.y, b.x, acc.y)));
 }
+// r z, acc + r z, acc - r z
+__device__ __forceinline__ cd rmul(double r, cd z) { return mk(r * z.x, r * z.y); }
+__device__ __forceinline__ cd rfma(double r, cd z, cd acc) {
+  return mk(fma(r, z.x, acc.x), fma(r, z.y, acc.y));
+}
+__device__ __forceinline__ cd rfms(double r, cd z, cd acc) {
+  return mk(fma(-r, z.x, acc.x), fma(-r, z.y, acc.y));
+}
 __device__ __forceinline__ cd csel(bool p, cd a, cd b) { return mk(p ? a.x : b.x, p ? a.y : b.y); }
 
 // 1/v from the hardware estimate refined by two Newton-Raphson steps

@@ -3,17 +3,19 @@
 //
 // T = 1 + i sigma C (sigma = tau E r) has a real off-diagonal times i and no other diagonal, so with
 // y_l = (-i)^l u_l and psi_l = (-i)^l f_l the system is real,
-//     u_l - sigma C_{l-1,l} u_{l-1} + sigma C_{l,l+1} u_{l+1} = f_l,
+//     u_l - sigma C_{l-1,l} u_{l-1} + sigma C_{l,l+1} u_{l+1}
+//         = f_l + sigma C_{l-1,l} f_{l-1} - sigma C_{l,l+1} f_{l+1},
 // with a complex right-hand side: the pivots 1 + sigma^2 C^2 / pivot and all multipliers are real
 // numbers, and a row keeps 6 registers (D and its reciprocal pivot) instead of the 12 of complex
-// reduced rows.  The step is f' = 2 u - f, f taken as the left side above from the solution.
+// reduced rows.  The first row of a block has its right-hand side split like its diagonal: the term
+// of f_{l-1} is in the D slot of the block before.
 //
 // As in k_cols, a wavefront's lanes take 64 neighbouring systems (radial points), wavefront w the
 // rows w M .. of each, and the joint lines of a system are eliminated in its lane by wavefront 0.
 // The couplings C of the rows are computed once per workgroup, a row per thread.
 //
 // Bound by memory: 64 waves of 65536 points (134 MB a step) 49.8 us with the complex column kernel
-// -> 23.5 us.  16 rows per lane need more than 128 registers.
+// -> 24.6 us.  16 rows per lane need more than 128 registers.
 #pragma once
 #include "nshaped_kernels.hpp"
 
@@ -36,10 +38,6 @@ struct LBlk {
   cd UD, DD;
 };
 
-__device__ __forceinline__ cd rmul(double a, cd z) { return mk(a * z.x, a * z.y); }
-__device__ __forceinline__ cd rfma(double a, cd z, cd w) {  // w + a z
-  return mk(fma(a, z.x, w.x), fma(a, z.y, w.y));
-}
 // i^q z
 __device__ __forceinline__ cd irot(int q, cd z) {
   switch (q & 3) {
@@ -64,10 +62,11 @@ __global__ __launch_bounds__(64 * kLWaves, 4) void k_lstep(LStepArgs A) {
   const uint32_t ob16 = (uint32_t)off * 16;
   const int r0 = wave * M, n = (int)A.n;
   // the rows' powers of -i count from this block's first row (M is a multiple of 4)
-  cd D[M];
+  cd D[M], fM;  // f; that of the row after the block
 #pragma unroll
   for (int j = 0; j < M; ++j)
     D[j] = col_at(A.in + c0, ob16, r0 + j < n ? r0 + j : n - 1, A.batch);
+  fM = col_at(A.in + c0, ob16, r0 + M < n ? r0 + M : n - 1, A.batch);
   for (int q = threadIdx.x; q <= W * M; q += blockDim.x) {
     const double l = (double)(A.l0 + q - 1);
     cl[q] = q > 0 && q < n ? (l + 1.0) / sqrt((2.0 * l + 1.0) * (2.0 * l + 3.0)) : 0.0;
@@ -75,11 +74,21 @@ __global__ __launch_bounds__(64 * kLWaves, 4) void k_lstep(LStepArgs A) {
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < M; ++j) D[j] = csel(r0 + j < n, irot(j, D[j]), czero());
+  fM = csel(r0 + M < n, irot(M, fM), czero());
   const double sg = A.s0 * (double)(c0 + off + 1);
   auto e = [&](int j) { return sg * cl[r0 + j]; };
   double g[M];
   LBlk b;
   {
+    // the right-hand sides (couplings past the system's ends are zero)
+    cd p = D[0];
+    D[0] = rfma(-e(1), D[1], p);
+#pragma unroll
+    for (int i = 1; i < M; ++i) {
+      const cd f = D[i];
+      D[i] = rfma(e(i), p, rfma(-e(i + 1), i + 1 < M ? D[i + 1 < M ? i + 1 : i] : fM, f));
+      p = f;
+    }
     g[1] = 1.0;
     double beta = -e(1), P = -e(2), fb = beta;
     cd fd = D[1];
@@ -99,7 +108,7 @@ __global__ __launch_bounds__(64 * kLWaves, 4) void k_lstep(LStepArgs A) {
     b.UD = rfma(-e1, fd, D[0]);
     b.DB = eM * beta;
     b.DA = eM * eM * g[M - 1];
-    b.DD = rmul(eM, D[M - 1]);
+    b.DD = rmul(eM, cadd(p, D[M - 1]));
   }
   sb[wave][lane] = b;
   __syncthreads();
@@ -134,7 +143,7 @@ __global__ __launch_bounds__(64 * kLWaves, 4) void k_lstep(LStepArgs A) {
   }
   __syncthreads();
   const cd pJ = jpsi[wave][lane];
-  cd hi = jpsi[wave + 1][lane];
+  const cd pM = jpsi[wave + 1][lane];
   bool bad = false;
   auto put = [&](int i, cd f) {
     const cd p = irot(-i, f);
@@ -152,16 +161,13 @@ __global__ __launch_bounds__(64 * kLWaves, 4) void k_lstep(LStepArgs A) {
       D[i] = rfma(-beta, pJ, D[i]);
     }
   }
-  cd y = rfma(-(e(M) * g[M - 1]), hi, D[M - 1]);
+  cd y = pM;
 #pragma unroll
   for (int i = M - 1; i >= 1; --i) {
-    const cd lo = i > 1 ? rfma(-(e(i) * g[i > 1 ? i - 1 : 1]), y, D[i > 1 ? i - 1 : 1]) : pJ;
-    put(i, rfma(e(i), lo, rfma(-e(i + 1), hi, y)));
-    hi = y;
-    y = lo;
+    y = rfma(-(e(i + 1) * g[i]), y, D[i]);
+    put(i, y);
   }
-  // row 0: 2 u - f, f still in D[0]
-  put(0, mk(fma(2.0, y.x, -D[0].x), fma(2.0, y.y, -D[0].y)));
+  put(0, pJ);
   if (__any(bad) && lane == 0) atomicOr(A.status, 1);
 }
 

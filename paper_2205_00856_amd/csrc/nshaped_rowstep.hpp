@@ -1,23 +1,24 @@
 // A Crank-Nicolson step of a batch of contiguous systems in one pass (gfx950, FP64 complex).
 //
 // A workgroup takes a tile of T = 64 W M rows of one system: a whole system, or one of its tiles.
-// The step solves T y = psi on rows scaled by i / kappa (those of k_window) and takes psi' =
-// 2 y - T y = y - i tau H y, whose large part is y itself (as 2 y - T y in one product the error
-// after 60 steps, kappa = 0.33, was 7.7e-15 instead of 4.3e-15; exact half-steps and solves leave
-// 3.8e-15).  Its solve is that of k_window: every lane reduces its M rows, lv binary levels join 2^lv lanes, after
-// which the joint lines are decoupled in every real potential (the host takes lv from the bound),
-// and each joint takes its own two slots, those across wavefronts through LDS.  Against k_tile
-// (levels over the whole workgroup, the upper six in one wavefront between two barriers) a tile
-// has lv levels, one barrier, no edge rows, and 128 registers or fewer.
+// Its rows and its solve are those of k_window: every lane reduces its M rows, lv binary levels join
+// 2^lv lanes, after which the joint lines are decoupled in every real potential (the host takes lv
+// from the bound), and each joint takes its own two slots, those across wavefronts through LDS.
+// Against k_tile (levels over the whole workgroup, the upper six in one wavefront between two
+// barriers) a tile has lv levels, one barrier, one edge row, and 104 registers or fewer.  The forms
+// T y = psi, psi' = 2 y - psi or y - i tau H y need no edge row, but their rounding errors are larger:
+// 1.7 times after 60 steps at kappa = 0.33, and 1.1 times in the second form.
 //
 // Tiles of a longer system exchange the slots of their first and last block through lines in
 // memory, as in k_tile<PH_LINK>: word by word, all-ones words marking what has not arrived, two
 // buffers in turn.  k_rowstep_fix runs the tiles whose wait reached its bound, from the lines, and
-// makes systems with a non-finite result all NaN.
+// makes systems with a non-finite row all NaN.  In place: a tile stores only when both neighbours
+// have published, so after the one before has loaded its edge row here; a tile that is left keeps
+// the edge row that it has loaded.
 //
 // Bound by memory (40 bytes a row): 4096 systems of 4096 rows 138 -> 132 us (5.1 TB/s), 1000 of
-// 1531 rows 23.5 -> 17.6, 10^4 of 300 rows 49.6 -> 31 us; systems of several tiles, before in two
-// passes: 64 of 65536 rows 65 -> 38 us, 2^24 rows 222 -> 131 us.
+// 1531 rows 23.5 -> 17.8, 10^4 of 300 rows 49.6 -> 31 us; systems of several tiles, before in two
+// passes: 64 of 65536 rows 65 -> 33 us, 2^24 rows 222 -> 131 us.
 #pragma once
 #include "nshaped_windows.hpp"
 
@@ -38,6 +39,7 @@ struct RowStepArgs {
   double* lk;  // lines: [2][lk_n][8]
   int64_t lk_n;
   int *st, *done, *bad;  // as in k_colstep
+  cd* edge;              // of a tile left to the fix: psi of the row after its last one
   int* status;
   int spin;  // polls of a line before its tile is left
 };
@@ -86,6 +88,7 @@ struct RowStepSmem {
   cd buf[W][kBytes / 16];
   cd ua[W], da[W], ud[W], dd[W];  // a wavefront's first block's U slot, its last one's D slot
   int bad[W], ok[2];
+  cd edge;  // psi of the row after the tile
 };
 
 // Four doubles of a line (two complex values) to or from memory, by lanes 0 .. 3 of a wavefront.
@@ -128,12 +131,12 @@ __device__ __forceinline__ void rowstep_run(const RowStepArgs& A, RowStepSmem<M,
   cd* buf = sm.buf[wave];
   double* bufd = reinterpret_cast<double*>(buf);
   RowNode* nodes = reinterpret_cast<RowNode*>(buf);
-  const double ik = 1.0 / A.kap;
+  const double kap = A.kap;
   const cd zero = czero();
   const bool multi = A.ntiles > 1;
 
   // ---- loads (coalesced), transposed to lane blocks
-  cd D[M];
+  cd D[M], zM;  // psi; its row J + M
   double va[M];
   {
     cd raw[M];
@@ -144,6 +147,7 @@ __device__ __forceinline__ void rowstep_run(const RowStepArgs& A, RowStepSmem<M,
     };
     const cd* gp = A.in + sys * A.bs + row0;
     const double* gv = A.V + sys * A.vbs + row0;
+    cd edge = sel(true, gp[IN || w0 + 64 * M < nloc ? w0 + 64 * M : nloc - 1], zero);
 #pragma unroll
     for (int k = 0; k < M; ++k) raw[k] = sel(true, gp[row(k)], zero);
 #pragma unroll
@@ -155,13 +159,20 @@ __device__ __forceinline__ void rowstep_run(const RowStepArgs& A, RowStepSmem<M,
     }
 #pragma unroll
     for (int k = 0; k < M; ++k) buf[S::addr(1 + 64 * k + lane)] = raw[k];
+    if (multi && wave == W - 1 && tile + 1 < A.ntiles) {
+      // (in place, the next tile may have stored by the time of the fix)
+      if constexpr (FIX) edge = A.edge[gt];
+      else if (lane == 0) sm.edge = edge;
+    }
+    if (lane == 0) buf[S::addr(S::QN - 1)] = edge;
     wave_sync();
 #pragma unroll
     for (int j = 0; j < M; ++j) {
-      const cd p = buf[S::addr(lane * M + j + 1)];
-      D[j] = mk(-ik * p.y, ik * p.x);
+      D[j] = buf[S::addr(lane * M + j + 1)];
       if constexpr (!IN) D[j] = csel(J + j < nloc, D[j], zero);
     }
+    zM = buf[S::addr(lane * M + M + 1)];
+    if constexpr (!IN) zM = csel(J + M < nloc, zM, zero);
     wave_sync();
     // the diagonal in the loads' order, where a potential of its own costs no second transposition
 #pragma unroll
@@ -173,7 +184,7 @@ __device__ __forceinline__ void rowstep_run(const RowStepArgs& A, RowStepSmem<M,
         const double l = (double)(A.l0 + sys);
         v += l * (l + 1.0) / (2.0 * r * r);
       }
-      bufd[S::addr(1 + 64 * k + lane)] = wdiag(A.tau * (A.idx2 + v), A.kap, ik);
+      bufd[S::addr(1 + 64 * k + lane)] = wdiag(A.tau, A.idx2, v);
     }
     wave_sync();
 #pragma unroll
@@ -190,24 +201,36 @@ __device__ __forceinline__ void rowstep_run(const RowStepArgs& A, RowStepSmem<M,
   WBlk b;
   WRhs<1> c;
   {
-    cd g = crecip(mk(va[1], ik));
-    cd beta = cpl(1, g);
-    D[1] = cmul(D[1], g);
-    cd fb = beta, fd = D[1];
+    cd p = D[0];  // psi of the row before (rows past the end hold zero and have no right-hand side)
+    D[0] = wrhs(va[0], kap, p, D[1]);
+    if constexpr (!IN) D[0] = csel(J < nloc, D[0], zero);
+    cd h = zero, beta = zero, fb = zero, fd = zero;
 #pragma unroll
-    for (int i = 2; i < M; ++i) {
-      g = crecip(csub(mk(va[i], ik), cpl(i, g)));
-      D[i] = cmul(csub(D[i], cpl(i, D[i - 1])), g);
-      fd = cfms(beta, D[i], fd);
-      const cd bi = cpl(i, cneg(cmul(beta, g)));
-      fb = cfms(beta, bi, fb);
-      beta = bi;
+    for (int i = 1; i < M; ++i) {
+      cd d = wrhs(va[i], kap, D[i], cadd(p, i + 1 < M ? D[i + 1 < M ? i + 1 : i] : zM));
+      if constexpr (!IN) d = csel(J + i < nloc, d, zero);
+      p = D[i];
+      if (i == 1) {
+        const cd g = crecip(mk(-va[1], 1.0));
+        h = rmul(kap, g);
+        D[1] = cmul(d, g);
+        fb = beta = cpl(1, h);
+        fd = D[1];
+      } else {
+        const cd g = crecip(rfms(kap, cpl(i, h), mk(-va[i], 1.0)));
+        h = rmul(kap, g);
+        D[i] = cmul(rfms(kap, cpl(i, D[i - 1]), d), g);
+        fd = cfms(beta, D[i], fd);
+        const cd bi = cpl(i, cneg(cmul(beta, h)));
+        fb = cfms(beta, bi, fb);
+        beta = bi;
+      }
     }
-    b.UA = csub(mk(va[0], ik), fb);
-    b.C = cpl(M, cneg(beta));
-    b.DA = cpl(M, cneg(g));
-    c.UD[0] = csub(D[0], fd);
-    c.DD[0] = cpl(M, cneg(D[M - 1]));
+    b.UA = rfms(kap, fb, mk(-va[0], 1.0));
+    b.C = cpl(M, rmul(-kap, beta));
+    b.DA = cpl(M, rmul(-kap, h));
+    c.UD[0] = rfms(kap, fd, D[0]);
+    c.DD[0] = cpl(M, rmul(-kap, cadd(p, D[M - 1])));
   }
   // a non-finite row of the block shows in its U slot
   bool bad = __any(!cfinite(b.UA) || !cfinite(c.UD[0]));
@@ -273,7 +296,10 @@ __device__ __forceinline__ void rowstep_run(const RowStepArgs& A, RowStepSmem<M,
         A.st[2 + (1 - e)] = 0;
       }
     }
-    if (!ok) return;
+    if (!ok) {
+      if (threadIdx.x == 0) A.edge[gt] = sm.edge;
+      return;
+    }
   }
   cd qA = lane_get(b.DA, (lane - sp) & 63), qD = lane_get(c.DD[0], (lane - sp) & 63);
   qA = csel(lane < sp, lA, qA);
@@ -289,31 +315,24 @@ __device__ __forceinline__ void rowstep_run(const RowStepArgs& A, RowStepSmem<M,
   rlevel_down<2>(pJ, pM, nodes, lane);
   rlevel_down<1>(pJ, pM, nodes, lane);
 
-  // ---- the pivots again (the empty asm hides that they are the same), y upwards and
-  // psi' = 2 y - T y = y - i tau H y; row J's right-hand side is still in D[0]
+  // ---- the pivots again (the empty asm hides that they are the same), psi' upwards
 #pragma unroll
   for (int j = 1; j < M; ++j) asm volatile("" : "+v"(va[j]));
   {
-    cd g[M];
-    g[1] = crecip(mk(va[1], ik));
-    cd beta = cpl(1, g[1]);
+    cd h[M];
+    h[1] = rmul(kap, crecip(mk(-va[1], 1.0)));
+    cd beta = cpl(1, h[1]);
     D[1] = cfms(beta, pJ, D[1]);
 #pragma unroll
     for (int i = 2; i < M; ++i) {
-      g[i] = crecip(csub(mk(va[i], ik), cpl(i, g[i - 1])));
-      beta = cpl(i, cneg(cmul(beta, g[i])));
+      h[i] = rmul(kap, crecip(rfms(kap, cpl(i, h[i - 1]), mk(-va[i], 1.0))));
+      beta = cpl(i, cneg(cmul(beta, h[i])));
       D[i] = cfms(beta, pJ, D[i]);
     }
-    cd hi = pM, y = cfms(g[M - 1], pM, D[M - 1]);
+    cd y = pM;
 #pragma unroll
-    for (int i = M - 1; i >= 1; --i) {
-      const cd lo = i > 1 ? cfms(g[i > 1 ? i - 1 : 1], y, D[i > 1 ? i - 1 : 1]) : pJ;
-      const cd s = mk(fma(va[i], y.x, lo.x + hi.x), fma(va[i], y.y, lo.y + hi.y));
-      D[i] = mk(fma(-A.kap, s.y, y.x), fma(A.kap, s.x, y.y));
-      hi = y;
-      y = lo;
-    }
-    D[0] = mk(fma(-A.kap, D[0].y, 2.0 * y.x), fma(A.kap, D[0].x, 2.0 * y.y));
+    for (int i = M - 1; i >= 1; --i) D[i] = y = cfms(h[i], y, D[i]);
+    D[0] = pJ;
   }
   if (FIX) bad = A.bad[(int64_t)e * (A.lk_n / A.ntiles) + sys] != 0;
   bool inf = false;

@@ -17,14 +17,13 @@
 // them).  No window waits for another and a step touches no memory: s steps cost one read of
 // the state and the potential and one write.
 //
-// A step solves T w = i tau H psi and takes psi' = psi - 2 w: (1 - i tau H) = T - 2 i tau H, so
-// T^-1 (1 - i tau H) psi = psi - 2 T^-1 i tau H psi.  The rounding errors of the solve are errors
-// of w, the change of the state, and not of the state itself: against T y = psi and
-// psi' = 2 y - psi, which saves 4 of 24 operations per row (200 steps of 65536 rows: 260 us, here
-// 277), the error after 175 steps of 5806 rows at kappa = 0.33 is 4.8e-15 instead of 2.4e-14.
-// With a field a row's diagonal is rounded as a' - (tau / kappa) x E, not as tau (1/dx^2 + V +
-// x E): against the coefficients before their rounding both forms leave the same errors (5.7e-14
-// and 6.0e-14 after 150 steps at kappa = 1.25, nearly all from the rounding of 1/dx^2).
+// A step is T psi' = (1 - i tau H) psi with the coefficients and the right-hand side of the other
+// forms in their order of operations (cn_rows), so its rounding errors are theirs.  Forms with fewer
+// operations were less exact: T y = psi and psi' = 2 y - psi saves 4 of 26 per row (200 steps of
+// 65536 rows: 260 us), but leaves 2.4e-14 instead of 4.9e-15 after 175 steps of 5806 rows at
+// kappa = 0.33; rows divided by kappa (off-diagonals 1) and psi' = psi - 2 w, T w = i tau H psi, saves
+// 2, but its rounded quotients leave up to 1.35 times the error after those 200 steps, and rough states
+// twice the error from kappa = 1 on.
 // Inside the window the solve is the nested partition (Sec. 4): every lane reduces its M rows in
 // the RD form (reduce_block_rd), and LV binary levels join 2^LV lane blocks.  Blocks of M * 2^LV
 // rows couple their two joint lines by less than 2^-66 of the diagonal (the host takes LV from
@@ -49,10 +48,11 @@ struct WinArgs {
   int64_t vr, halo;  // window t starts at row t * vr; its results hold `halo` rows from a cut end
   double vscale, tau, kap, idx2;
   int nst;
-  // NR = 2: dV_j += acc Im(conj(lambda_j) mu_j) summed over the steps, and per step k and
+  // NR = 2: dV_j += acc Im(conj(lambda_j) mu_j) summed over the steps (lambda and mu twice the means
+  // of a step's two gradients and states), and per step k and
   // wavefront the sum of xg_j times the same term (acc without vscale) in part[k * nparts + ...]
   double* dV;
-  double acc_dV, acc_dE;  // factors: of the term in dV, of tau x_j times the term in dE
+  double acc_dV, acc_dE;  // factors: of the term in dV, of x_j times the term in dE
   double* part;
   int64_t nparts;
   int* status;
@@ -74,16 +74,15 @@ struct WinEnd {
   int64_t vbs;
 };
 
-// The rows are multiplied by i / kappa, which makes the off-diagonals 1: row j reads
-//     w_{j-1} + a'_j w_j + w_{j+1} = psi_{j-1} + Re(a'_j) psi_j + psi_{j+1},
-//     a' = -v / kappa + i / kappa,
-// v the imaginary part of T's diagonal.  The first row of a block has its right-hand side split
-// like its diagonal: psi_{j-1} is in the D slot of the block before.  T is symmetric, so a
-// reduced block has one coupling C instead of two (UC = DB), and the products of Table 1's
-// multipliers that JU needs are the beta of the RD rows with the other sign: with g_i the
-// reciprocal pivots, beta_1 = g_1, beta_i = -beta_{i-1} g_i, gamma_i = g_i and the forward sum of
-// reduce_block_rd is
-//     w_{J+1} = D_1 - sum_{k >= 2} beta_{k-1} D_k - (beta_1 - sum_{k >= 2} beta_{k-1} beta_k) w_J
+// The rows are multiplied by i, which makes the off-diagonals real: with v the imaginary part of T's
+// diagonal, row j reads
+//     kappa y_{j-1} + (i - v_j) y_j + kappa y_{j+1} = (i + v_j) psi_j - kappa (psi_{j-1} + psi_{j+1}).
+// The first row of a block has its right-hand side split like its diagonal: -kappa psi_{j-1} is in
+// the D slot of the block before.  T is symmetric, so a reduced block has one coupling C instead of
+// two (UC = DB), and the products of Table 1's multipliers that JU needs are the beta of the RD rows
+// with the other sign: with g_i the reciprocal pivots and h_i = kappa g_i, beta_1 = h_1,
+// beta_i = -beta_{i-1} h_i, gamma_i = h_i and the forward sum of reduce_block_rd is
+//     y_{J+1} = D_1 - sum_{k >= 2} beta_{k-1} D_k - (beta_1 - sum_{k >= 2} beta_{k-1} beta_k) y_J
 //     + ...
 struct WBlk {
   cd UA, C, DA;
@@ -92,10 +91,14 @@ template <int NR>
 struct WRhs {
   cd UD[NR], DD[NR];
 };
-// Re(a') = -v / kappa, ik = 1 / kappa, to the last bit: its error is that of every step.
-__device__ __forceinline__ double wdiag(double v, double kap, double ik) {
-  const double q = v * ik;
-  return -fma(fma(-q, kap, v), ik, q);
+// The imaginary part of T's diagonal, in cn_rows' order: its rounding is that of the other forms.
+__device__ __forceinline__ double wdiag(double tau, double idx2, double v) {
+#pragma clang fp contract(off)
+  return tau * (idx2 + v);
+}
+// The right-hand side of a row with the sum s of its neighbours, in cn_rows' order.
+__device__ __forceinline__ cd wrhs(double v, double kap, cd z, cd s) {
+  return mk(fma(v, z.x, fma(-kap, s.x, -z.y)), fma(v, z.y, fma(-kap, s.y, z.x)));
 }
 // An eliminated joint line: the reciprocal of its pivot, its couplings to the left and right
 // neighbours and the scaled row (B, C) that the way down applies.
@@ -238,9 +241,9 @@ __device__ __forceinline__ void window_run(const WinArgs& A, WinSmem<M, W, NR, X
   double* keep = reinterpret_cast<double*>(dl + 64);
 
   // ---- loads (coalesced), transposed to lane blocks through the staging buffer
-  const double ik = 1.0 / A.kap;
+  const double kap = A.kap;
   cd z[NR][M], zM[NR];  // the state; its row J + M, which the next lane (or wavefront) owns
-  double va[M];  // real part of a' without the field
+  double va[M];  // imaginary part of T's diagonal; with a field, V
   auto row = [&](int k) {
     const int r = w0 + 64 * k + lane;
     return IN ? r : (r < nloc ? r : nloc - 1);
@@ -282,15 +285,14 @@ __device__ __forceinline__ void window_run(const WinArgs& A, WinSmem<M, W, NR, X
       if constexpr (!IN) zM[r] = csel(J + M < nloc, zM[r], czero());
       wave_sync();
     }
-    const double c = -A.tau * ik;  // of the field's term
 #pragma unroll
     for (int k = 0; k < M; ++k) bufd[S::addr(1 + 64 * k + lane)] = rv[k];
     wave_sync();
 #pragma unroll
     for (int j = 0; j < M; ++j) {
-      const double v = A.tau * (A.idx2 + A.vscale * bufd[S::addr(lane * M + j + 1)]);
-      va[j] = -v / A.kap;  // to the last bit: its error is that of every step
-      if constexpr (!IN) va[j] = J + j < nloc ? va[j] : 0.0;
+      const double v = A.vscale * bufd[S::addr(lane * M + j + 1)];
+      va[j] = XG ? v : wdiag(A.tau, A.idx2, v);
+      if constexpr (!IN) va[j] = J + j < nloc ? va[j] : (XG ? -A.idx2 : 0.0);
     }
     wave_sync();
     if constexpr (XG) {
@@ -299,7 +301,7 @@ __device__ __forceinline__ void window_run(const WinArgs& A, WinSmem<M, W, NR, X
       wave_sync();
 #pragma unroll
       for (int j = 0; j < M; ++j) {
-        xt[j] = c * bufd[S::addr(lane * M + j + 1)];
+        xt[j] = bufd[S::addr(lane * M + j + 1)];
         if constexpr (!IN) xt[j] = J + j < nloc ? xt[j] : 0.0;
       }
       wave_sync();
@@ -335,24 +337,27 @@ __device__ __forceinline__ void window_run(const WinArgs& A, WinSmem<M, W, NR, X
     for (int j = 0; j < M; ++j) acc[j] = 0.0;
   }
   auto pot = [&](int j, double E) {
-    if constexpr (XG) return fma(keep[(M + j) * 64 + lane], E, keep[j * 64 + lane]);
+    if constexpr (XG)
+      return wdiag(A.tau, A.idx2, fma(keep[(M + j) * 64 + lane], E, keep[j * 64 + lane]));
     return va[j];
   };
-  auto diag = [&](int j, double E) { return mk(pot(j, E), ik); };
+  auto diag = [&](int j, double E) { return mk(-pot(j, E), 1.0); };
   // RD of the matrix, JD and JU
   auto reduce_matrix = [&](double E, WBlk& b) {
     g[1] = crecip(diag(1, E));
-    beta[1] = cpl(1, g[1]);
+    cd h = rmul(kap, g[1]);
+    beta[1] = cpl(1, h);
     cd fb = beta[1];
 #pragma unroll
     for (int i = 2; i < M; ++i) {
-      g[i] = crecip(csub(diag(i, E), cpl(i, g[i - 1])));
-      beta[i] = cpl(i, cneg(cmul(beta[i - 1], g[i])));
+      g[i] = crecip(rfms(kap, cpl(i, h), diag(i, E)));
+      h = rmul(kap, g[i]);
+      beta[i] = cpl(i, cneg(cmul(beta[i - 1], h)));
       fb = cfms(beta[i - 1], beta[i], fb);
     }
-    b.UA = csub(diag(0, E), fb);
-    b.C = cpl(M, cneg(beta[M - 1]));
-    b.DA = cpl(M, cneg(g[M - 1]));
+    b.UA = rfms(kap, fb, diag(0, E));
+    b.C = cpl(M, rmul(-kap, beta[M - 1]));
+    b.DA = cpl(M, rmul(-kap, h));
   };
   auto reduce_rhs = [&](double E, cd (&D)[NR][M], WRhs<NR>& c) {
 #pragma unroll
@@ -360,18 +365,17 @@ __device__ __forceinline__ void window_run(const WinArgs& A, WinSmem<M, W, NR, X
       auto rhs = [&](int i) {
         const cd hi = i + 1 < M ? z[r][i + 1 < M ? i + 1 : i] : zM[r];
         const cd s = i > 0 ? cadd(cpl(i, z[r][i > 0 ? i - 1 : 0]), hi) : hi;
-        const double u = pot(i, E);
-        return mk(fma(u, z[r][i].x, s.x), fma(u, z[r][i].y, s.y));
+        return wrhs(pot(i, E), kap, z[r][i], s);
       };
       D[r][1] = cmul(rhs(1), g[1]);
       cd fd = D[r][1];
 #pragma unroll
       for (int i = 2; i < M; ++i) {
-        D[r][i] = cmul(csub(rhs(i), cpl(i, D[r][i - 1])), g[i]);
+        D[r][i] = cmul(rfms(kap, cpl(i, D[r][i - 1]), rhs(i)), g[i]);
         fd = cfms(beta[i - 1], D[r][i], fd);
       }
-      c.UD[r] = csub(rhs(0), fd);
-      c.DD[r] = cpl(M, csub(z[r][M - 1], D[r][M - 1]));
+      c.UD[r] = rfms(kap, fd, rhs(0));
+      c.DD[r] = cpl(M, rmul(-kap, cadd(z[r][M - 1], D[r][M - 1])));
     }
   };
   WBlk b;
@@ -475,26 +479,25 @@ __device__ __forceinline__ void window_run(const WinArgs& A, WinSmem<M, W, NR, X
     if constexpr (LV > 2) wlevel_down<4, NR>(pJ, pM, nodes, dl, lane);
     if constexpr (LV > 1) wlevel_down<2, NR>(pJ, pM, nodes, dl, lane);
     if constexpr (LV > 0) wlevel_down<1, NR>(pJ, pM, nodes, dl, lane);
-    // ---- the rows of the block, upwards, and psi' = psi - 2 w
+    // ---- the rows of the block, upwards
     {
       double part = 0.0;
-      cd w[NR], y[NR];
+      cd y[NR];
 #pragma unroll
-      for (int r = 0; r < NR; ++r) {
-        w[r] = pM[r];
-        zM[r] = mk(fma(-2.0, w[r].x, zM[r].x), fma(-2.0, w[r].y, zM[r].y));
-      }
+      for (int r = 0; r < NR; ++r) zM[r] = pM[r];
 #pragma unroll
       for (int i = M - 1; i >= 0; --i) {
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
-          w[r] = i > 0 ? cfms(g[i > 0 ? i : 1], w[r], cfms(beta[i > 0 ? i : 1], pJ[r], D[r][i > 0 ? i : 1]))
-                       : pJ[r];
-          if constexpr (NR > 1) y[r] = csub(z[r][i], w[r]);
-          z[r][i] = mk(fma(-2.0, w[r].x, z[r][i].x), fma(-2.0, w[r].y, z[r][i].y));
+          const cd w = i < M - 1 ? z[r][i < M - 1 ? i + 1 : i] : pM[r];
+          const cd n = i > 0 ? cfms(g[i > 0 ? i : 1], rmul(kap, w),
+                                    cfms(beta[i > 0 ? i : 1], pJ[r], D[r][i > 0 ? i : 1]))
+                             : pJ[r];
+          if constexpr (NR > 1) y[r] = cadd(z[r][i], n);
+          z[r][i] = n;
         }
         if constexpr (NR > 1) {
-          // psi - w of the state is (psi_k + psi_k+1) / 2, that of the gradient is lambda
+          // twice (psi_k + psi_k+1) / 2 of the state, twice lambda of the gradient
           const double q = y[1].x * y[0].y - y[1].y * y[0].x;
           acc[i] += q;
           if constexpr (XG) {
