@@ -874,8 +874,9 @@ WinPlan window_plan(int64_t n, int64_t batch, double kap, int64_t m, int nr, boo
         vr = T - 2 * halo;
         nwin = (n - 2 * halo + vr - 1) / vr;
       }
+      // (launches of fewer than 2^32 threads, k_window_end's of 256 per system among them)
       const double nwg = (double)batch * (double)nwin;
-      if (nwg > 2147483647.0) continue;
+      if (nwg * (double)(64 * W) > 4294967295.0 || (double)batch * 256.0 > 4294967295.0) continue;
       const double rows = (double)n * (double)batch;
       const double mem = (nwg * (double)T * (16.0 * nr + 8.0) + rows * 16.0 * nr) / 4.5e6;
       const double q = std::ceil(nwg / (W < 4 ? 1024.0 / (double)W : 256.0)) * (W < 4 ? 1 : W / 4);
@@ -1636,7 +1637,8 @@ cn_status run_colstep(cn_handle_t h, Plan* P, const UserArgs& u, int ci, hipStre
 }
 
 // The tile of a one-pass step of contiguous systems, or -1: the shortest that holds a system, for
-// longer ones 2048 rows; the off-diagonal has to decouple within a wavefront.
+// longer ones 2048 rows; the off-diagonal has to decouple within a wavefront, and the workgroups,
+// all along x, have to make fewer than 2^32 threads (2^26 short systems take k_tile's grid).
 int rowstep_cfg(Plan* P, double kap) {
   if (kap != P->row_kap) {
     P->row_kap = kap;
@@ -1646,7 +1648,8 @@ int rowstep_cfg(Plan* P, double kap) {
         const Cfg c = nsk::kRowStepCfgs[i];
         if (P->row_mem ? c.T() != kRowTile : c.T() < P->row_n) continue;
         const int lv = window_levels(kap, c.M);
-        if (lv < 0) continue;
+        if (lv < 0 || (P->row_n + c.T() - 1) / c.T() * P->row_batch > UINT32_MAX / (64 * c.W))
+          continue;
         P->row_cfg = i;
         P->row_lv = lv;
         break;
