@@ -2164,8 +2164,7 @@ cn_status launch_window(nsd::WinArgs& a, const WinPlan& w, int64_t batch, int nr
 }
 // The end of a sequence on windows: the lines of systems with a mark become NaN, the marks zero.
 cn_status launch_window_end(const nsd::WinArgs& a, int64_t batch, const WinIo* out, double* dV,
-                            hipStream_t s) {
-  nsd::WinEnd e{};
+                            hipStream_t s, nsd::WinEnd e = nsd::WinEnd{}) {
   e.bad = a.bad;
   e.n = a.n;
   for (int r = 0; r < 2; ++r) {
@@ -2257,7 +2256,12 @@ cn_status run_windows(cn_handle_t h, const Plan* P, const cn_layout* L, const cn
   WinIo e[2];
   e[0].out = psi;
   e[0].obs = L->batch_stride;
-  return launch_window_end(a, L->batch, e, nullptr, s);
+  nsd::WinEnd c{};
+  c.ckpt = ckpt ? ckpt + P->span : nullptr;
+  c.nck = (nsteps - 1) / K;
+  c.cspan = P->span;
+  c.cbs = L->batch_stride;
+  return launch_window_end(a, L->batch, e, nullptr, s, c);
 }
 
 // The reverse mode (propagate_adjoint_impl) on windows: state and gradient go backwards together,

@@ -203,7 +203,8 @@ __global__ void k_radial_coupling(AuxArgs A) {
 
 // The end of a sequence on windows: one non-finite value makes its whole line non-finite in exact
 // steps, which the windows that it did not reach do not see.  Workgroup s fills the arrays of a
-// marked system s with NaN (dV if either mark is set) and clears the mark.
+// marked system s with NaN (dV if either mark is set), of its checkpoints those that hold a
+// non-finite value, and clears the mark.
 __global__ __launch_bounds__(256) void k_window_end(WinEnd A) {
   const int64_t s = blockIdx.x;
   const int m = A.bad[s];
@@ -214,6 +215,14 @@ __global__ __launch_bounds__(256) void k_window_end(WinEnd A) {
       for (int64_t i = threadIdx.x; i < A.n; i += 256) A.x[r][s * A.bs[r] + i] = mk(nan, nan);
   if (A.dV)
     for (int64_t i = threadIdx.x; i < A.n; i += 256) A.dV[s * A.vbs + i] = nan;
+  if ((m & 1) && A.ckpt)
+    for (int64_t k = 0; k < A.nck; ++k) {
+      cd* p = A.ckpt + k * A.cspan + s * A.cbs;
+      int bad = 0;
+      for (int64_t i = threadIdx.x; i < A.n; i += 256) bad |= !cfinite(p[i]);
+      if (__syncthreads_or(bad))
+        for (int64_t i = threadIdx.x; i < A.n; i += 256) p[i] = mk(nan, nan);
+    }
   __syncthreads();
   if (threadIdx.x == 0) A.bad[s] = 0;
 }

@@ -72,6 +72,10 @@ struct WinEnd {
   int64_t bs[2];
   double* dV;
   int64_t vbs;
+  // checkpoints after the first one (which holds the input): elements between them and between
+  // their systems
+  cd* ckpt;
+  int64_t nck, cspan, cbs;
 };
 
 // The rows are multiplied by i, which makes the off-diagonals real: with v the imaginary part of T's
