@@ -1720,9 +1720,10 @@ bool link_turn(Plan* P) {
 cn_status run_plan(cn_handle_t h, Plan* P, const UserArgs& u, hipStream_t s,
                    void* ws_base = nullptr) {
   char* ws = (char*)(ws_base ? ws_base : h->ws);
-  // plain steps in one pass (the lines of several tiles belong to the plan: a run on another
-  // workspace may overlap one on this)
-  if ((P->col || P->row) && !ws_base && !u.rhs && !u.acc_pa && !u.dxs) {
+  // Plain steps in one pass, which need no workspace.  The lines of several tiles belong to the
+  // plan; the one run that overlaps another (the reverse mode's recompute on the second workspace)
+  // overlaps steps that accumulate, which do not take this form.
+  if ((P->col || P->row) && !u.rhs && !u.acc_pa && !u.dxs) {
     const double kap = std::fabs((0.5 * u.dt) * 0.5 * (1.0 / (u.dx * u.dx)));
     const int ci = P->col ? colstep_cfg(P, kap) : rowstep_cfg(P, kap);
     if (ci >= 0)
