@@ -314,9 +314,9 @@ def main():
         "norm_after": norm,
     }
 
+    ex = {}
     if not args.no_extra:
         ex = extras(torch, np, cn, workloads, dev)
-        result["extra"] = ex
 
         def get(leg, key):
             v = ex.get(leg, {})
@@ -334,7 +334,15 @@ def main():
             "differentiated_loss": get("differentiated", "parity_rel_loss"),
             "differentiated_fd_64": get("differentiated", "fd_rel_l2_64"),
         }
-    print(json.dumps(result), flush=True)
+    emit(result, ex)
+
+
+def emit(result, legs):
+    """The other workloads' results on lines of their own, then the headline as one JSON line, short
+    enough for a reader that keeps the end of the output."""
+    for name, leg in legs.items():
+        print(f"leg {name}: {json.dumps(leg)}", flush=True)
+    print(json.dumps({**result, "legs": list(legs)}), flush=True)
 
 
 def large_system(torch, np, cn, dev, sweep=True, oracle_parity=True):
