@@ -223,9 +223,9 @@ cn_status cn_rhs(cn_handle_t handle, const cn_layout* layout, const cn_operator*
  * explicit half-step fused into the reduction sweep (Sec. 5.3).  E is the field of this
  * step, used on both sides.  psi_out may alias psi_in.  Interleaved batches (batch_stride 1, real
  * potential, one dx) run in one pass over memory where the joint lines of their tiles are
- * decoupled in every real potential (kappa up to about 1.1; see cn_tridiag_solve); uniform
+ * decoupled in every real potential (kappa up to 1.2; see cn_tridiag_solve); uniform
  * batches of unit element stride do so with the joint lines inside their tiles as well (kappa up
- * to about 4.6). */
+ * to 4.7). */
 cn_status cn_step(cn_handle_t handle, const cn_layout* layout, const cn_operator* op, double E,
                   const void* psi_in, void* psi_out, cn_stream_t stream);
 

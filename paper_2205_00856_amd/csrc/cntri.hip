@@ -18,6 +18,7 @@
 
 #include "../../include/cntri.h"
 #include "kern_table.hpp"
+#include "decay_bound.hpp"
 #include "nshaped_kernels.hpp"
 #include "nshaped_colstep.hpp"
 #include "nshaped_lstep.hpp"
@@ -198,39 +199,6 @@ struct Launch {
           o_hin = -1;
   int64_t o_hout2 = -1;  // second edge-row array of a Crank-Nicolson first pass (PH_FUSE chains)
 };
-
-// Minimum of f over eta in (0, hi) by golden-section search (f has one minimum there).
-template <typename F>
-double min_over(double hi, const F& f) {
-  const double g = 0.6180339887498949;
-  double a = 0.0, b = hi, x1 = b - g * (b - a), x2 = a + g * (b - a), f1 = f(x1), f2 = f(x2);
-  for (int i = 0; i < 48; ++i) {
-    if (f1 < f2) {
-      b = x2;
-      x2 = x1;
-      f2 = f1;
-      x1 = b - g * (b - a);
-      f1 = f(x1);
-    } else {
-      a = x1;
-      x1 = x2;
-      f1 = f2;
-      x2 = a + g * (b - a);
-      f2 = f(x2);
-    }
-  }
-  return std::min(f1, f2);
-}
-double eta_max(double kap) { return kap > 0.0 ? std::min(8.0, std::asinh(0.5 / kap)) : 8.0; }
-
-// Whether two joint lines B rows apart are decoupled to 2^-66 in every real potential: their
-// coupling kappa^2 (T^-1)_{1,m} against a diagonal of real part at least 1.
-bool decoupled(double kap, double B) {
-  return min_over(eta_max(kap), [&](double e) {
-    const double th = std::min(2.0 * kap * std::sinh(e), 1.0 - 1e-12);
-    return 2.0 * std::log(std::max(kap, 1e-30)) - e * (B - 2.0) - std::log(1.0 - th);
-  }) <= -66.0 * M_LN2;
-}
 
 struct Plan {
   std::vector<Launch> L;
@@ -811,23 +779,6 @@ bool windows_enabled() {
   return on;
 }
 
-// Rows that a cut of the line has to stay away after s steps (nshaped_windows.hpp): the smallest
-// D with r^s exp(-eta D) / (2 sinh eta) <= 2^-70 for some eta.
-double window_halo(double kap, int64_t s) {
-  return std::ceil(min_over(eta_max(kap), [&](double e) {
-    const double th = std::min(2.0 * kap * std::sinh(e), 1.0 - 1e-12);
-    return (70.0 * M_LN2 + (double)s * std::log((1.0 + th) / (1.0 - th)) -
-            std::log(2.0 * std::sinh(e))) / e;
-  })) + 1.0;
-}
-// Levels of lane blocks of M rows whose reduced systems are diagonal (joints M * 2^levels rows
-// apart).  More than 6 levels would leave the wavefront: -1.
-int window_levels(double kap, int M) {
-  for (int lv = nsk::kWinLevelMin; lv < nsk::kWinLevelMin + nsk::kNumWinLevel; ++lv)
-    if (decoupled(kap, (double)(M << lv))) return lv;
-  return -1;
-}
-
 // A piece of a sequence in launches of at most s steps each.
 struct WinPlan {
   int cfg = -1, lv = 0;
@@ -847,7 +798,7 @@ WinPlan window_plan(int64_t n, int64_t batch, double kap, int64_t m, int nr, boo
   for (int ci = 0; ci < nsk::kNumWinCfg; ++ci) {
     const Cfg cfg = nsk::kWinCfgs[nr - 1][ci];
     const int64_t W = cfg.W, T = cfg.T();
-    int lv = window_levels(kap, cfg.M);
+    int lv = decay_levels(kap, cfg.M, nsk::kWinLevelMin, nsk::kNumWinLevel);
     // one wavefront that holds the whole system runs all its levels: any off-diagonal
     if (lv < 0 && W == 1 && n <= T) lv = nsk::kWinLevelMin + nsk::kNumWinLevel - 1;
     if (lv < 0) continue;
@@ -1647,7 +1598,7 @@ int rowstep_cfg(Plan* P, double kap) {
       for (int i = 0; i < nsk::kNumRowStepCfg; ++i) {
         const Cfg c = nsk::kRowStepCfgs[i];
         if (P->row_mem ? c.T() != kRowTile : c.T() < P->row_n) continue;
-        const int lv = window_levels(kap, c.M);
+        const int lv = decay_levels(kap, c.M, nsk::kWinLevelMin, nsk::kNumWinLevel);
         if (lv < 0 || (P->row_n + c.T() - 1) / c.T() * P->row_batch > UINT32_MAX / (64 * c.W))
           continue;
         P->row_cfg = i;

@@ -24,7 +24,7 @@ constexpr Cfg kColCfgs[] = {{4, 8}, {8, 4}, {8, 8}, {4, 16}, {16, 4}, {8, 16}};
 constexpr int kNumColCfg = sizeof(kColCfgs) / sizeof(kColCfgs[0]);
 
 // One-pass steps of interleaved batches (k_colstep): T = W M rows of 64 neighbouring systems.  64
-// rows decouple up to kappa = 0.52, 128 up to 1.1 (4096 x 4096: 150 and 176 us; 128 rows as 8 per
+// rows decouple up to kappa = 0.56, 128 up to 1.2 (4096 x 4096: 150 and 176 us; 128 rows as 8 per
 // lane over 16 wavefronts 185).
 constexpr Cfg kColStepCfgs[] = {{8, 8}, {16, 8}};
 constexpr int kNumColStepCfg = sizeof(kColStepCfgs) / sizeof(kColStepCfgs[0]);
