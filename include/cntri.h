@@ -179,7 +179,11 @@ cn_status cn_reserve(cn_handle_t handle, const cn_layout* layout);
  * joint takes its own row of the reduced system alone.  The other tiles are solved by the launches
  * that follow, with the whole reduced system.  One matrix with several right-hand sides, cn_step
  * and the adjoint solves run the same way.
- * CN_LINK=0 in the environment turns it off. */
+ * What is dropped is below 2^-66 of the neighbouring joints, nothing in the norm of a solution, but
+ * everything to a part that is itself that small beside rows one tile away: the far response to
+ * a single right-hand side entry ends after a tile or two, and where it fell below 1e-20 of its
+ * source it is zero instead of exact to its own digits.  A partition set in the layout solves the
+ * whole reduced system as well, as does CN_LINK=0 in the environment, which turns the form off. */
 cn_status cn_tridiag_solve(cn_handle_t handle, const cn_layout* layout, const void* a,
                            const void* b, const void* c, const void* d, void* x,
                            cn_stream_t stream);
@@ -225,7 +229,9 @@ cn_status cn_rhs(cn_handle_t handle, const cn_layout* layout, const cn_operator*
  * potential, one dx) run in one pass over memory where the joint lines of their tiles are
  * decoupled in every real potential (kappa up to 1.2; see cn_tridiag_solve); uniform
  * batches of unit element stride do so with the joint lines inside their tiles as well (kappa up
- * to 4.7). */
+ * to 4.7).  Parts of a state that are below 2^-66 of the rows some hundred rows away are then
+ * exact to that fraction of those rows, not to their own digits (see cn_tridiag_solve for the
+ * form that keeps them). */
 cn_status cn_step(cn_handle_t handle, const cn_layout* layout, const cn_operator* op, double E,
                   const void* psi_in, void* psi_out, cn_stream_t stream);
 
@@ -243,10 +249,13 @@ cn_status cn_step(cn_handle_t handle, const cn_layout* layout, const cn_operator
  * partition run on independent windows instead where that is faster (off-diagonals kappa up to
  * about 4): a window of up to 4096 rows, cut off from its line, takes up to 128 steps in one
  * launch with its rows in registers, and only its rows beyond the reach of the cut (below 2^-70
- * of the state for any real potential) are stored.  Sequences whose single steps run in one pass
- * over the tiles (see cn_tridiag_solve; from 2^20 rows on, kappa up to 500 or a dx per system) run
- * as such steps instead of chained passes.  A non-finite value makes its whole line
- * non-finite, as in single steps.  CN_WINDOWS=0 in the environment turns the windows off. */
+ * of the state for any real potential) are stored; tails of a state below that are exact to that
+ * fraction of its norm, not to their own digits (a partition set in the layout, or CN_WINDOWS=0 in
+ * the environment, keeps the other forms).  Sequences whose single steps run in one pass over the
+ * tiles (see cn_tridiag_solve; from 2^20 rows on, with an absorbing potential from 2^18; kappa up
+ * to 500 or a dx per system) run as such steps instead of chained passes, unless the last such pass
+ * met joints that couple.  A non-finite value makes its whole line non-finite, checkpoints among
+ * them, as in single steps. */
 cn_status cn_propagate(cn_handle_t handle, const cn_layout* layout, const cn_operator* op,
                        int64_t nsteps, const double* E, void* psi, void* ckpt, int64_t K,
                        cn_stream_t stream);
@@ -408,9 +417,10 @@ cn_status cn_get_status(cn_handle_t handle, cn_stream_t stream);
 /* Version string and the plan chosen for a layout (for logs and benchmarks; with CN_LOG=1 in
  * the environment every plan is also described on stderr when it is built).  cn_mode 0: the
  * plan of cn_tridiag_solve; 1: the Crank-Nicolson plan (real potential), whose description ends
- * with how cn_propagate chains its steps: one fused pass per step, and whether the pass's last
- * workgroup also solves the reduced system of the tile joints (one system whose joints fit one
- * whole-system tile), which saves a launch per step; 2: the plan of the fused steps with an
+ * with the ways in which cn_propagate may run its steps, tried in this order by the operator's
+ * potential and off-diagonal: windows, single one-pass steps, or the chain of one fused pass per
+ * step, with whether the pass's last workgroup also solves the reduced system of the tile joints
+ * (one system whose joints fit one whole-system tile), which saves a launch per step; 2: the plan of the fused steps with an
  * absorbing potential (CN_ERR_UNSUPPORTED for a layout whose absorbing steps run
  * materialised).  Other values: CN_ERR_INVALID_ARG. */
 const char* cn_version(void);

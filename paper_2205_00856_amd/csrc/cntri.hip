@@ -2044,12 +2044,14 @@ UserArgs cn_args(const cn_operator* op, double E, const cd* in, cd* out) {
 // an off-diagonal for which the estimate beats the chained passes.  Those take per step about
 // 16 us of launches, or 6 us where one tile holds the system, plus the state and potential once
 // at 4 TB/s (48 and 40 bytes per row).
+bool windows_layout(const cn_layout* L, const Plan* P) {
+  return windows_enabled() && fuse_enabled() && P->t_bad >= 0 && !L->offsets &&
+         L->elem_stride == 1 && !L->partition && !L->rows_per_thread && !L->levels;
+}
 WinPlan sequence_windows(cn_handle_t h, const cn_layout* L, const cn_operator* op, const Plan* P,
                          int64_t m, int nr, bool field) {
   WinPlan none;
-  if (!windows_enabled() || !fuse_enabled() || P->t_bad < 0 || L->offsets || L->elem_stride != 1 ||
-      L->partition || L->rows_per_thread || L->levels || op->absorb || op->dx_per_system || m < 1)
-    return none;
+  if (!windows_layout(L, P) || op->absorb || op->dx_per_system || m < 1) return none;
   const double kap = std::fabs(0.5 * op->dt * 0.5 * (1.0 / (op->dx * op->dx)));
   char key[128];
   snprintf(key, sizeof(key), "%lld|%lld|%a|%lld|%d|%d", (long long)L->n, (long long)L->batch, kap,
@@ -2396,7 +2398,11 @@ cn_status cn_describe_plan(cn_handle_t h, const cn_layout* L, int cn_mode, char*
   if (st != CN_OK) return st;
   std::string d = P->desc;
   if (cn_mode) {
-    // how cn_propagate runs this plan
+    // how cn_propagate runs this plan: by the operator, the first of these that it takes
+    if (cn_mode == 1 && windows_layout(L, P))
+      d += "sequences on windows where estimated faster (off-diagonals up to about 4); ";
+    if (P->link)
+      d += "sequences in single one-pass steps (off-diagonals up to 500, joints decoupled); ";
     const FusePlan f = fuse_enabled() ? fuse_plan(P) : FusePlan();
     if (f.ok)
       d += f.inl ? "chain: one fused pass per step, reduced system solved in the pass; "

@@ -33,3 +33,21 @@ def test_chained_where_joints_couple():
     assert logged == []
     assert ((seq - one).norm() / one.norm()).item() <= steps * 16 * 4 * kap * 2.0 ** -53
     assert cn.get_status() == 0
+
+
+def test_description_names_the_forms_of_a_sequence():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2205_00856_amd as cn
+
+    def forms(L, **kw):
+        d = cn.describe_plan(L, **kw)
+        return ["windows" in d, "single one-pass steps" in d, "chain: one fused pass" in d]
+
+    n = (1 << 20) + 5
+    assert forms(cn.Layout.contiguous(n, 1), cn_mode=True) == [True, True, True]
+    assert forms(cn.Layout.contiguous(n, 1), absorbing=True) == [False, True, True]
+    assert forms(cn.Layout.contiguous(n, 1, partition=2048), cn_mode=True) == [False, False, True]
+    assert forms(cn.Layout.contiguous(300, 64), cn_mode=True) == [True, False, False]
+    assert forms(cn.Layout.interleaved(300, 64), cn_mode=True) == [False, False, False]
