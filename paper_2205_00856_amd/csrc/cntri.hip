@@ -1314,6 +1314,9 @@ cn_status plan_rowstep(const cn_layout* L, int src, Plan& P) {
   for (const Cfg& c : nsk::kRowStepCfgs) longest = std::max(longest, c.T());
   const int64_t tiles = (L->n + kRowTile - 1) / kRowTile * L->batch;
   if (tiles > INT32_MAX) return CN_OK;
+  // (shorter systems leave most of the smallest tile empty: 2^20 rows of 2 each 705 us by k_tile,
+  // 727 in one pass; of 32 each 50.6 and 49.9)
+  if (L->n < 32) return CN_OK;
   P.row_n = L->n;
   P.row_batch = L->batch;
   P.row_bs = L->batch_stride;
@@ -1717,6 +1720,9 @@ cn_status run_plan(cn_handle_t h, Plan* P, const UserArgs& u, hipStream_t s,
         l.fn = P->link_fn[1];
         if (P->link_rhs) a.nrhs = P->link_rhs;
         l.grid = dim3((unsigned)((P->link_n + 3) / 4));
+      } else if (l.cfg >= 0 && l.src == nsd::SRC_SLOTS && l.fn == g_kern[l.cfg][l.src][l.ph] &&
+                 nsk::tables().mid[l.cfg][l.ph]) {
+        l.fn = nsk::tables().mid[l.cfg][l.ph];
       }
     }
     cn_status st = log.begin([&](char* lab, size_t len) {

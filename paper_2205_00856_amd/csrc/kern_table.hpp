@@ -71,6 +71,7 @@ struct Tables {
   // a multi-tile system in one pass, and the launch for the tiles it leaves: [0: k_tile<PH_LINK>,
   // 1: k_tile_fix, 2: k_tile<PH_HAND> (Crank-Nicolson sources), 3: k_tile<PH_SUBST_LK>]
   const void* link[kNumCfg][kNumSrc][4];
+  const void* mid[kNumCfg][3];  // k_tile_mid, by phase
   // [0: k_mrhs_link, 1: k_mrhs_fix, 3: k_tile_mrhs<PH_SUBST_LK>]
   const void* mrhs_link[kNumCfg][4];
   const void* cols[kNumColCfg][kNumSrc][3];

@@ -11,6 +11,9 @@ void reg_one(Tables& t) {
   t.tile[I][S][nsd::PH_SINGLE] = (const void*)&nsd::k_tile<M, W, S, nsd::PH_SINGLE>;
   t.tile[I][S][nsd::PH_REDUCE] = (const void*)&nsd::k_tile<M, W, S, nsd::PH_REDUCE>;
   t.tile[I][S][nsd::PH_SUBST] = (const void*)&nsd::k_tile<M, W, S, nsd::PH_SUBST>;
+  t.mid[I][nsd::PH_SINGLE] = (const void*)&nsd::k_tile_mid<M, W, nsd::PH_SINGLE>;
+  t.mid[I][nsd::PH_REDUCE] = (const void*)&nsd::k_tile_mid<M, W, nsd::PH_REDUCE>;
+  t.mid[I][nsd::PH_SUBST] = (const void*)&nsd::k_tile_mid<M, W, nsd::PH_SUBST>;
 }
 template <int... I>
 void reg_range(Tables& t, std::integer_sequence<int, I...>) {

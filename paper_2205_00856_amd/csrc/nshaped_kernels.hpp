@@ -1132,15 +1132,22 @@ __device__ __forceinline__ void fuse_reduced_last(const KArgs& A, TileSmem<M, W>
 template <int M, int W, int SRC, int PH>
 __global__ __launch_bounds__(64 * W, (tile_min_waves<M, PH, SRC>())) void k_tile(KArgs A) {
   __shared__ TileSmem<M, W> sm;
-  if constexpr (SRC == SRC_SLOTS) {
-    if (link_idle(A)) return;
-  }
   const Geo G = geometry<PH>(A);
   tile_run<M, W, SRC, PH>(A, G, sm);
   if constexpr (PH == PH_FUSE && cn_src(SRC)) {
     __shared__ int last;
     if (A.inl_sync) fuse_reduced_last<M, W>(A, sm, last);
   }
+}
+
+// The levels of the reduced system after a PH_LINK pass.  (Kernels of their own: the test costs the
+// reduced systems of other plans 0.2 us a launch, 2 % of a chained step of 4 x 1869 rows.)
+template <int M, int W, int PH>
+__global__ __launch_bounds__(64 * W) void k_tile_mid(KArgs A) {
+  __shared__ TileSmem<M, W> sm;
+  if (link_idle(A)) return;
+  const Geo G = geometry<PH>(A);
+  tile_run<M, W, SRC_SLOTS, PH>(A, G, sm);
 }
 
 // The tiles that a PH_LINK pass has not finished, in second-pass form (psi_if: the reduced
