@@ -1595,15 +1595,26 @@ cn_status run_colstep(cn_handle_t h, Plan* P, const UserArgs& u, int ci, hipStre
 // all along x, have to make fewer than 2^32 threads (2^26 short systems take k_tile's grid).
 int rowstep_cfg(Plan* P, double kap) {
   if (kap != P->row_kap) {
+    const int least = nsk::kWinLevelMin, count = nsk::kNumWinLevel;
     P->row_kap = kap;
     P->row_cfg = -1;
-    if (kap >= 1e-60 && std::isfinite(kap))
+    if (kap >= 1e-60 && std::isfinite(kap) && decay_levels(kap, 8, least, count) >= 0)
       for (int i = 0; i < nsk::kNumRowStepCfg; ++i) {
         const Cfg c = nsk::kRowStepCfgs[i];
         if (P->row_mem ? c.T() != kRowTile : c.T() < P->row_n) continue;
-        const int lv = decay_levels(kap, c.M, nsk::kWinLevelMin, nsk::kNumWinLevel);
+        int lv = decay_levels(kap, c.M, least, count);
+        // a block that holds the whole system has nothing to decouple from (kappa = 4, systems of
+        // 64 rows: 29.2 us per 2^20 rows by k_tile, 41.5 in the 512-row tile whose blocks decouple)
+        if (c.W == 1 && c.T() >= P->row_n) {
+          int own = least;
+          while (((int64_t)c.M << own) < P->row_n) ++own;
+          lv = lv < 0 ? own : std::min(lv, own);
+        }
         if (lv < 0 || (P->row_n + c.T() - 1) / c.T() * P->row_batch > UINT32_MAX / (64 * c.W))
           continue;
+        // (five levels over a tile that is less than 7/16 full: 100 rows 21.8 us by k_tile's 128-row
+        // tile, 22.6 so; with four levels 21.1)
+        if (lv == 5 && P->row_n < 112 && c.M == 4) break;
         P->row_cfg = i;
         P->row_lv = lv;
         break;
@@ -1658,13 +1669,13 @@ cn_status run_rowstep(cn_handle_t h, Plan* P, const UserArgs& u, int ci, int64_t
   return CN_OK;
 }
 
-// Whether the next call on a linked plan takes one pass: not within 63 calls of a pass that left a
+// Whether the next call on a linked plan takes one pass: not within 255 calls of a pass that left a
 // tile, as far as its report has arrived.
 bool link_turn(Plan* P) {
   volatile int* hint = (volatile int*)P->link_hint;
   if (*hint) {
     *hint = 0;
-    P->link_skip = 63;
+    P->link_skip = 255;
   }
   if (P->link_skip == 0) return true;
   --P->link_skip;
@@ -1686,7 +1697,7 @@ cn_status run_plan(cn_handle_t h, Plan* P, const UserArgs& u, hipStream_t s,
   LogLaunch log{h, s, h->profiling && !capturing(s), {}};
   // One pass over the level-1 tiles.  A matrix whose joints couple makes it a first pass with
   // waits (2^24 rows 532 us against 448 in two passes; 253 where they decouple), so a plan whose
-  // last pass left a tile takes 63 calls in two passes before it tries again; the results are the
+  // last pass left a tile takes 255 calls in two passes before it tries again; the results are the
   // same bits (a first pass of Crank-Nicolson rows is PH_HAND then: with the slots of PH_REDUCE 43
   // of 2^18 rows differed in the last bit).  (The lines belong to the plan: a run on another
   // workspace may overlap one on this.)
@@ -2017,7 +2028,7 @@ cn_status cn_plan(cn_handle_t h, const cn_layout* L, const cn_operator* op, hipS
 // up to kappa = 1000 in a potential near zero (the inverse falls by exp(-1 / sqrt(2 kappa)) a row);
 // with larger ones the chain is the faster form, as it is where a deep potential makes the joints
 // couple (kappa = 250, V = -1 / dx^2: 190 us a step against 234 in two passes): a sequence that
-// follows a pass which left tiles is chained, once in 64 it tries again.
+// follows a pass which left tiles is chained, once in 256 it tries again.
 bool step_by_step(Plan* P, const cn_operator* op) {
   if (!P->link) return false;
   if (!op->dx_per_system &&

@@ -881,19 +881,19 @@ __device__ __forceinline__ void tile_core(const KArgs& A, const Geo& G, SM& sm, 
       pJ = A.psi_if[G.gt];
       const cd nxt = A.psi_if[(G.tile + 1 < G.ntile) ? G.gt + 1 : G.gt];
       pM = csel(G.tile + 1 < G.ntile, nxt, czero());
-      if (PH == PH_SUBST_LK && cfinite(pJ) && cfinite(pM)) {
+      if constexpr (PH == PH_SUBST_LK) {
         // the joints that a PH_LINK pass takes, where they decouple (a joint that is not finite
-        // makes the whole system so)
+        // makes the whole system so); without a branch around the loads, which wait once
         const bool lf = G.tile > 0, rt = G.tile + 1 < G.ntile;
         const cd* l = A.oD + 3 * (lf ? G.gt - 1 : G.gt);
         const cd* r = A.oU + 3 * (rt ? G.gt + 1 : G.gt);
         cd jJ, jM;
-        if (link_joints(blk, csel(lf, l[1], czero()), csel(lf, l[2], czero()),
-                        lf ? cmag(l[0]) : 0.0, csel(rt, r[0], czero()), csel(rt, r[2], czero()),
-                        rt ? cmag(r[1]) : 0.0, rt, jJ, jM)) {
-          pJ = jJ;
-          pM = jM;
-        }
+        bool ok = link_joints(blk, csel(lf, l[1], czero()), csel(lf, l[2], czero()),
+                              lf ? cmag(l[0]) : 0.0, csel(rt, r[0], czero()),
+                              csel(rt, r[2], czero()), rt ? cmag(r[1]) : 0.0, rt, jJ, jM);
+        ok = ok && cfinite(pJ) && cfinite(pM);
+        pJ = csel(ok, jJ, pJ);
+        pM = csel(ok, jM, pM);
       }
     }
   }
@@ -1531,6 +1531,16 @@ __device__ __forceinline__ bool mrhs_step(const KArgs& A, const Geo& G0, MrhsSme
     qJ = A.psi_if[G.gt];
     qM = A.psi_if[(G.tile + 1 < G.ntile) ? G.gt + 1 : G.gt];
   }
+  cd ql[3], qr[3];  // the neighbours' slots there
+  if constexpr (PH == PH_SUBST_LK) {
+    const cd* l = A.oD + 3 * (G.tile > 0 ? G.gt - 1 : G.gt);
+    const cd* rr = A.oU + 3 * (G.tile + 1 < G.ntile ? G.gt + 1 : G.gt);
+#pragma unroll
+    for (int f = 0; f < 3; ++f) {
+      ql[f] = l[f];
+      qr[f] = rr[f];
+    }
+  }
   cd vd[M + 2];
   transpose_in<M>(buf, lane, cur, zero, vd);
   if (r + 2 < A.nrhs && G.sys + 2 < A.batch)
@@ -1577,21 +1587,19 @@ __device__ __forceinline__ bool mrhs_step(const KArgs& A, const Geo& G0, MrhsSme
     } else {
       pJ = qJ;
       pM = csel(G.tile + 1 < G.ntile, qM, zero);
-      if (PH == PH_SUBST_LK && cfinite(pJ) && cfinite(pM)) {
+      if constexpr (PH == PH_SUBST_LK) {
         // the joints that a linked pass takes, where they decouple
         Blk b = top;
         b.UD = UD;
         b.DD = DD;
         const bool lf = G.tile > 0, rt = G.tile + 1 < G.ntile;
-        const cd* l = A.oD + 3 * (lf ? G.gt - 1 : G.gt);
-        const cd* rr = A.oU + 3 * (rt ? G.gt + 1 : G.gt);
         cd jJ, jM;
-        if (link_joints(b, csel(lf, l[1], zero), csel(lf, l[2], zero), lf ? cmag(l[0]) : 0.0,
-                        csel(rt, rr[0], zero), csel(rt, rr[2], zero), rt ? cmag(rr[1]) : 0.0, rt,
-                        jJ, jM)) {
-          pJ = jJ;
-          pM = jM;
-        }
+        bool ok = link_joints(b, csel(lf, ql[1], zero), csel(lf, ql[2], zero),
+                              lf ? cmag(ql[0]) : 0.0, csel(rt, qr[0], zero), csel(rt, qr[2], zero),
+                              rt ? cmag(qr[1]) : 0.0, rt, jJ, jM);
+        ok = ok && cfinite(pJ) && cfinite(pM);
+        pJ = csel(ok, jJ, pJ);
+        pM = csel(ok, jM, pM);
       }
     }
   }
