@@ -2229,7 +2229,7 @@ cn_status run_windows(cn_handle_t h, const Plan* P, const cn_layout* L, const cn
   e[0].obs = L->batch_stride;
   nsd::WinEnd c{};
   c.ckpt = ckpt ? ckpt + P->span : nullptr;
-  c.nck = (nsteps - 1) / K;
+  c.nck = ckpt ? (nsteps - 1) / K : 0;  // (K counts only with checkpoints)
   c.cspan = P->span;
   c.cbs = L->batch_stride;
   return launch_window_end(a, L->batch, e, nullptr, s, c);

@@ -53,3 +53,19 @@ def test_checkpoints_of_a_non_finite_line(value, resident):
         assert cn.get_status() == 1
         assert torch.isnan(dV[s]).all()
         assert all(torch.isfinite(dV[o]).all() for o in range(batch) if o != s)
+
+
+@pytest.mark.parametrize("n", [300, 20_011])
+def test_no_checkpoints_any_interval(n):
+    """Without checkpoints their interval has no meaning and may be 0."""
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2205_00856_amd as cn
+
+    g = np.random.default_rng(5)
+    V = torch.from_numpy(g.uniform(-2.0, 2.0, n)).cuda()
+    p = torch.from_numpy(workloads.complex_normal(g, n)).cuda()
+    want = cn.propagate(p.clone(), V, 0.1, 0.02, 7).clone()
+    assert torch.equal(cn.propagate(p.clone(), V, 0.1, 0.02, 7, K=0), want)
+    assert torch.equal(cn.propagate_resident(p.clone(), V, 0.1, 0.02, 7, K=0), want)
