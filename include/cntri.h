@@ -372,8 +372,8 @@ cn_status cn_propagate_adjoint_reconstruct(cn_handle_t handle, const cn_layout* 
  * layout whose partition and rows_per_thread are 0.  cn_mode = 0 times
  * cn_tridiag_solve(a, b, c, d -> x); cn_mode = 1 times cn_step(op, E, psi_in = d -> psi_out = x)
  * and ignores a, b, c; cn_mode = 2 times a sequence of 8 steps in place on x (copied from d
- * before each timing), as cn_propagate runs it (one fused pass per step over two-pass plans),
- * and reports the time per step -- the choice for sequences, where the per-step latency
+ * before each timing), as cn_propagate runs it (on windows, as a chain of fused passes or one by
+ * one), and reports the time per step -- the choice for sequences, where the per-step latency
  * decides.  Modes 1 and 2 tune the same automatic layout (the last call wins).  x is
  * overwritten and must not alias d.  A text report of the median timings is written to report
  * (may be NULL).  Not allowed during graph capture. */
@@ -420,9 +420,9 @@ cn_status cn_get_status(cn_handle_t handle, cn_stream_t stream);
  * with the ways in which cn_propagate may run its steps, tried in this order by the operator's
  * potential and off-diagonal: windows, single one-pass steps, or the chain of one fused pass per
  * step, with whether the pass's last workgroup also solves the reduced system of the tile joints
- * (one system whose joints fit one whole-system tile), which saves a launch per step; 2: the plan of the fused steps with an
- * absorbing potential (CN_ERR_UNSUPPORTED for a layout whose absorbing steps run
- * materialised).  Other values: CN_ERR_INVALID_ARG. */
+ * (one system whose joints fit one whole-system tile), which saves a launch per step; 2: the plan
+ * of the fused steps with an absorbing potential (CN_ERR_UNSUPPORTED for a layout whose absorbing
+ * steps run materialised).  Other values: CN_ERR_INVALID_ARG. */
 const char* cn_version(void);
 cn_status cn_describe_plan(cn_handle_t handle, const cn_layout* layout, int cn_mode, char* buf,
                            int64_t buflen);

@@ -2309,6 +2309,47 @@ cn_status run_windows_adjoint(cn_handle_t h, const Plan* P, const cn_layout* L,
   return launch_window_end(a, L->batch, e, dV, s);
 }
 
+// The steps of cn_propagate on fused kernels: on windows, as a chain of fused passes, or one by one.
+cn_status run_sequence(cn_handle_t h, Plan* P, const cn_layout* L, const cn_operator* op,
+                       int64_t nsteps, const double* E, cd* psi, cd* ckpt, int64_t K,
+                       hipStream_t s) {
+  cn_status st;
+  if (nsteps >= 1) {
+    const WinPlan w = sequence_windows(h, L, op, P, ckpt ? std::min(K, nsteps) : nsteps, 1,
+                                      E && op->xgrid);
+    if (w.cfg >= 0)
+      return run_windows(h, P, L, op, w, nsteps, E, psi, ckpt, K, s);
+  }
+  UserArgs u = cn_args(op, 0.0, psi, psi);
+  if (nsteps >= 2 && fuse_enabled() && !step_by_step(P, op)) {
+    const FusePlan f = fuse_plan(P);
+    if (f.ok) {
+      auto args = [&](int64_t k) {
+        UserArgs v = u;
+        v.E_mat = v.E_rhs = E ? E[k] : 0.0;
+        return v;
+      };
+      auto before = [&](int64_t k) -> cn_status {
+        if (ckpt && k % K == 0)
+          HIP_TRY(hipMemcpyAsync(ckpt + (k / K) * P->span, psi, P->span * sizeof(cd),
+                                 hipMemcpyDeviceToDevice, s));
+        return CN_OK;
+      };
+      return run_chain(h, P, f, nsteps, args, before, nullptr, s);
+    }
+  }
+  for (int64_t k = 0; k < nsteps; ++k) {
+    if (ckpt && k % K == 0) {
+      HIP_TRY(hipMemcpyAsync(ckpt + (k / K) * P->span, psi, P->span * sizeof(cd),
+                             hipMemcpyDeviceToDevice, s));
+    }
+    u.E_mat = u.E_rhs = E ? E[k] : 0.0;
+    st = run_plan(h, P, u, s);
+    if (st != CN_OK) return st;
+  }
+  return CN_OK;
+}
+
 }  // namespace
 
 // =============================================================================== C ABI
@@ -2587,40 +2628,7 @@ cn_status cn_propagate(cn_handle_t h, const cn_layout* L, const cn_operator* op,
     }
     return CN_OK;
   }
-  if (nsteps >= 1) {
-    const WinPlan w = sequence_windows(h, L, op, P, ckpt ? std::min(K, nsteps) : nsteps, 1,
-                                      E && op->xgrid);
-    if (w.cfg >= 0)
-      return run_windows(h, P, L, op, w, nsteps, E, (cd*)psi, (cd*)ckpt, K, s);
-  }
-  UserArgs u = cn_args(op, 0.0, (const cd*)psi, (cd*)psi);
-  if (nsteps >= 2 && fuse_enabled() && !step_by_step(P, op)) {
-    const FusePlan f = fuse_plan(P);
-    if (f.ok) {
-      auto args = [&](int64_t k) {
-        UserArgs v = u;
-        v.E_mat = v.E_rhs = E ? E[k] : 0.0;
-        return v;
-      };
-      auto before = [&](int64_t k) -> cn_status {
-        if (ckpt && k % K == 0)
-          HIP_TRY(hipMemcpyAsync((cd*)ckpt + (k / K) * P->span, psi, P->span * sizeof(cd),
-                                 hipMemcpyDeviceToDevice, s));
-        return CN_OK;
-      };
-      return run_chain(h, P, f, nsteps, args, before, nullptr, s);
-    }
-  }
-  for (int64_t k = 0; k < nsteps; ++k) {
-    if (ckpt && k % K == 0) {
-      HIP_TRY(hipMemcpyAsync((cd*)ckpt + (k / K) * P->span, psi, P->span * sizeof(cd),
-                             hipMemcpyDeviceToDevice, s));
-    }
-    u.E_mat = u.E_rhs = E ? E[k] : 0.0;
-    st = run_plan(h, P, u, s);
-    if (st != CN_OK) return st;
-  }
-  return CN_OK;
+  return run_sequence(h, P, L, op, nsteps, E, (cd*)psi, (cd*)ckpt, K, s);
 }
 
 // Resident propagation (k_resident): the configuration for n rows, or -1.  The smallest tile
@@ -2915,19 +2923,9 @@ cn_status cn_autotune(cn_handle_t h, const cn_layout* L, int cn_mode, const cn_o
       u.d = (const cd*)d;
     }
     u.x = (cd*)x;
-    // cn_mode 2: a sequence of kSeq steps in place on x from d, as cn_propagate runs it (one
-    // fused pass per step over two-pass plans)
-    const FusePlan fz = (cn_mode == 2 && fuse_enabled()) ? fuse_plan(P) : FusePlan();
-    auto seq = [&]() -> cn_status {
-      UserArgs v = u;
-      v.psi = (const cd*)x;
-      if (fz.ok) return run_chain(h, P, fz, kSeq, [&](int64_t) { return v; }, nullptr, nullptr, s);
-      for (int64_t k = 0; k < kSeq; ++k) {
-        const cn_status r = run_plan(h, P, v, s);
-        if (r != CN_OK) return r;
-      }
-      return CN_OK;
-    };
+    // cn_mode 2: a sequence of kSeq steps in place on x from d, as cn_propagate runs it
+    const std::vector<double> Es(kSeq, E);
+    auto seq = [&]() { return run_sequence(h, P, &L2, op, kSeq, Es.data(), (cd*)x, nullptr, 0, s); };
     std::vector<float> ts;
     bool ok = true;
     for (int r = 0; r < 7 && ok; ++r) {
