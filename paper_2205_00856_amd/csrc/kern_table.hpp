@@ -24,7 +24,7 @@ constexpr Cfg kColCfgs[] = {{4, 8}, {8, 4}, {8, 8}, {4, 16}, {16, 4}, {8, 16}};
 constexpr int kNumColCfg = sizeof(kColCfgs) / sizeof(kColCfgs[0]);
 
 // One-pass steps of interleaved batches (k_colstep): T = W M rows of 64 neighbouring systems.  64
-// rows decouple up to kappa = 0.56, 128 up to 1.2 (4096 x 4096: 150 and 176 us; 128 rows as 8 per
+// rows decouple up to kappa = 0.56, 128 up to 1.2 (4096 x 4096: 150 and 181 us; 128 rows as 8 per
 // lane over 16 wavefronts 185).
 constexpr Cfg kColStepCfgs[] = {{8, 8}, {16, 8}};
 constexpr int kNumColStepCfg = sizeof(kColStepCfgs) / sizeof(kColStepCfgs[0]);
@@ -38,11 +38,11 @@ constexpr Cfg kResCfgs[] = {{8, 1}, {8, 2}, {8, 4}};
 constexpr int kNumResCfg = sizeof(kResCfgs) / sizeof(kResCfgs[0]);
 
 // Windows of a sequence of steps (k_window), of the state alone and of state and gradient, and
-// 3 .. 6 levels joining the lane blocks.  8 rows per lane keep a state's rows and factors in 200
+// 3 .. 6 levels joining the lane blocks.  8 rows per lane keep a state's rows and factors in 180
 // registers, 2 wavefronts per SIMD; with the gradient they spill (2^20 rows and a field: 15.1 us
 // a step against 11.5 with 6 rows).  4 rows shorten the chain of a step that one wavefront per
 // SIMD runs alone (65536 rows and a field: 2.19 against 2.33 us, with the gradient 3.46 against
-// 3.84).
+// 3.84; these on rows divided by kappa, which took 1 to 3 % less).
 constexpr Cfg kWinCfgs[2][5] = {{{8, 1}, {8, 2}, {8, 4}, {8, 8}, {4, 4}},
                                 {{6, 1}, {6, 2}, {6, 4}, {6, 8}, {4, 4}}};
 constexpr int kNumWinCfg = 5;

@@ -17,9 +17,9 @@
 // k_colstep_fix makes all of it NaN, as exact steps would.
 //
 // Workgroups are numbered in bands of kColBand column groups, tile by tile: a wait is for the
-// workgroup kColBand ids later, which has to be resident beside this one (tiles of 16 rows per lane:
-// 256 at a time), and 4096 neighbouring systems keep the accesses long.  Numbered over all groups
-// of a wider batch the waits ran to their bound and every tile was left.
+// workgroup kColBand ids later, which has to be resident beside this one (with 16 rows per lane 256
+// are), and 4096 neighbouring systems keep the accesses long.  Numbered over all groups of a wider
+// batch the waits ran to their bound and every tile was left.
 //
 // Bound by memory: 40 bytes a row and the lines (8 KB written and 4 KB read per tile of 64 rows of
 // 64 systems, 160 KB of rows).  4096 x 4096 rows: 231 us in two passes (64 bytes a row, the second
