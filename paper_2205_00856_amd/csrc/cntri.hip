@@ -1358,12 +1358,13 @@ cn_status get_plan(cn_handle_t h, const cn_layout* L, int src, hipStream_t s, Pl
   int64_t rows = 0, span = 0;
   cn_status st = validate(L, rows, span);
   if (st != CN_OK) return st;
-  const std::string own_key = plan_key(L, src);
-  std::string key = own_key;
+  std::string key = plan_key(L, src);  // (of an uneven batch with its offsets: never copied)
+  bool own = true;  // the plan is the layout's own, not a tuned one
   cn_layout Lc;  // the cached tuned configuration of this layout's class, if any
   {
     auto tk = h->tuned.find(key);
     if (tk != h->tuned.end() && h->plans.count(tk->second)) {
+      own = tk->second == key;
       key = tk->second;
     } else if (!h->cache.empty() && L->partition == 0 && L->rows_per_thread == 0) {
       auto ck = h->cache.find(cache_class(L, src));
@@ -1377,6 +1378,7 @@ cn_status get_plan(cn_handle_t h, const cn_layout* L, int src, hipStream_t s, Pl
           if (validate(&Lc, r2, s2) == CN_OK) {
             L = &Lc;
             key = plan_key(L, src);
+            own = false;
           }
         }
       }
@@ -1417,7 +1419,7 @@ cn_status get_plan(cn_handle_t h, const cn_layout* L, int src, hipStream_t s, Pl
     if (st2 != CN_OK) return st2;
   }
   // a plan that stands in for another layout (tuned) is looked up each time
-  if (!L->offsets && key == own_key) h->last[src].store(P, std::memory_order_release);
+  if (!L->offsets && own) h->last[src].store(P, std::memory_order_release);
   *out = P;
   return CN_OK;
 }
