@@ -297,7 +297,8 @@ struct BatchDesc {
 
 // Shortest tile of a solve in one pass (plan_link).  From 2^16 rows on such tiles replace those of
 // 256 rows: 2^19 rows 28 -> 17 us, 10^5 rows x 16 right-hand sides 51 -> 27 us, 2^16 rows 17.4 ->
-// 15.4 us (18.4 in two passes, where the joints couple).
+// 15.4 us.  Where the joints couple, the tiles in two passes lose: 2^16 rows 18.4 us, 31 systems
+// of 5491 rows 17.5 -> 20.2, 40 right-hand sides of 6100 rows 19.7 -> 22.4.
 constexpr int64_t kLinkTile = 512;
 
 int multi_cfg(int64_t n, int64_t batch, const Knobs& k, int level, int src) {
